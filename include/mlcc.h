@@ -82,9 +82,9 @@ typedef enum {
                                      advancing all fronts; batches of rounds run as hipGraphs;
                                      per-kind kernel times in the stats */
     MLCC_SCHEDULE_PERSISTENT = 1  /* the default: one persistent launch (captured into a
-                                     hipGraph and run from it), (front, block) passes
-                                     from a device-side queue, each front advanced by the work
-                                     group that finishes its pass, no global rounds.  Same
+                                     hipGraph and run from it), passes over runs of a front's
+                                     blocks from a device-side queue, each front advanced by the
+                                     work group that finishes its pass, no global rounds.  Same
                                      results bit for bit; no front waits for the slowest pass
                                      of a round.  A launch in which no pass finishes for
                                      watchdog_ms (default 5 s) ends with MLCC_ERR_HIP. */

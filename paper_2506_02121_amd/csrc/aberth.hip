@@ -43,26 +43,25 @@ namespace mlcc {
 constexpr int RCP_STAR = 1;
 constexpr int RCP_ROOT = 1;
 
-// Streams the records p[0..n) through body(i, rec) for a one-wave work
-// group.  Tiles of 64 records (one per lane) are fetched with coalesced
+// Streams the records p[0..n) through body(i, rec) for one wave.  Tiles of 64 records (one per lane) are fetched with coalesced
 // vector loads, the next tile while the current one is consumed, converted
 // by cvt and parked in LDS, and read back with one wave-uniform (broadcast)
 // LDS read per record; tile_end() runs after each tile.  Vector loads retire
 // in order, so waiting for the older tile never waits for the prefetch
 // behind it.  Indices past n-1 are clamped on load, so nothing outside the
-// array is read.  `lds` holds two tiles.
+// array is read.  `lds` holds two tiles of the wave's own.
 template <class T, class L, class Cvt, class Body, class End>
 __device__ __forceinline__ void stream_tiles_ex(const T *__restrict__ p, int n, L *lds, Cvt &&cvt,
                                                 Body &&body, End &&tile_end)
 {
     if (n <= 0) return;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
     const int ntiles = (n + 63) >> 6;
     T reg = p[min(lane, n - 1)];
     for (int t = 0; t < ntiles; ++t) {
         L *buf = lds + ((t & 1) << 6);
         buf[lane] = cvt(reg);
-        __syncthreads();
+        wave_sync();
         if (t + 1 < ntiles) reg = p[min(((t + 1) << 6) + lane, n - 1)];
         const int base = t << 6;
         const int cnt = min(64, n - base);
@@ -74,7 +73,7 @@ __device__ __forceinline__ void stream_tiles_ex(const T *__restrict__ p, int n, 
         }
         tile_end();
     }
-    __syncthreads();
+    wave_sync();
 }
 
 struct Same {
@@ -784,6 +783,9 @@ template <class T> struct BlockCtx {
     bool valid, boundary;
     bool from_out;   // first pass of a row after a pass that ran several: the previous
                      // row's roots come from the output, not the iterate buffer
+    bool reseed, second;   // restart the row from its start values; from the second seeds
+    bool fast;       // root-root terms in FP32 (fast_roots_pass)
+    int32_t *count, *upd;   // the pass's totals: roots left open (or moving), updates made
     int64_t base_f, out_off, bnd_row_off;
     const T *stars;
     const double2 *zsrc;
@@ -792,14 +794,23 @@ template <class T> struct BlockCtx {
     double2 e;   // (1 - kappa_s) e^{-i phi} of the front's row
 };
 
+// Which FP64 Aberth passes take the root-root sum in FP32 (add_root_hl):
+// warm rows of a field solved in MLCC_FP64_R32.  Cold starts, where the
+// repulsion between the iterates steers global convergence from the seeds,
+// MLCC_FP64 and the mixed form's FP64 restarts keep it in FP64.
+__device__ __forceinline__ bool fast_roots_pass(const Front &fr, const Real &r)
+{
+    return r.root32 && fr.dir != 0 && fr.mode == PH_F64;
+}
+
+// Context of block q of front f, whose record is F (in LDS under the
+// persistent schedule); `count` and `upd` take the pass's totals.
 template <class T>
-__device__ __forceinline__ bool enter_fq(const RoundArgs<T> &A, int phase, int f, int q,
-                                         BlockCtx<T> &B)
+__device__ __forceinline__ void enter_fq(const RoundArgs<T> &A, const Front *F, int f, int q,
+                                         int32_t *count, int32_t *upd, BlockCtx<T> &B)
 {
     B.f = f;
     B.q = q;
-    const Front *F = A.fronts + B.f;
-    if (F->state != FRONT_ACTIVE || (phase >= 0 && F->phase != phase)) return false;
     const Real *R = A.reals + F->real;
     B.r = F->real;
     B.row = F->row;
@@ -807,6 +818,11 @@ __device__ __forceinline__ bool enter_fq(const RoundArgs<T> &A, int phase, int f
     B.vslot = F->blk0 + B.q;
     B.dir = F->dir;
     B.pred = (F->fresh && F->dir != 0 && F->hist >= 2) ? min(A.predictor, F->hist - 1) : 0;
+    B.reseed = F->reseed != 0;
+    B.second = F->seedvar > 0;
+    B.fast = fast_roots_pass(*F, *R);
+    B.count = count;
+    B.upd = upd;
     B.hist = F->hist;
     B.end_row = F->end_row;
     B.from_out = F->fresh == 2 && F->dir != 0;
@@ -833,11 +849,10 @@ __device__ __forceinline__ bool enter_fq(const RoundArgs<T> &A, int phase, int f
     B.bnd_row_off = R->bnd_off + (int64_t)max(F->bnd_slot, 0) * R->n_r;
     const double2 u = A.unit[B.row];
     B.e = make_double2(B.a * u.x, B.a * u.y);
-    B.lane = threadIdx.x;
+    B.lane = threadIdx.x & 63;
     B.k0 = B.q * 64;
     B.k = B.k0 + B.lane;
     B.valid = B.k < B.n_r;
-    return true;
 }
 
 // Block context of this work group in a round: (front, block) from bmap.
@@ -845,7 +860,10 @@ template <class T>
 __device__ __forceinline__ bool enter(const RoundArgs<T> &A, int phase, BlockCtx<T> &B)
 {
     const int2 fq = A.bmap[blockIdx.x];
-    return enter_fq(A, phase, fq.x, fq.y, B);
+    const Front *F = A.fronts + fq.x;
+    if (F->state != FRONT_ACTIVE || F->phase != phase) return false;
+    enter_fq(A, F, fq.x, fq.y, A.counts + fq.x, A.passupd + fq.x, B);
+    return true;
 }
 
 // Start of a new row's first pass for root k: extrapolation along its chain
@@ -887,15 +905,6 @@ __device__ __forceinline__ void put(const RoundArgs<T> &A, const BlockCtx<T> &B,
     }
 }
 
-// Which FP64 Aberth passes take the root-root sum in FP32 (add_root_hl):
-// warm rows of a field solved in MLCC_FP64_R32.  Cold starts, where the
-// repulsion between the iterates steers global convergence from the seeds,
-// MLCC_FP64 and the mixed form's FP64 restarts keep it in FP64.
-__device__ __forceinline__ bool fast_roots_pass(const Front &fr, const Real &r)
-{
-    return r.root32 && fr.dir != 0 && fr.mode == PH_F64;
-}
-
 // One FP64 Aberth pass of a block (the block context is set by enter()).
 // `tiles` holds two tiles of up to 32-byte records.
 template <bool EQUAL, bool FMM>
@@ -904,12 +913,12 @@ __device__ __forceinline__ void sweep_f64_pass(const RoundArgs<typename StarRec<
                                                double4 *tiles)
 {
     using T = typename StarRec<EQUAL>::T;
-    if (A.fronts[B.f].reseed) {
+    if (B.reseed) {
         // restart the row from its start values: the seeds z_i +- 1 for a
         // cold start, the previous row of the subchain otherwise.  The second
         // set for a stalled cold start: z_i +- i, and the extra roots of a
         // rectangular sheet turned by half their spacing.
-        const bool second = A.fronts[B.f].seedvar > 0;
+        const bool second = B.second;
         if (B.valid) {
             double2 z;
             if (B.dir == 0 && B.k >= 2 * B.n_stars) {   // a rectangular sheet's extra root
@@ -931,7 +940,7 @@ __device__ __forceinline__ void sweep_f64_pass(const RoundArgs<typename StarRec<
             B.nxt[B.base_f + B.k] = z;
         }
         const int n_valid = __popcll(__ballot(B.valid));
-        if (threadIdx.x == 0) atomicAdd(&A.counts[B.f], n_valid);
+        if (B.lane == 0) atomicAdd(B.count, n_valid);
         return;
     }
     const int lane = B.lane, k0 = B.k0, k = B.k, n_r = B.n_r, n_stars = B.n_stars;
@@ -1019,7 +1028,7 @@ __device__ __forceinline__ void sweep_f64_pass(const RoundArgs<typename StarRec<
                                      add_star_group<EQUAL, decltype(g)::value>(S, zr, zi, r);
                                  });
         }
-        if (!fast_roots_pass(A.fronts[B.f], A.reals[B.r])) {
+        if (!B.fast) {
             // the other roots in FP64, in groups outside the own block;
             // within it one at a time, skipping the root itself
             double2 *rtiles = reinterpret_cast<double2 *>(tiles);
@@ -1069,8 +1078,8 @@ __device__ __forceinline__ void sweep_f64_pass(const RoundArgs<typename StarRec<
         }
     }
     if (lane == 0) {
-        if (n_after) atomicAdd(&A.counts[B.f], n_after);
-        atomicAdd(&A.passupd[B.f], n_act);
+        if (n_after) atomicAdd(B.count, n_after);
+        atomicAdd(B.upd, n_act);
     }
 }
 
@@ -1220,8 +1229,8 @@ __device__ __forceinline__ void sweep_f32_pass(const RoundArgs<typename StarRec<
     const double mr = u.zr - zr, mi = u.zi - zi;
     const int n_moving = __popcll(__ballot(valid && !(mr * mr + mi * mi <= TOL_F32 * TOL_F32)));
     if (lane == 0) {
-        if (n_moving) atomicAdd(&A.counts[B.f], n_moving);
-        atomicAdd(&A.passupd[B.f], n_valid);
+        if (n_moving) atomicAdd(B.count, n_moving);
+        atomicAdd(B.upd, n_valid);
     }
 }
 
@@ -1505,7 +1514,7 @@ __device__ __forceinline__ void polish_pass(const RoundArgs<typename StarRec<EQU
     if (lane == 0) {
         A.vieta[2 * B.vslot] = make_double4(s1r, s1i, s2r, s2i);
         A.vieta[2 * B.vslot + 1] = make_double4(t_e, t_e2, t_a, t_a2);
-        if (n_after) atomicAdd(&A.counts[B.f], n_after);
+        if (n_after) atomicAdd(B.count, n_after);
     }
     int n_xsteps = 0;   // Newton steps this lane took in further rows
     const int xmax = A.xrows ? A.reals[B.r].xrows : 0;
@@ -1636,7 +1645,7 @@ __device__ __forceinline__ void polish_pass(const RoundArgs<typename StarRec<EQU
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) n_upd += __shfl_xor(n_upd, off, 64);
     if (n_steps < 0) n_upd += n_act;
-    if (lane == 0 && n_upd) atomicAdd(&A.passupd[B.f], n_upd);
+    if (lane == 0 && n_upd) atomicAdd(B.upd, n_upd);
     if constexpr (FMM) fmm_flush(A.fmm_tally, FMM_T_POLISH, ptl);
 }
 
@@ -2003,11 +2012,12 @@ __global__ void control_end(Control *__restrict__ ctl, const int32_t *__restrict
 // Persistent scheduler
 // ---------------------------------------------------------------------------
 //
-// One launch of as many single-wave work groups as fit on the chip.  Work
-// items are (front, block) passes in a device-side ring: a worker claims
-// the next slot, waits until it is filled, runs the pass the front's phase
-// asks for, and the worker that completes the last block of a front's pass
-// advances that front (advance_front) and queues its next pass, so fronts
+// One launch of as many work groups as fit on the chip.  Work items are
+// (front, task) passes in a device-side ring, a task being a run of the
+// front's blocks: a worker claims the next slot, waits until it is filled,
+// runs the pass the front's phase asks for, and the worker that completes the
+// last task of a front's pass advances that front (advance_front) and queues
+// its next pass, or runs it itself when the front makes one task, so fronts
 // move on independently instead of in global rounds.  Each front keeps its
 // own ping-pong parity; a cold start hands its converged centre row to its
 // partner by copying it into the partner's buffer.  No worker ever waits
@@ -2032,24 +2042,78 @@ struct PQueue {
 };
 // Slot sequence numbers are spread one per 64-byte line.
 constexpr int SEQ_STRIDE = 8;
+// Most waves of a work group of the persistent launch.
+constexpr int MAX_WORK_WAVES = 16;
 
-// Queues the bpf block passes of front f (whole wave).
-__device__ __forceinline__ void push_front(PQueue *q, int2 *tasks, unsigned long long *seq,
-                                           unsigned long long mask, int f, int bpf)
+// Tasks of a pass over a front of field r.
+__device__ __forceinline__ int task_count(const Real &r)
 {
+    return (((r.n_r + 63) >> 6) + r.chunk - 1) / r.chunk;
+}
+
+// Queues the n tasks of a pass of front f (whole wave).
+__device__ __forceinline__ void push_front(PQueue *q, int2 *tasks, unsigned long long *seq,
+                                           unsigned long long mask, int f, int n)
+{
+    const int lane = threadIdx.x & 63;
     unsigned long long base = 0;
-    if (threadIdx.x == 0) base = atomicAdd(&q->tail, (unsigned long long)bpf);
+    if (lane == 0) base = atomicAdd(&q->tail, (unsigned long long)n);
     base = __shfl(base, 0, 64);
-    for (int i = threadIdx.x; i < bpf; i += 64) tasks[(base + i) & mask] = make_int2(f, i);
-    // publishes the tasks and everything the wave wrote before them
+    for (int i = lane; i < n; i += 64) tasks[(base + i) & mask] = make_int2(f, i);
+    // publishes the tasks and everything the work group wrote before them
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    for (int i = threadIdx.x; i < bpf; i += 64)
+    for (int i = lane; i < n; i += 64)
         __hip_atomic_store(&seq[((base + i) & mask) * SEQ_STRIDE], base + i + 1,
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Waits until the wave's stores have reached L2, where a release fence of
+// another wave of the work group publishes them.
+__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Row sums of a polished row from its blocks' partial sums (slots of one
+// row), in row_sums' order (whole wave; every lane holds the result).
+__device__ __forceinline__ void sum_row(const double4 *__restrict__ v, int bpf, double4 *rs)
+{
+    double v0 = 0, v1 = 0, v2 = 0, v3 = 0, v4 = 0, v5 = 0, v6 = 0, v7 = 0;
+    for (int b = threadIdx.x & 63; b < bpf; b += 64) {
+        const double4 t = v[2 * b], u = v[2 * b + 1];
+        v0 += t.x; v1 += t.y; v2 += t.z; v3 += t.w;
+        v4 += u.x; v5 += u.y; v6 += u.z; v7 += u.w;
+    }
+    wave_sum(v0); wave_sum(v1); wave_sum(v2); wave_sum(v3);
+    wave_sum(v4); wave_sum(v5); wave_sum(v6); wave_sum(v7);
+    rs[0] = make_double4(v0, v1, v2, v3);
+    rs[1] = make_double4(v4, v5, v6, v7);
+}
+
+// What the waves of a work group share: the front it works on, the pass's
+// block cursor and totals, and what its first wave decided after the pass.
+struct WorkShare {
+    Front fr;
+    int32_t task_f, task_c;   // claimed task (task_f < 0: leave)
+    int32_t begin, end;       // blocks of the task
+    int32_t count, upd;       // the pass's totals over this task
+    int32_t go;               // the work group owns the front and runs its next pass
+    int32_t partner;          // front whose cold start just ended here (else -1)
+    int64_t src_off, dst_off;
+    int32_t src_par, dst_par;
+    // per phase, and [3] fast-root FP64 passes: updates, updates x N
+    unsigned long long upd_tot[4], star_tot[4];
+};
+
+// What bounds short passes is not their sums but what surrounds them: a
+// device saturates at ~12.6 M agent-scope release fences plus queue claims per
+// second, so with one 64-root block per claim the 1,000-star workload (32
+// blocks per front, ~700 k block passes) ran at that rate whatever its
+// kernels did.  A work group therefore has several waves and takes a task of
+// several blocks, dealt to its waves in turn: one claim, one fence and one
+// count per task.  A front that makes a single task is owned
+// by the work group that took it: its passes follow each other behind work
+// group barriers alone, the front record stays in LDS, and nothing crosses
+// XCDs until it is done or hands a cold start to its partner.
 template <bool EQUAL, bool FMM>
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(64 * MAX_WORK_WAVES)
 __attribute__((amdgpu_waves_per_eu(FMM ? MLCC_FMM_WAVES : MLCC_SWEEP_WAVES, 8)))
 aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ fronts_w,
                   PQueue *__restrict__ q, int2 *__restrict__ tasks,
@@ -2058,11 +2122,15 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
                   int32_t max_warm, unsigned long long stall_ticks)
 {
     using T = typename StarRec<EQUAL>::T;
-    __shared__ double4 tiles[128];
-    const int lane = threadIdx.x;
+    extern __shared__ double4 tiles_all[];   // two tiles of 64 records per wave
+    __shared__ WorkShare W;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
+    double4 *tiles = reinterpret_cast<double4 *>(reinterpret_cast<T *>(tiles_all) + wave * 128);
+    if (threadIdx.x < 4) W.upd_tot[threadIdx.x] = W.star_tot[threadIdx.x] = 0ull;
     for (;;) {
-        int tf = -1, tq = 0;
-        if (lane == 0) {
+        if (threadIdx.x == 0) {
+            int tf = -1, tq = 0;
             const unsigned long long t = atomicAdd(&q->head, 1ull);
             const unsigned long long *my = &seq[(t & mask) * SEQ_STRIDE];
             unsigned long long seen = load_relaxed(&q->progress);
@@ -2090,146 +2158,190 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
                 }
                 __builtin_amdgcn_s_sleep(2);
             }
+            W.task_f = tf;
+            W.task_c = tq;
         }
-        tf = __shfl(tf, 0, 64);
-        tq = __shfl(tq, 0, 64);
-        if (tf < 0) return;
-
-        BlockCtx<T> B;
-        if (enter_fq(A, -1, tf, tq, B)) {
-            const int ph = A.fronts[tf].phase;
-            if (ph == PH_F64)
-                sweep_f64_pass<EQUAL, FMM>(A, B, tiles);
-            else if (ph == PH_F32)
-                sweep_f32_pass<EQUAL, FMM>(A, B, tiles);
-            else
-                polish_pass<EQUAL, FMM>(A, B, tiles);
-        }
-        // the last block of the front's pass advances the front; every
-        // block publishes its writes before counting itself done
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        const Front *F = A.fronts + tf;
-        const Real *R = A.reals + F->real;
-        const int bpf = (R->n_r + 63) >> 6;
-        int last = 0;
-        if (lane == 0) last = atomicAdd(&fdone[tf], 1) + 1 == bpf;
-        last = __shfl(last, 0, 64);
-        if (!last) continue;
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        Front fr = fronts_w[tf];
-        double4 rs[2] = {make_double4(0, 0, 0, 0), make_double4(0, 0, 0, 0)};
-        if (fr.phase == PH_POLISH) {
-            double v0 = 0, v1 = 0, v2 = 0, v3 = 0, v4 = 0, v5 = 0, v6 = 0, v7 = 0;
-            for (int b = lane; b < bpf; b += 64) {
-                const double4 t = A.vieta[2 * (fr.blk0 + b)], u = A.vieta[2 * (fr.blk0 + b) + 1];
-                v0 += t.x; v1 += t.y; v2 += t.z; v3 += t.w;
-                v4 += u.x; v5 += u.y; v6 += u.z; v7 += u.w;
-            }
-            wave_sum(v0); wave_sum(v1); wave_sum(v2); wave_sum(v3);
-            wave_sum(v4); wave_sum(v5); wave_sum(v6); wave_sum(v7);
-            rs[0] = make_double4(v0, v1, v2, v3);
-            rs[1] = make_double4(v4, v5, v6, v7);
-        }
-        int partner = -1, state = FRONT_ACTIVE, finished = 0, xr = 0, dir0 = 0;
-        int64_t p_off = 0;
-        int p_par = 0;
-        if (lane == 0) {
-            fdone[tf] = 0;
-            const unsigned long long u = (unsigned)A.passupd[tf];
-            A.passupd[tf] = 0;
-            const unsigned long long us = u * (unsigned)R->n_stars;
-            if (fr.phase == PH_F64) {
-                atomicAdd(&A.ctl->updates, u);
-                atomicAdd(&A.ctl->star_updates, us);
-                if (fast_roots_pass(fr, *R)) {
-                    atomicAdd(&A.ctl->updates_fast, u);
-                    atomicAdd(&A.ctl->star_updates_fast, us);
-                }
-            } else if (fr.phase == PH_F32) {
-                atomicAdd(&A.ctl->updates_f32, u);
-                atomicAdd(&A.ctl->star_updates_f32, us);
-            } else {
-                atomicAdd(&A.ctl->polish_updates, u);
-                atomicAdd(&A.ctl->star_updates_polish, us);
-            }
-            const int32_t c = A.counts[tf];
-            A.counts[tf] = 0;
-            dir0 = fr.dir;
-            const int row0 = fr.row, ph0 = fr.phase;
-            partner = advance_front(fr, tf, c, rs, fronts_w, nullptr, 0, A.ctl, A.reals, A.unit,
-                                    max_cold, max_warm, A.predictor);
-            fr.par ^= 1;   // the pass wrote the other buffer
-            if (A.xrows && ph0 == PH_POLISH) {
-                // further rows the pass finished in every block (see polish_pass)
-                xr = A.xrows[tf];
-                A.xrows[tf] = R->xrows;
-                if (!(dir0 != 0 && fr.state == FRONT_ACTIVE && fr.phase == PH_POLISH &&
-                      fr.row == row0 + dir0))
-                    xr = 0;
-            }
-        }
-        // the further rows, in order, while their row identities hold
-        xr = __shfl(xr, 0, 64);
-        int moved = 0;
-        for (int x = 1; x <= xr; ++x) {
-            double v0 = 0, v1 = 0, v2 = 0, v3 = 0, v4 = 0, v5 = 0, v6 = 0, v7 = 0;
-            for (int b = lane; b < bpf; b += 64) {
-                const int64_t sl = 2 * ((int64_t)x * A.nvslots + fr.blk0 + b);
-                const double4 t = A.vieta[sl], u = A.vieta[sl + 1];
-                v0 += t.x; v1 += t.y; v2 += t.z; v3 += t.w;
-                v4 += u.x; v5 += u.y; v6 += u.z; v7 += u.w;
-            }
-            wave_sum(v0); wave_sum(v1); wave_sum(v2); wave_sum(v3);
-            wave_sum(v4); wave_sum(v5); wave_sum(v6); wave_sum(v7);
-            int ok = 0;
-            if (lane == 0) {
-                const double4 rx[2] = {make_double4(v0, v1, v2, v3), make_double4(v4, v5, v6, v7)};
-                if (row_identities_hold(*R, A.unit[fr.row], rx)) {
-                    row_converged(fr, tf, fronts_w, nullptr, 0, A.predictor);
-                    ok = 1;
+        __syncthreads();
+        const int tf = __builtin_amdgcn_readfirstlane(W.task_f);
+        if (tf < 0) break;
+        int tc = __builtin_amdgcn_readfirstlane(W.task_c);
+        constexpr int FRONT_WORDS = sizeof(Front) / 4;
+        static_assert(FRONT_WORDS <= 64 && sizeof(Front) % 4 == 0, "front copied by one wave");
+        if (wave == 0 && lane < FRONT_WORDS)
+            reinterpret_cast<int32_t *>(&W.fr)[lane] =
+                reinterpret_cast<const int32_t *>(fronts_w + tf)[lane];
+        for (;;) {   // passes over the front: one, or all of them while it is owned
+            if (wave == 0) {
+                wave_sync();
+                if (lane == 0) {
+                    const int c = A.reals[W.fr.real].chunk;
+                    const int bpf = (A.reals[W.fr.real].n_r + 63) >> 6;
+                    W.begin = tc * c;
+                    W.end = min((tc + 1) * c, bpf);
+                    W.count = 0;
+                    W.upd = 0;
                 }
             }
-            ok = __shfl(ok, 0, 64);
-            if (!ok) break;
-            moved = x;
-        }
-        if (lane == 0) {
-            if constexpr (!FMM) {
-                // the further rows the front keeps, one Newton step per root
-                // each, as the first pass of each row would have counted them
-                if (moved) {
-                    const unsigned long long ux = (unsigned long long)moved * (unsigned)R->n_r;
-                    atomicAdd(&A.ctl->polish_updates, ux);
-                    atomicAdd(&A.ctl->star_updates_polish, ux * (unsigned)R->n_stars);
+            __syncthreads();
+            const int end = __builtin_amdgcn_readfirstlane(W.end);
+            const int ph = __builtin_amdgcn_readfirstlane(W.fr.phase);
+            for (int blk = __builtin_amdgcn_readfirstlane(W.begin) + wave; blk < end; blk += waves) {
+                BlockCtx<T> B;
+                enter_fq(A, &W.fr, tf, blk, &W.count, &W.upd, B);
+                if (ph == PH_F64)
+                    sweep_f64_pass<EQUAL, FMM>(A, B, tiles);
+                else if (ph == PH_F32)
+                    sweep_f32_pass<EQUAL, FMM>(A, B, tiles);
+                else
+                    polish_pass<EQUAL, FMM>(A, B, tiles);
+            }
+            // every wave's stores have reached L2 before the first wave, which
+            // publishes them, leaves the barrier
+            wait_stores();
+            __syncthreads();
+            if (wave == 0) {
+                Front &fr = W.fr;
+                const Real *R = A.reals + fr.real;
+                const int bpf = (R->n_r + 63) >> 6;
+                const int nt = task_count(*R);
+                int last = 1;
+                if (nt > 1) {
+                    // the last task of the front's pass advances the front;
+                    // every task publishes its writes before counting itself
+                    if (lane == 0) {
+                        if (W.count) atomicAdd(&A.counts[tf], W.count);
+                        if (W.upd) atomicAdd(&A.passupd[tf], W.upd);
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                    if (lane == 0) last = atomicAdd(&fdone[tf], 1) + 1 == nt;
+                    last = __shfl(last, 0, 64);
+                    if (last) {
+                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                        if (lane == 0) {
+                            fdone[tf] = 0;
+                            W.count = load_relaxed(&A.counts[tf]);
+                            W.upd = load_relaxed(&A.passupd[tf]);
+                            A.counts[tf] = 0;
+                            A.passupd[tf] = 0;
+                        }
+                    }
+                }
+                int go = 0, partner = -1;
+                if (last) {
+                    double4 rs[2] = {make_double4(0, 0, 0, 0), make_double4(0, 0, 0, 0)};
+                    if (ph == PH_POLISH) sum_row(A.vieta + 2 * (int64_t)fr.blk0, bpf, rs);
+                    int finished = 0, xr = 0, dir0 = 0;
+                    if (lane == 0) {
+                        const unsigned long long u = (unsigned)W.upd;
+                        const unsigned long long us = u * (unsigned)R->n_stars;
+                        W.upd_tot[ph] += u;
+                        W.star_tot[ph] += us;
+                        if (ph == PH_F64 && fast_roots_pass(fr, *R)) {
+                            W.upd_tot[3] += u;
+                            W.star_tot[3] += us;
+                        }
+                        dir0 = fr.dir;
+                        const int row0 = fr.row;
+                        partner = advance_front(fr, tf, W.count, rs, fronts_w, nullptr, 0, A.ctl,
+                                                A.reals, A.unit, max_cold, max_warm, A.predictor);
+                        fr.par ^= 1;   // the pass wrote the other buffer
+                        if (A.xrows && ph == PH_POLISH) {
+                            // further rows the pass finished in every block (see polish_pass)
+                            xr = load_relaxed(&A.xrows[tf]);
+                            __hip_atomic_store(&A.xrows[tf], R->xrows, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+                            if (!(dir0 != 0 && fr.state == FRONT_ACTIVE && fr.phase == PH_POLISH &&
+                                  fr.row == row0 + dir0))
+                                xr = 0;
+                        }
+                    }
+                    // the further rows, in order, while their row identities hold
+                    xr = __shfl(xr, 0, 64);
+                    int moved = 0;
+                    for (int x = 1; x <= xr; ++x) {
+                        double4 rx[2];
+                        sum_row(A.vieta + 2 * ((int64_t)x * A.nvslots + fr.blk0), bpf, rx);
+                        int ok = 0;
+                        if (lane == 0 && row_identities_hold(*R, A.unit[fr.row], rx)) {
+                            row_converged(fr, tf, fronts_w, nullptr, 0, A.predictor);
+                            ok = 1;
+                        }
+                        ok = __shfl(ok, 0, 64);
+                        if (!ok) break;
+                        moved = x;
+                    }
+                    if (lane == 0) {
+                        if constexpr (!FMM) {
+                            // the further rows the front keeps, one Newton step per root
+                            // each, as the first pass of each row would have counted them
+                            if (moved) {
+                                const unsigned long long ux =
+                                    (unsigned long long)moved * (unsigned)R->n_r;
+                                W.upd_tot[PH_POLISH] += ux;
+                                W.star_tot[PH_POLISH] += ux * (unsigned)R->n_stars;
+                            }
+                        }
+                        // its first pass takes the previous row from the output
+                        if (moved) fr.fresh = 2;
+                        const int state = fr.state;
+                        if (state != FRONT_ACTIVE)
+                            finished = (state == FRONT_FAILED && dir0 == 0) ? 2 : 1;
+                        else
+                            go = task_count(*R) == 1 ? 1 : 2;
+                        if (partner >= 0) {
+                            W.src_par = fr.par;
+                            W.src_off = fr.it_off;
+                            W.dst_par = fronts_w[partner].par;
+                            W.dst_off = fronts_w[partner].it_off;
+                        }
+                    }
+                    wave_sync();
+                    go = __shfl(go, 0, 64);
+                    if (go != 1 && lane < FRONT_WORDS)   // it leaves this work group
+                        reinterpret_cast<int32_t *>(fronts_w + tf)[lane] =
+                            reinterpret_cast<const int32_t *>(&W.fr)[lane];
+                    if (lane == 0) {
+                        if (finished) atomicAdd(&q->done, finished);
+                        atomicAdd(&q->progress, 1ull);
+                    }
+                }
+                if (lane == 0) {
+                    W.go = go;
+                    W.partner = partner;
                 }
             }
-            if (moved) fr.fresh = 2;   // its first pass takes the previous row from the output
-            fronts_w[tf] = fr;
-            state = fr.state;
-            if (state != FRONT_ACTIVE) finished = (state == FRONT_FAILED && dir0 == 0) ? 2 : 1;
+            __syncthreads();
+            const int partner = W.partner, go = W.go;
             if (partner >= 0) {
-                p_off = fronts_w[partner].it_off;
-                p_par = fronts_w[partner].par;
+                // the partner starts from the converged centre row (copied before
+                // the front's own next pass is queued: the one after it
+                // overwrites this buffer)
+                const Real *R = A.reals + W.fr.real;
+                const double2 *src = (W.src_par ? A.iter1 : A.iter0) + W.src_off;
+                double2 *dst = (W.dst_par ? A.iter1 : A.iter0) + W.dst_off;
+                for (int i = threadIdx.x; i < R->n_r; i += blockDim.x) dst[i] = src[i];
+                wait_stores();
+                __syncthreads();
+                if (wave == 0) push_front(q, tasks, seq, mask, partner, task_count(*R));
             }
+            if (go == 2 && wave == 0)
+                push_front(q, tasks, seq, mask, tf, task_count(A.reals[W.fr.real]));
+            if (go != 1) break;
+            tc = 0;
         }
-        partner = __shfl(partner, 0, 64);
-        state = __shfl(state, 0, 64);
-        finished = __shfl(finished, 0, 64);
-        if (partner >= 0) {
-            // the partner starts from the converged centre row
-            p_off = __shfl(p_off, 0, 64);
-            p_par = __shfl(p_par, 0, 64);
-            const int cur_par = __shfl(fr.par, 0, 64);
-            const int64_t my_off = __shfl(fr.it_off, 0, 64);
-            const double2 *src = (cur_par ? A.iter1 : A.iter0) + my_off;
-            double2 *dst = (p_par ? A.iter1 : A.iter0) + p_off;
-            for (int i = lane; i < R->n_r; i += 64) dst[i] = src[i];
-            push_front(q, tasks, seq, mask, partner, bpf);
-        }
-        if (state == FRONT_ACTIVE) push_front(q, tasks, seq, mask, tf, bpf);
-        if (lane == 0) {
-            if (finished) atomicAdd(&q->done, finished);
-            atomicAdd(&q->progress, 1ull);
+        __syncthreads();   // the claim below overwrites what the waves just read
+    }
+    // the work group's share of the totals
+    if (threadIdx.x == 0) {
+        unsigned long long *dst[4][2] = {{&A.ctl->updates, &A.ctl->star_updates},
+                                         {&A.ctl->updates_f32, &A.ctl->star_updates_f32},
+                                         {&A.ctl->polish_updates, &A.ctl->star_updates_polish},
+                                         {&A.ctl->updates_fast, &A.ctl->star_updates_fast}};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (!W.upd_tot[k]) continue;
+            atomicAdd(dst[k][0], W.upd_tot[k]);
+            atomicAdd(dst[k][1], W.star_tot[k]);
         }
     }
 }
@@ -2342,6 +2454,43 @@ static int autotune_subchains(const std::vector<RealHost> &reals, int64_t m, boo
         }
     }
     return best_s;
+}
+
+// ---------------------------------------------------------------------------
+// Work groups of the persistent launch
+// ---------------------------------------------------------------------------
+
+// Workers beyond the tasks a launch can have at a time: they find nothing to
+// run and watch for a stall.
+constexpr int WATCHERS = 8;
+// Most blocks of a front whose passes one work group may own, and waves per
+// work group when the longest front has more.
+constexpr int OWN_MAX_BLOCKS = 8;
+#ifndef MLCC_WORK_WAVES
+#define MLCC_WORK_WAVES 4
+#endif
+
+// Waves per work group, and per field the blocks of a front that make one
+// task (Real::chunk).  Fronts of at most 8 blocks are owned, one wave per
+// block: a pass of so few blocks is shorter than the claim and the fences
+// (N = 10: 1.09 -> 0.31 ms per launch; N = 137, 5 blocks: 3.07 -> 1.08 ms, where
+// four waves and two tasks take 1.43).  Longer fronts go through the queue in
+// tasks of four blocks, one per wave: measured launches, ms, with 1 / 2 / 4 / 8
+// / 16 waves and as many blocks: rectangular field of 15 blocks 28.0 / 22.4 /
+// 16.3 / 20.1 / 17.7; N = 3,000 with multipole sums 148 / 132 / 126 / 127 / 139;
+// N = 6,000 FP64 1197 / 1139 / 1035 / 1042 / 1099; N = 10,000 mixed with
+// multipole sums 146 / 128 / 121 / 119 / 124.  More blocks per task than waves
+// lost everywhere (N = 1,000: 51 to 64 ms against 43), as did owning fronts
+// of several blocks per wave (51 ms).
+static int plan_workers(std::vector<Real> &rd)
+{
+    int64_t longest = 0;
+    for (const Real &R : rd) longest = std::max(longest, ceil_div(R.n_r, 64));
+    int waves = 1;
+    while (waves < longest && waves < OWN_MAX_BLOCKS) waves <<= 1;
+    if (longest > OWN_MAX_BLOCKS) waves = MLCC_WORK_WAVES;
+    for (Real &R : rd) R.chunk = waves;
+    return waves;
 }
 
 // ---------------------------------------------------------------------------
@@ -2582,6 +2731,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
             }
         }
     }
+    const int work_waves = plan_workers(rd);
     const int F = (int)fr.size();
     const int64_t nblocks = (int64_t)bmap.size();   // blocks of all fronts, in front order
     if (F > MAX_FRONTS || nblocks > 0x3fffffff)
@@ -2893,8 +3043,17 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
 
     // The persistent scheduler: one launch, fronts advance independently.
     auto run_persistent = [&]() -> mlcc_status {
+        int cus = 0, clock_khz = 0;
+        MLCC_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
+        MLCC_HIP(hipDeviceGetAttribute(&clock_khz, hipDeviceAttributeWallClockRate, c->device));
+        if (cus < 1 || clock_khz < 1) return fail(MLCC_ERR_HIP, "cannot size the persistent launch");
+        int64_t ntasks = 0;
+        for (int f = 0; f < F; ++f) {
+            const Real &R = rd[fr[f].real];
+            ntasks += ceil_div(ceil_div(R.n_r, 64), R.chunk);
+        }
         int64_t cap = 1024;
-        while (cap < 2 * nblocks) cap <<= 1;
+        while (cap < 2 * ntasks) cap <<= 1;
         const size_t o_tasks = (sizeof(PQueue) + 255) & ~(size_t)255;
         const size_t o_seq = o_tasks + (size_t)cap * sizeof(int2);
         const size_t o_fdone = o_seq + (size_t)cap * SEQ_STRIDE * sizeof(unsigned long long);
@@ -2911,7 +3070,8 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         std::vector<int2> t0;
         for (int f = 0; f < F; ++f) {
             if (fr[f].state != FRONT_ACTIVE) continue;
-            for (int64_t qb = 0; qb < ceil_div(rd[fr[f].real].n_r, 64); ++qb)
+            const Real &R = rd[fr[f].real];
+            for (int64_t qb = 0; qb < ceil_div(ceil_div(R.n_r, 64), R.chunk); ++qb)
                 t0.push_back(make_int2(f, (int)qb));
         }
         std::vector<unsigned long long> s0(t0.size() * SEQ_STRIDE, 0ull);
@@ -2932,18 +3092,22 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
             A.xrow_max = xrow_max;
             A.nvslots = (int32_t)nblocks;
         };
-        int cus = 0, per_cu = 0, clock_khz = 0;
-        MLCC_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
-        MLCC_HIP(hipDeviceGetAttribute(&clock_khz, hipDeviceAttributeWallClockRate, c->device));
         const void *kfn =
             equal ? (fmm_on ? reinterpret_cast<const void *>(&aberth_persistent<true, true>)
                             : reinterpret_cast<const void *>(&aberth_persistent<true, false>))
                   : (fmm_on ? reinterpret_cast<const void *>(&aberth_persistent<false, true>)
                             : reinterpret_cast<const void *>(&aberth_persistent<false, false>));
-        MLCC_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kfn, 64, 0));
-        if (cus < 1 || per_cu < 1 || clock_khz < 1)
-            return fail(MLCC_ERR_HIP, "cannot size the persistent launch");
-        const unsigned workers = (unsigned)(cus * per_cu);
+        const unsigned threads = 64u * (unsigned)work_waves;
+        const size_t lds = (size_t)work_waves * 128 * (equal ? sizeof(double2) : sizeof(double4));
+        if (lds + sizeof(WorkShare) > 65536)
+            MLCC_HIP(hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        int per_cu = 0;
+        MLCC_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kfn, (int)threads, lds));
+        if (per_cu < 1) return fail(MLCC_ERR_HIP, "cannot size the persistent launch");
+        // as many workers as fit, but hardly more than there are tasks at a time
+        // (the few beyond them watch for a stall)
+        const unsigned workers =
+            (unsigned)std::min<int64_t>((int64_t)cus * per_cu, ntasks + WATCHERS);
         // a worker gives up after watchdog_ms (default 5 s) in which no pass
         // finished anywhere
         const unsigned long long stall =
@@ -2960,12 +3124,12 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
                 A2.iter0 = c->iter[0].as<double2>();
                 A2.iter1 = c->iter[1].as<double2>();
                 if (fmm_on)
-                    hipLaunchKernelGGL((aberth_persistent<true, true>), dim3(workers), dim3(64), 0,
+                    hipLaunchKernelGGL((aberth_persistent<true, true>), dim3(workers), dim3(threads), lds,
                                        rs, A2, c->fronts.as<Front>(), dq, dtasks, dseq,
                                        (unsigned long long)(cap - 1), dfdone, F, max_cold, max_warm,
                                        stall);
                 else
-                    hipLaunchKernelGGL((aberth_persistent<true, false>), dim3(workers), dim3(64), 0,
+                    hipLaunchKernelGGL((aberth_persistent<true, false>), dim3(workers), dim3(threads), lds,
                                        rs, A2, c->fronts.as<Front>(), dq, dtasks, dseq,
                                        (unsigned long long)(cap - 1), dfdone, F, max_cold, max_warm,
                                        stall);
@@ -2976,12 +3140,12 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
                 A4.iter0 = c->iter[0].as<double2>();
                 A4.iter1 = c->iter[1].as<double2>();
                 if (fmm_on)
-                    hipLaunchKernelGGL((aberth_persistent<false, true>), dim3(workers), dim3(64), 0,
+                    hipLaunchKernelGGL((aberth_persistent<false, true>), dim3(workers), dim3(threads), lds,
                                        rs, A4, c->fronts.as<Front>(), dq, dtasks, dseq,
                                        (unsigned long long)(cap - 1), dfdone, F, max_cold, max_warm,
                                        stall);
                 else
-                    hipLaunchKernelGGL((aberth_persistent<false, false>), dim3(workers), dim3(64), 0,
+                    hipLaunchKernelGGL((aberth_persistent<false, false>), dim3(workers), dim3(threads), lds,
                                        rs, A4, c->fronts.as<Front>(), dq, dtasks, dseq,
                                        (unsigned long long)(cap - 1), dfdone, F, max_cold, max_warm,
                                        stall);

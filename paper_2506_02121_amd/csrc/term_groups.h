@@ -64,14 +64,24 @@ __device__ __forceinline__ void rcp_group(const double (&q)[G], double (&iq)[G])
 
 template <int G> using GroupOf = std::integral_constant<int, G>;
 
-// Streams the records p[0..n) for a one-wave work group: tiles of 64 records
+// Orders a wave's own LDS accesses.  The LDS serves one wave's accesses in
+// order, so this only keeps the compiler from moving them; waves of a work
+// group that stream tiles of their own never wait for each other here.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Streams the records p[0..n) for one wave: tiles of 64 records
 // (one per lane) fetched with coalesced vector loads, the next tile while the
 // current one is consumed, parked in LDS and read back as wave-uniform
 // broadcasts.  The records go to group(GroupOf<G>{}, r) with r pointing at G
 // consecutive records in LDS: G = MLCC_RCP_GROUP in full tiles, and a partial
 // tile ends with groups of half, a quarter ... of that, so the terms meet the
 // sums in record order.  Indices past n-1 are clamped on load; `lds` holds
-// two tiles.
+// two tiles of the wave's own.
 template <class T, class Group>
 __device__ __forceinline__ void stream_tiles_grouped(const T *__restrict__ p, int n, T *lds,
                                                      Group &&group)
@@ -79,13 +89,13 @@ __device__ __forceinline__ void stream_tiles_grouped(const T *__restrict__ p, in
     constexpr int G = MLCC_RCP_GROUP;
     static_assert(G == 1 || G == 2 || G == 4 || G == 8, "group of 1, 2, 4 or 8 terms");
     if (n <= 0) return;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
     const int ntiles = (n + 63) >> 6;
     T reg = p[min(lane, n - 1)];
     for (int t = 0; t < ntiles; ++t) {
         T *buf = lds + ((t & 1) << 6);
         buf[lane] = reg;
-        __syncthreads();
+        wave_sync();
         if (t + 1 < ntiles) reg = p[min(((t + 1) << 6) + lane, n - 1)];
         const int cnt = min(64, n - (t << 6));
         if (cnt == 64) {
@@ -111,7 +121,7 @@ __device__ __forceinline__ void stream_tiles_grouped(const T *__restrict__ p, in
             }
         }
     }
-    __syncthreads();
+    wave_sync();
 }
 
 } // namespace mlcc
