@@ -50,7 +50,17 @@ typedef enum {
                       refined by one Newton step (relative error below 2^-47, against
                       2^-53 for a correctly rounded division); consecutive star terms,
                       and consecutive root-root terms, are taken in groups of eight that
-                      share one refined reciprocal of the product of their eight |d|^2 */
+                      share one refined reciprocal of the product of their eight |d|^2.
+                      With predictor = 2, a warm row with three finished rows behind it
+                      takes the correction 2 S1 - R, which equals -F''/(2 F') at a root,
+                      from F' along the root's chain (second divided differences over
+                      this iterate and the last two rows) in place of the root-root sum R,
+                      as long as the step stays within a twentieth of the root's basin and
+                      the correction's error moves the root by less than 1e-16; every
+                      other root takes the step with R.  With the persistent schedule such
+                      a pass goes on through up to 7 further rows of its front (multipole
+                      star sums; direct sums for fields of at most 160 stars); the results
+                      are those of one row per pass */
     MLCC_MIXED = 1,/* Aberth sweeps in FP32 (FP64 star distances, FP32 sums per tile of
                       64 stars carried in FP64), every root finished by FP64 Newton
                       polish passes that accept a root on the same cutoffs as the
@@ -256,17 +266,17 @@ typedef struct {
     double polish_ms;        /* same, polish launches */
     int64_t sweep_launches, sweep_f32_launches, polish_launches;   /* launches that did work */
     double algorithmic_flop; /* FP64 sweeps, FP64 part: root_updates * 29 N (star terms) plus
-                                10 (2N - 1) per update whose root-root terms run in FP64
-                                (every update of MLCC_FP64; cold starts and the mixed form's
-                                restarts otherwise); FMA = 2, add/mul/reciprocal = 1 */
+                                10 (2N - 1) per update that sums its root-root terms in FP64
+                                (not those that take the correction from the chain, nor warm
+                                rows of MLCC_FP64_R32); FMA = 2, add/mul/reciprocal = 1 */
     double algorithmic_flop_f32;    /* FP32 sweeps: root_updates_f32 * (29 N + 10 (2N - 1)) */
     double algorithmic_flop_polish; /* polish: polish_updates * 29 N (star terms only) */
     double persistent_ms;    /* MLCC_SCHEDULE_PERSISTENT: GPU time of the one launch that runs
                                 every pass (timing != 0); the per-kind times above stay 0 */
     int64_t persistent_launches;    /* 1 with MLCC_SCHEDULE_PERSISTENT, else 0 */
     double algorithmic_flop_sweep_roots; /* FP64 sweeps, FP32 part: 10 (2N - 1) per update of
-                                a warm MLCC_FP64_R32 row (its root-root terms run in FP32);
-                                0 for MLCC_FP64 */
+                                a warm MLCC_FP64_R32 row that sums its root-root terms (they
+                                run in FP32); 0 for MLCC_FP64 */
     int64_t fmm_near_terms;  /* MLCC_STARS_FMM: star terms summed directly in the updates that
                                 took the multipole sums (the 3 x 3 near cells), all pass kinds;
                                 0 otherwise */

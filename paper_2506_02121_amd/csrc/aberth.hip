@@ -20,6 +20,9 @@
 //    polish again, then FP64 Aberth sweeps.
 //  * A warm row's first pass may start each root from an extrapolation
 //    along its chain instead of its previous-row value.
+//  * FP64 rows with enough rows behind them take the Aberth correction from
+//    their chains' F' instead of the O(N) sum over the other roots, and finish
+//    in one pass, or several rows in one (chain_rows).
 //  * A single-work-group control kernel after every round advances the
 //    fronts (device-side; the host polls a status block one batch ahead).
 //  * Converged roots are mapped to the caustic in the same kernel.
@@ -50,14 +53,14 @@ constexpr int RCP_ROOT = 1;
 // in order, so waiting for the older tile never waits for the prefetch
 // behind it.  Indices past n-1 are clamped on load, so nothing outside the
 // array is read.  `lds` holds two tiles of the wave's own.
-template <class T, class L, class Cvt, class Body, class End>
-__device__ __forceinline__ void stream_tiles_ex(const T *__restrict__ p, int n, L *lds, Cvt &&cvt,
+template <class Src, class L, class Cvt, class Body, class End>
+__device__ __forceinline__ void stream_tiles_ex(const Src p, int n, L *lds, Cvt &&cvt,
                                                 Body &&body, End &&tile_end)
 {
     if (n <= 0) return;
     const int lane = threadIdx.x & 63;
     const int ntiles = (n + 63) >> 6;
-    T reg = p[min(lane, n - 1)];
+    auto reg = p[min(lane, n - 1)];
     for (int t = 0; t < ntiles; ++t) {
         L *buf = lds + ((t & 1) << 6);
         buf[lane] = cvt(reg);
@@ -83,8 +86,8 @@ struct NoEnd {
     __device__ __forceinline__ void operator()() const {}
 };
 
-template <class T, class Body>
-__device__ __forceinline__ void stream_tiles(const T *__restrict__ p, int n, T *lds, Body &&body)
+template <class Src, class T, class Body>
+__device__ __forceinline__ void stream_tiles(const Src p, int n, T *lds, Body &&body)
 {
     stream_tiles_ex(p, n, lds, Same{}, body, NoEnd{});
 }
@@ -272,6 +275,7 @@ struct Update {
     double wr, wi;   // its image under the lens map
     bool flag;       // converged
     double err;      // Newton polish: estimated error of the new iterate
+    double dr, di;   // F' at the iterate the step was taken from (Aberth sweep)
 };
 
 // Degenerate iterate (on a star, or two iterates equal): nudge it off.
@@ -328,11 +332,16 @@ __device__ __forceinline__ void sheet_map_term(const double *__restrict__ dm, in
     Qi = qr * zi + qi * zr;
 }
 
+// F and F' at an iterate.
+struct FieldAt {
+    double Fr, Fi, Fpr, Fpi;
+};
+
+// F and F' from the sums at z, which are completed in place: the common mass
+// and the sign of Im s2.
 template <bool EQUAL>
-__device__ __forceinline__ Update finish(Sums S, double zr, double zi, double m0, double2 e,
-                                         double gamma, double a, double a1, double tol_step2,
-                                         double tol_mu, int k, const double *sheet = nullptr,
-                                         int n_poly = 0)
+__device__ __forceinline__ FieldAt field_at(Sums &S, double zr, double zi, double m0, double2 e,
+                                            double gamma, const double *sheet, int n_poly)
 {
     S.s2i *= -2.0;
     if (EQUAL) {   // every mass equals m0: the sums above left it out
@@ -344,24 +353,38 @@ __device__ __forceinline__ Update finish(Sums S, double zr, double zi, double m0
         S.s3i *= m0;
     }
     // F = gamma + S2 - (1 - kappa_s) e^{-i phi}, F' = -2 S3
-    double Fr = gamma + S.s2r - e.x, Fi = S.s2i - e.y;
-    double Fpr = -2.0 * S.s3r, Fpi = -2.0 * S.s3i;
+    FieldAt Q;
+    Q.Fr = gamma + S.s2r - e.x;
+    Q.Fi = S.s2i - e.y;
+    Q.Fpr = -2.0 * S.s3r;
+    Q.Fpi = -2.0 * S.s3i;
     if (n_poly > 0) {   // rectangular field: F -= P(z), F' -= P'(z)
         double Pr, Pi, Qr, Qi;
         sheet_terms(sheet, n_poly, zr, zi, Pr, Pi, Qr, Qi);
-        Fr -= Pr;
-        Fi -= Pi;
-        Fpr -= Qr;
-        Fpi -= Qi;
+        Q.Fr -= Pr;
+        Q.Fi -= Pi;
+        Q.Fpr -= Qr;
+        Q.Fpi -= Qi;
     }
-    // Aberth step: 1 / (F'/F + 2 S1 - R) = F / (F' + F (2 S1 - R))
-    const double Gr = 2.0 * S.s1r - S.Rr, Gi = 2.0 * S.s1i - S.Ri;
-    const double Dr = Fpr + (Fr * Gr - Fi * Gi);
-    const double Di = Fpi + (Fr * Gi + Fi * Gr);
+    return Q;
+}
+
+// The step F / (F' + F G), G = 2 S1 - R (the Aberth step
+// 1 / (F'/F + 2 S1 - R)), its tests and the lens map, from completed sums.
+__device__ __forceinline__ Update take_step(const Sums &S, const FieldAt &Q, double Gr, double Gi,
+                                            double zr, double zi, double gamma, double a,
+                                            double a1, double tol_step2, double tol_mu, int k,
+                                            const double *sheet, int n_poly)
+{
+    const double Fr = Q.Fr, Fi = Q.Fi;
+    const double Dr = Q.Fpr + (Fr * Gr - Fi * Gi);
+    const double Di = Q.Fpi + (Fr * Gi + Fi * Gr);
     const double den = Dr * Dr + Di * Di;
     const double stepr = (Fr * Dr + Fi * Di) / den;
     const double stepi = (Fi * Dr - Fr * Di) / den;
     Update u;
+    u.dr = Q.Fpr;
+    u.di = Q.Fpi;
     u.zr = zr - stepr;
     u.zi = zi - stepi;
     const double aF = sqrt(Fr * Fr + Fi * Fi);
@@ -382,6 +405,59 @@ __device__ __forceinline__ Update finish(Sums S, double zr, double zi, double m0
     }
     return u;
 }
+
+template <bool EQUAL>
+__device__ __forceinline__ Update finish(Sums S, double zr, double zi, double m0, double2 e,
+                                         double gamma, double a, double a1, double tol_step2,
+                                         double tol_mu, int k, const double *sheet = nullptr,
+                                         int n_poly = 0)
+{
+    const FieldAt Q = field_at<EQUAL>(S, zr, zi, m0, e, gamma, sheet, n_poly);
+    return take_step(S, Q, 2.0 * S.s1r - S.Rr, 2.0 * S.s1i - S.Ri, zr, zi, gamma, a, a1,
+                     tol_step2, tol_mu, k, sheet, n_poly);
+}
+
+// The Aberth correction without the root-root sum.  At a simple zero of F,
+// G = 2 S1 - R equals -F''/(2 F') (both are half the logarithmic derivative
+// of F'/F's deflation there), and F' depends on z alone, so its values at
+// this iterate and at the roots of the two rows before give F'' by second
+// divided differences: error O(h^2) for a row step h, where the sum over the
+// other roots' previous-row values is off by O(h).  `f1` and `f2` are F' at
+// z1 and z2, the chain's last two roots; `last` receives the size of the
+// second difference's share of G, which bounds what the third would add.
+__device__ __forceinline__ double2 cdiv(double2 p, double2 q)
+{
+    const double inv = rcp_refined<2>(fma(q.x, q.x, q.y * q.y));
+    return make_double2(fma(p.x, q.x, p.y * q.y) * inv, fma(p.y, q.x, -(p.x * q.y)) * inv);
+}
+
+__device__ __forceinline__ double2 chain_correction(double2 z, double2 f, double2 z1, double2 f1,
+                                                    double2 z2, double2 f2, double &last2)
+{
+    const double2 h1 = make_double2(z.x - z1.x, z.y - z1.y);
+    const double2 a = cdiv(make_double2(f.x - f1.x, f.y - f1.y), h1);
+    const double2 b = cdiv(make_double2(f1.x - f2.x, f1.y - f2.y),
+                           make_double2(z1.x - z2.x, z1.y - z2.y));
+    const double2 c = cdiv(make_double2(a.x - b.x, a.y - b.y),
+                           make_double2(z.x - z2.x, z.y - z2.y));
+    const double2 t = make_double2(h1.x * c.x - h1.y * c.y, h1.x * c.y + h1.y * c.x);
+    const double2 g = cdiv(make_double2(a.x + t.x, a.y + t.y), f);
+    last2 = 0.25 * (t.x * t.x + t.y * t.y) / (f.x * f.x + f.y * f.y);
+    return make_double2(-0.5 * g.x, -0.5 * g.y);
+}
+
+// A root takes steps D with the correction G from the chain while
+// |D G| < CHAIN_BASIN, which keeps it deep inside its zero's basin, and is
+// accepted when it is flagged and its G can be off by no more than moves the
+// new iterate by CHAIN_ERR (|D|^2 times the second difference's share of G),
+// far below the rounding of its sums.  A root this does not settle in
+// CHAIN_STEPS steps starts over with the Aberth step.
+constexpr double CHAIN_BASIN = 0.05;
+constexpr double CHAIN_ERR = 1e-16;
+constexpr int CHAIN_STEPS = 3;
+// F' of a front's last rows: rows are kept in a ring, so that the rows a pass
+// runs ahead leave the last two that its front keeps.
+constexpr int FP_RING = 16;
 
 // Resident waves per SIMD the sweep and polish kernels are compiled for
 // (register budget 512 / waves); the loops keep their instruction counts.
@@ -414,8 +490,8 @@ constexpr int SPARSE_MAX = 16;
 // default of mlcc_cc_params.cold_restart_sweeps).
 constexpr int STALL_START = 100;
 
-// Newton steps a root may take within one polish pass with multipole sums.
-constexpr int FMM_POLISH_STEPS = 3;
+// Newton steps a root may take within one polish pass.
+constexpr int POLISH_STEPS = 3;
 
 // Further rows a polish pass with multipole sums may finish after its own
 // (persistent schedule; see polish_pass).
@@ -753,11 +829,17 @@ template <class T> struct RoundArgs {
     double *out_re, *out_im, *caus_re, *caus_im;
     double2 *bnd;
     int32_t *counts;
-    int32_t *passupd;  // per front: roots updated by this round's pass (the control kernel sums them)
+    int32_t *passupd;  // per front, two counts of the pass: updates, and those of them that
+                       // took no root-root sum
     Control *ctl;
     unsigned long long *fmm_tally;   // multipole tallies (FMM_STRIPES copies)
     double4 *vieta;    // two per block: row sums, and their error terms
     double *errbuf;    // estimated error of each polished root
+    // F' at the accepted roots of the front's last rows, row j in slot
+    // j mod FP_RING of fp_stride elements (null: the sweeps always form the
+    // root-root sums)
+    double2 *fprime;
+    int64_t fp_stride;
     int32_t predictor;
     int32_t persistent; // the persistent scheduler: iterates by per-front parity
     double2 *iter0, *iter1;
@@ -771,6 +853,9 @@ template <class T> struct RoundArgs {
     int32_t *xrows;
     int32_t xrow_max;
     int32_t nvslots;
+    // and per front and further row: the row's updates and near-star terms
+    // (the front's finisher counts those of the rows it keeps)
+    unsigned long long *xcount;
 };
 
 // What one block knows about its front and star field.
@@ -785,7 +870,9 @@ template <class T> struct BlockCtx {
                      // row's roots come from the output, not the iterate buffer
     bool reseed, second;   // restart the row from its start values; from the second seeds
     bool fast;       // root-root terms in FP32 (fast_roots_pass)
-    int32_t *count, *upd;   // the pass's totals: roots left open (or moving), updates made
+    bool chain;      // the pass takes the Aberth correction from the chain (chain_pass)
+    int32_t *count, *upd;   // the pass's totals: roots left open (or moving); updates made,
+                            // and those of them without a root-root sum
     int64_t base_f, out_off, bnd_row_off;
     const T *stars;
     const double2 *zsrc;
@@ -801,6 +888,15 @@ template <class T> struct BlockCtx {
 __device__ __forceinline__ bool fast_roots_pass(const Front &fr, const Real &r)
 {
     return r.root32 && fr.dir != 0 && fr.mode == PH_F64;
+}
+
+// Whether this pass takes the Aberth correction from the chain: the first
+// pass of a row of a plain FP64 field whose front has three finished rows
+// behind it, two of them its own (the centre row's F' is not kept).
+template <class T>
+__device__ __forceinline__ bool chain_pass(const RoundArgs<T> &A, const Front &fr)
+{
+    return A.fprime && fr.fresh && fr.dir != 0 && fr.hist >= 3;
 }
 
 // Context of block q of front f, whose record is F (in LDS under the
@@ -821,6 +917,7 @@ __device__ __forceinline__ void enter_fq(const RoundArgs<T> &A, const Front *F, 
     B.reseed = F->reseed != 0;
     B.second = F->seedvar > 0;
     B.fast = fast_roots_pass(*F, *R);
+    B.chain = chain_pass(A, *F);
     B.count = count;
     B.upd = upd;
     B.hist = F->hist;
@@ -862,7 +959,7 @@ __device__ __forceinline__ bool enter(const RoundArgs<T> &A, int phase, BlockCtx
     const int2 fq = A.bmap[blockIdx.x];
     const Front *F = A.fronts + fq.x;
     if (F->state != FRONT_ACTIVE || F->phase != phase) return false;
-    enter_fq(A, F, fq.x, fq.y, A.counts + fq.x, A.passupd + fq.x, B);
+    enter_fq(A, F, fq.x, fq.y, A.counts + fq.x, A.passupd + 2 * fq.x, B);
     return true;
 }
 
@@ -886,6 +983,29 @@ __device__ __forceinline__ void predict(const RoundArgs<T> &A, const BlockCtx<T>
     }
 }
 
+// The other roots' values a pass reads: the iterate buffer, or, on the first
+// pass after one that finished several rows, the previous row of the output.
+struct RootSrc {
+    const double2 *it;
+    const double *re, *im;
+    __device__ __forceinline__ double2 operator[](int64_t j) const
+    {
+        return re ? make_double2(re[j], im[j]) : it[j];
+    }
+    __device__ __forceinline__ RootSrc operator+(int64_t o) const
+    {
+        return RootSrc{it + o, re ? re + o : nullptr, re ? im + o : nullptr};
+    }
+};
+
+template <class T>
+__device__ __forceinline__ RootSrc root_src(const RoundArgs<T> &A, const BlockCtx<T> &B)
+{
+    if (!B.from_out) return RootSrc{B.zsrc, nullptr, nullptr};
+    const int64_t o = B.out_off + (int64_t)(B.row - B.dir) * B.n_r;
+    return RootSrc{B.zsrc, A.out_re + o, A.out_im + o};
+}
+
 // Write-back of a converged root: its row of the output (or the duplicate
 // boundary row of a subchain) and its caustic image.
 template <class T>
@@ -903,6 +1023,283 @@ __device__ __forceinline__ void put(const RoundArgs<T> &A, const BlockCtx<T> &B,
         A.caus_re[o] = u.wr;
         A.caus_im[o] = u.wi;
     }
+}
+
+// ---------------------------------------------------------------------------
+// Star sums of Newton-like steps, and FP64 rows from their chains
+// ---------------------------------------------------------------------------
+
+// Sums for the Newton polish: s0 = sum m u, s2 = sum m u^2, s3 = sum m u^3
+// (F = gamma + s2 - (1 - kappa_s) e^{-i phi}, F' = -2 s3) and the real
+// q = sum m |u|^4, which bounds |F''| = 6 |sum m u^4| <= 6 q.
+struct PSums {
+    double s0r, s0i, s2r, s2i, s3r, s3i, q;
+};
+
+__device__ __forceinline__ void zero(PSums &S)
+{
+    S.s0r = S.s0i = S.s2r = S.s2i = S.s3r = S.s3i = S.q = 0.0;
+}
+
+template <bool EQUAL, class T>
+__device__ __forceinline__ void add_star_polish_inv(PSums &S, double dx, double dy, double inv,
+                                                    const T &s);
+
+template <bool EQUAL, class T>
+__device__ __forceinline__ void add_star_polish(PSums &S, double zr, double zi, const T &s)
+{
+    const double dx = zr - s.x;
+    const double dy = zi - s.y;
+    add_star_polish_inv<EQUAL>(S, dx, dy, rcp_refined<RCP_STAR>(fma(dx, dx, dy * dy)), s);
+}
+
+// G consecutive polish star terms sharing one refined reciprocal.
+template <bool EQUAL, int G, class T>
+__device__ __forceinline__ void add_star_polish_group(PSums &S, double zr, double zi, const T *r)
+{
+    double dx[G], dy[G], q[G], iq[G];
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+        dx[j] = zr - r[j].x;
+        dy[j] = zi - r[j].y;
+        q[j] = fma(dx[j], dx[j], dy[j] * dy[j]);
+    }
+    rcp_group<G, RCP_STAR>(q, iq);
+#pragma unroll
+    for (int j = 0; j < G; ++j) add_star_polish_inv<EQUAL>(S, dx[j], dy[j], iq[j], r[j]);
+}
+
+template <bool EQUAL, class T>
+__device__ __forceinline__ void add_star_polish_inv(PSums &S, double dx, double dy, double inv,
+                                                    const T &s)
+{
+    // u = ux - i uy, a = ux^2, b = uy^2:  u^2 = (a - b) - 2i ux uy,
+    // u^3 = ux (a - 3b) + i uy (b - 3a), formed from b alone as in
+    // add_star_inv (t = a - b = inv - 2b, a - 3b = t - 2b, b - 3a = -2t - inv);
+    // |u|^4 = inv^2
+    // (s2i accumulates sum m ux uy; polish_finish turns it into Im s2 = -2 that)
+    const double uy = dy * inv;
+    const double b = uy * uy;
+    const double t = fma(-2.0, b, inv);
+    const double c3r = fma(-2.0, b, t), c3i = fma(-2.0, t, -inv);
+    if (EQUAL) {
+        const double ux = dx * inv;
+        S.s0r += ux; S.s0i -= uy;
+        S.s2r += t;
+        S.s2i = fma(ux, uy, S.s2i);
+        S.s3r = fma(ux, c3r, S.s3r);
+        S.s3i = fma(uy, c3i, S.s3i);
+        S.q = fma(inv, inv, S.q);
+    } else {
+        // the mass enters through m inv, shared by m u = conj(d) m inv and
+        // the bound's m inv^2; u's real part is not needed on its own
+        const double mi = StarRec<EQUAL>::mass(s);
+        const double minv = mi * inv;
+        const double mux = dx * minv, muy = mi * uy;
+        S.s0r += mux; S.s0i -= muy;
+        S.s2r = fma(mi, t, S.s2r);
+        S.s2i = fma(mux, uy, S.s2i);
+        S.s3r = fma(mux, c3r, S.s3r);
+        S.s3i = fma(muy, c3i, S.s3i);
+        S.q = fma(minv, inv, S.q);
+    }
+}
+
+// Star sums at (zr, zi) for the lanes of `mask` (PSums; what is not read is
+// not computed).  Multipole sums: every lane its cell's series and near
+// stars, whose number goes to n_near.  Direct sums: the whole wave one root
+// after another when the mask holds few, else the star tiles for every lane.
+template <bool EQUAL, bool FMM>
+__device__ __forceinline__ void newton_sums(const RoundArgs<typename StarRec<EQUAL>::T> &A,
+                                            const BlockCtx<typename StarRec<EQUAL>::T> &B,
+                                            unsigned long long mask, double zr, double zi,
+                                            double4 *tiles, PSums &S, int &n_near)
+{
+    using T = typename StarRec<EQUAL>::T;
+    zero(S);
+    n_near = 0;
+    if constexpr (FMM) {
+        int cell;
+        double2 f, f1, f2, g;
+        double q;
+        fmm_far(A.fmm[B.r], zr, zi, cell, f, f1, f2, g, q, false);
+        n_near = fmm_near(A.fmm[B.r], cell, [&](const double4 &s4) {
+            if constexpr (EQUAL) add_star_polish<EQUAL>(S, zr, zi, make_double2(s4.x, s4.y));
+            else add_star_polish<EQUAL>(S, zr, zi, s4);
+        });
+        S.s0r += f.x; S.s0i += f.y;
+        S.s2r -= f1.x; S.s2i += 0.5 * f1.y;
+        S.s3r += 0.5 * f2.x; S.s3i += 0.5 * f2.y;
+        S.q += q;
+    } else if (__popcll(mask) <= SPARSE_MAX) {
+        while (mask) {
+            const int l = __ffsll((long long)mask) - 1;
+            mask &= mask - 1;
+            const double xk = __shfl(zr, l, 64), yk = __shfl(zi, l, 64);
+            PSums C;
+            zero(C);
+#pragma unroll 4
+            for (int i = B.lane; i < B.n_stars; i += 64)
+                add_star_polish<EQUAL>(C, xk, yk, B.stars[i]);
+            wave_sum(C.s0r); wave_sum(C.s0i); wave_sum(C.s2r); wave_sum(C.s2i);
+            wave_sum(C.s3r); wave_sum(C.s3i); wave_sum(C.q);
+            if (B.lane == l) S = C;
+        }
+    } else {
+        stream_tiles_grouped(B.stars, B.n_stars, reinterpret_cast<T *>(tiles),
+                             [&](auto g, const T *r) {
+                                 add_star_polish_group<EQUAL, decltype(g)::value>(S, zr, zi, r);
+                             });
+    }
+}
+
+// Sum over the wave of a per-lane count.
+__device__ __forceinline__ int wave_count(int v)
+{
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    return __builtin_amdgcn_readfirstlane(v);
+}
+
+// Adds a further row's work to its front's counts (see RoundArgs::xcount).
+template <class T>
+__device__ __forceinline__ void count_further(const RoundArgs<T> &A, int f, int x, int n_upd,
+                                              int n_near)
+{
+    unsigned long long *c = A.xcount + 2 * ((int64_t)f * (A.xrow_max + 1) + x);
+    if ((threadIdx.x & 63) == 0) {
+        atomicAdd(&c[0], (unsigned long long)n_upd);
+        if (n_near) atomicAdd(&c[1], (unsigned long long)n_near);
+    }
+}
+
+// Rows of a plain FP64 field from their chains (see chain_correction): each
+// root of the block starts from the quadratic extrapolation of its last three
+// rows and takes steps whose correction comes from the chain, with no sum over
+// the other roots.  Roots accepted in the pass's row are stored; `open` tells
+// which the caller still has to step from (zr, zi).  Once every root of the
+// block is accepted the block goes on through the next rows of its front by
+// itself, as polish_pass does: nothing couples its roots to other blocks.
+// Direct star sums bound it: ~19 instructions a term against ~19 and twice 9
+// for a star and two root terms of the Aberth step, and one pass a row where
+// the stragglers of a row took a second one.  Whole calls before and after:
+// N = 6,000 FP64 1041 -> 547 ms, N = 1,000 44.3 -> 27.4, rectangular N = 437
+// 17.0 -> 10.5, N = 3,000 with multipole sums, whose rows keep no O(N) part,
+// 129.0 -> 28.4 ms.  Against 80-bit roots of 8 fields of 10 to 3,000 stars the
+// errors are those of the rows with the root-root sum (rms 2e-16 to 2.7e-15,
+// within 1% of each other).
+template <bool EQUAL, bool FMM>
+__device__ __forceinline__ void chain_rows(const RoundArgs<typename StarRec<EQUAL>::T> &A,
+                                           const BlockCtx<typename StarRec<EQUAL>::T> &B,
+                                           double4 *tiles, double &zr, double &zi, bool &open)
+{
+    using T = typename StarRec<EQUAL>::T;
+    const int k = B.k, n_r = B.n_r;
+    const int64_t base_f = B.base_f;
+    const bool valid = B.valid;
+    double2 z1 = make_double2(0.0, 0.0), z2 = z1, z3 = z1, f1 = z1, f2 = z1;
+    auto fp = [&](int row) { return A.fprime + (row % FP_RING) * A.fp_stride + base_f; };
+    if (valid) {
+        const int64_t o1 = B.out_off + (int64_t)(B.row - B.dir) * n_r + k;
+        const int64_t o2 = o1 - (int64_t)B.dir * n_r, o3 = o2 - (int64_t)B.dir * n_r;
+        z1 = make_double2(A.out_re[o1], A.out_im[o1]);
+        z2 = make_double2(A.out_re[o2], A.out_im[o2]);
+        z3 = make_double2(A.out_re[o3], A.out_im[o3]);
+        f1 = fp(B.row - B.dir)[k];
+        f2 = fp(B.row - 2 * B.dir)[k];
+    }
+    const int xmax = A.xrows ? A.reals[B.r].xrows : 0;
+    int done = 0;
+    for (int x = 0; x <= xmax; ++x) {
+        BlockCtx<T> C = B;
+        C.row = B.row + x * B.dir;
+        if (x > 0) {
+            // the front's last row is left to a pass of its own; rows another
+            // block already stopped short of will not be kept
+            if ((C.row - B.end_row) * B.dir >= 0 || load_relaxed(&A.xrows[B.f]) < x) break;
+            C.boundary = false;
+        }
+        const double2 un = A.unit[C.row];
+        const double2 e = make_double2(B.a * un.x, B.a * un.y);
+        const double pr = fma(3.0, z1.x - z2.x, z3.x), pi = fma(3.0, z1.y - z2.y, z3.y);
+        double xr = pr, xi = pi;
+        bool going = valid, left = valid;   // left: not accepted in this row
+        Update u{};
+        int n_steps = 0, n_near = 0;
+        for (int it = 0; it < CHAIN_STEPS; ++it) {
+            const unsigned long long mask = __ballot(going);
+            if (!mask) break;
+            PSums P;
+            int near;
+            newton_sums<EQUAL, FMM>(A, B, mask, xr, xi, tiles, P, near);
+            Sums S;
+            zero(S);
+            S.s0r = P.s0r; S.s0i = P.s0i;
+            S.s1r = P.s0r; S.s1i = P.s0i;   // what s0 is formed from when the masses are equal
+            S.s2r = P.s2r; S.s2i = P.s2i; S.s3r = P.s3r; S.s3i = P.s3i;
+            const FieldAt Q = field_at<EQUAL>(S, xr, xi, B.m0, e, B.gamma, B.sheet, B.n_poly);
+            double last2;
+            const double2 G = chain_correction(make_double2(xr, xi), make_double2(Q.Fpr, Q.Fpi), z1,
+                                               f1, z2, f2, last2);
+            const Update v = take_step(S, Q, G.x, G.y, xr, xi, B.gamma, B.a, B.a1, A.tol_step2,
+                                       A.tol_mu, k, B.sheet, B.n_poly);
+            const double sr = xr - v.zr, si = xi - v.zi, d2 = sr * sr + si * si;
+            if (going) {
+                n_steps += 1;
+                n_near += near;
+                going = d2 * (G.x * G.x + G.y * G.y) < CHAIN_BASIN * CHAIN_BASIN;
+                if (going && v.flag && d2 * d2 * last2 < CHAIN_ERR * CHAIN_ERR) {
+                    u = v;
+                    left = false;
+                    going = false;
+                }
+                xr = v.zr;
+                xi = v.zi;
+            }
+        }
+        const bool all = !__ballot(left);
+        if (x == 0) {
+            zr = pr;
+            zi = pi;
+            open = left;
+            if (valid && !left) {
+                B.nxt[base_f + k] = make_double2(u.zr, u.zi);
+                A.flagrow[base_f + k] = B.stamp;
+            }
+        }
+        if (x == 0 || all) {
+            if (valid && !left) {
+                fp(C.row)[k] = make_double2(u.dr, u.di);
+                put(A, C, k, u);
+            }
+            const int n_upd = wave_count(n_steps), n_nr = FMM ? wave_count(n_near) : 0;
+            if (x > 0) {
+                count_further(A, B.f, x, n_upd, n_nr);
+                done = x;
+            } else {
+                if (B.lane == 0) {
+                    atomicAdd(&B.upd[0], n_upd);
+                    atomicAdd(&B.upd[1], n_upd);
+                }
+                if constexpr (FMM) {
+                    FmmTally tl;
+                    tl.near = (unsigned long long)n_nr;
+                    tl.far = (unsigned long long)n_upd;
+                    tl.far_n = (unsigned long long)n_upd * (unsigned long long)B.n_stars;
+                    fmm_flush(A.fmm_tally, FMM_T_F64, tl);
+                }
+            }
+        }
+        if (!all) {
+            // tell the other blocks now
+            if (xmax > 0 && B.lane == 0) atomicMin(&A.xrows[B.f], done);
+            break;
+        }
+        z3 = z2; z2 = z1; f2 = f1;
+        z1 = make_double2(u.zr, u.zi);
+        f1 = make_double2(u.dr, u.di);
+    }
+    if (xmax > 0 && B.lane == 0) atomicMin(&A.xrows[B.f], done);
 }
 
 // One FP64 Aberth pass of a block (the block context is set by enter()).
@@ -946,7 +1343,7 @@ __device__ __forceinline__ void sweep_f64_pass(const RoundArgs<typename StarRec<
     const int lane = B.lane, k0 = B.k0, k = B.k, n_r = B.n_r, n_stars = B.n_stars;
     const bool valid = B.valid;
     const int64_t base_f = B.base_f;
-    const double2 *__restrict__ zsrc = B.zsrc;
+    const RootSrc zsrc = root_src(A, B);
     const T *__restrict__ stars = B.stars;
     double2 *__restrict__ nxt = B.nxt;
     int32_t *__restrict__ flagrow = A.flagrow;
@@ -954,23 +1351,27 @@ __device__ __forceinline__ void sweep_f64_pass(const RoundArgs<typename StarRec<
     const double tol_step2 = A.tol_step2, tol_mu = A.tol_mu;
     double zr = 0.0, zi = 0.0;
     bool act = false;
-    if (valid) {
+    if (B.chain) {
+        chain_rows<EQUAL, FMM>(A, B, tiles, zr, zi, act);
+    } else if (valid) {
         const double2 z = zsrc[k];
         zr = z.x;
         zi = z.y;
         act = flagrow[base_f + k] != B.stamp;
         if (B.pred) predict(A, B, k, zr, zi);
+        if (!act) nxt[base_f + k] = make_double2(zr, zi);   // carried forward
     }
     const unsigned long long amask = __ballot(act);
     const int n_act = __popcll(amask);
-    if (valid && !act) nxt[base_f + k] = make_double2(zr, zi);   // carried forward
     if (n_act == 0) return;
 
     const double2 e = B.e;
+    double2 *fp = A.fprime ? A.fprime + (B.row % FP_RING) * A.fp_stride : nullptr;
     auto store = [&](int kk, const Update &u) {
         nxt[base_f + kk] = make_double2(u.zr, u.zi);
         if (!u.flag) return;
         flagrow[base_f + kk] = B.stamp;
+        if (fp) fp[base_f + kk] = make_double2(u.dr, u.di);
         put(A, B, kk, u);
     };
 
@@ -1045,37 +1446,34 @@ __device__ __forceinline__ void sweep_f64_pass(const RoundArgs<typename StarRec<
                 S.Ri = self ? S.Ri : T2.Ri;
             });
             stream_tiles_grouped(zsrc + own_hi, n_r - own_hi, rtiles, group);
-            const Update u = finish<EQUAL>(S, zr, zi, m0, e, gamma, a, a1, tol_step2, tol_mu, k,
-                                           B.sheet, B.n_poly);
-            if (act) store(k, u);
-            n_after = __popcll(__ballot(act && !u.flag));
         } else {
-        // root-root sum in FP32 (add_root_hl), summed per tile and carried
-        // across tiles in FP64
-        float4 *rtiles = reinterpret_cast<float4 *>(tiles);
-        const float4 zs = SplitRoot{}(make_double2(zr, zi));
-        float pr = 0.f, pi = 0.f;
-        auto other = [&](int, const float4 &o) { add_root_hl(pr, pi, zs, o); };
-        auto carry = [&]() {
-            S.Rr += (double)pr;
-            S.Ri += (double)pi;
-            pr = pi = 0.f;
-        };
-        const int own_hi = min(k0 + 64, n_r);
-        stream_tiles_ex(zsrc, k0, rtiles, SplitRoot{}, other, carry);
-        stream_tiles_ex(zsrc + k0, own_hi - k0, rtiles, SplitRoot{}, [&](int j, const float4 &o) {
-            float tr = pr, ti = pi;
-            add_root_hl(tr, ti, zs, o);
-            const bool self = j == lane;
-            pr = self ? pr : tr;
-            pi = self ? pi : ti;
-        }, carry);
-        stream_tiles_ex(zsrc + own_hi, n_r - own_hi, rtiles, SplitRoot{}, other, carry);
+            // root-root sum in FP32 (add_root_hl), summed per tile and carried
+            // across tiles in FP64
+            float4 *rtiles = reinterpret_cast<float4 *>(tiles);
+            const float4 zs = SplitRoot{}(make_double2(zr, zi));
+            float pr = 0.f, pi = 0.f;
+            auto other = [&](int, const float4 &o) { add_root_hl(pr, pi, zs, o); };
+            auto carry = [&]() {
+                S.Rr += (double)pr;
+                S.Ri += (double)pi;
+                pr = pi = 0.f;
+            };
+            const int own_hi = min(k0 + 64, n_r);
+            stream_tiles_ex(zsrc, k0, rtiles, SplitRoot{}, other, carry);
+            stream_tiles_ex(zsrc + k0, own_hi - k0, rtiles, SplitRoot{},
+                            [&](int j, const float4 &o) {
+                                float tr = pr, ti = pi;
+                                add_root_hl(tr, ti, zs, o);
+                                const bool self = j == lane;
+                                pr = self ? pr : tr;
+                                pi = self ? pi : ti;
+                            }, carry);
+            stream_tiles_ex(zsrc + own_hi, n_r - own_hi, rtiles, SplitRoot{}, other, carry);
+        }
         const Update u = finish<EQUAL>(S, zr, zi, m0, e, gamma, a, a1, tol_step2, tol_mu, k,
                                        B.sheet, B.n_poly);
         if (act) store(k, u);
         n_after = __popcll(__ballot(act && !u.flag));
-        }
     }
     if (lane == 0) {
         if (n_after) atomicAdd(B.count, n_after);
@@ -1248,82 +1646,6 @@ aberth_sweep_f32(RoundArgs<typename StarRec<EQUAL>::T> A)
 // FP64 Newton polish (mixed mode)
 // ---------------------------------------------------------------------------
 
-// Sums for the Newton polish: s0 = sum m u, s2 = sum m u^2, s3 = sum m u^3
-// (F = gamma + s2 - (1 - kappa_s) e^{-i phi}, F' = -2 s3) and the real
-// q = sum m |u|^4, which bounds |F''| = 6 |sum m u^4| <= 6 q.
-struct PSums {
-    double s0r, s0i, s2r, s2i, s3r, s3i, q;
-};
-
-__device__ __forceinline__ void zero(PSums &S)
-{
-    S.s0r = S.s0i = S.s2r = S.s2i = S.s3r = S.s3i = S.q = 0.0;
-}
-
-template <bool EQUAL, class T>
-__device__ __forceinline__ void add_star_polish_inv(PSums &S, double dx, double dy, double inv,
-                                                    const T &s);
-
-template <bool EQUAL, class T>
-__device__ __forceinline__ void add_star_polish(PSums &S, double zr, double zi, const T &s)
-{
-    const double dx = zr - s.x;
-    const double dy = zi - s.y;
-    add_star_polish_inv<EQUAL>(S, dx, dy, rcp_refined<RCP_STAR>(fma(dx, dx, dy * dy)), s);
-}
-
-// G consecutive polish star terms sharing one refined reciprocal.
-template <bool EQUAL, int G, class T>
-__device__ __forceinline__ void add_star_polish_group(PSums &S, double zr, double zi, const T *r)
-{
-    double dx[G], dy[G], q[G], iq[G];
-#pragma unroll
-    for (int j = 0; j < G; ++j) {
-        dx[j] = zr - r[j].x;
-        dy[j] = zi - r[j].y;
-        q[j] = fma(dx[j], dx[j], dy[j] * dy[j]);
-    }
-    rcp_group<G, RCP_STAR>(q, iq);
-#pragma unroll
-    for (int j = 0; j < G; ++j) add_star_polish_inv<EQUAL>(S, dx[j], dy[j], iq[j], r[j]);
-}
-
-template <bool EQUAL, class T>
-__device__ __forceinline__ void add_star_polish_inv(PSums &S, double dx, double dy, double inv,
-                                                    const T &s)
-{
-    // u = ux - i uy, a = ux^2, b = uy^2:  u^2 = (a - b) - 2i ux uy,
-    // u^3 = ux (a - 3b) + i uy (b - 3a), formed from b alone as in
-    // add_star_inv (t = a - b = inv - 2b, a - 3b = t - 2b, b - 3a = -2t - inv);
-    // |u|^4 = inv^2
-    // (s2i accumulates sum m ux uy; polish_finish turns it into Im s2 = -2 that)
-    const double uy = dy * inv;
-    const double b = uy * uy;
-    const double t = fma(-2.0, b, inv);
-    const double c3r = fma(-2.0, b, t), c3i = fma(-2.0, t, -inv);
-    if (EQUAL) {
-        const double ux = dx * inv;
-        S.s0r += ux; S.s0i -= uy;
-        S.s2r += t;
-        S.s2i = fma(ux, uy, S.s2i);
-        S.s3r = fma(ux, c3r, S.s3r);
-        S.s3i = fma(uy, c3i, S.s3i);
-        S.q = fma(inv, inv, S.q);
-    } else {
-        // the mass enters through m inv, shared by m u = conj(d) m inv and
-        // the bound's m inv^2; u's real part is not needed on its own
-        const double mi = StarRec<EQUAL>::mass(s);
-        const double minv = mi * inv;
-        const double mux = dx * minv, muy = mi * uy;
-        S.s0r += mux; S.s0i -= muy;
-        S.s2r = fma(mi, t, S.s2r);
-        S.s2i = fma(mux, uy, S.s2i);
-        S.s3r = fma(mux, c3r, S.s3r);
-        S.s3i = fma(muy, c3i, S.s3i);
-        S.q = fma(minv, inv, S.q);
-    }
-}
-
 // Newton step z' = z - D, D = F/F', accepted on the paper's cutoffs for the
 // step just taken (|D| < tol_step, or the App. C bound on |1/mu| at z), or
 // when the error it leaves, at most ~|F''| |D|^2 / (2 |F'|) by quadratic
@@ -1368,285 +1690,126 @@ __device__ __forceinline__ Update polish_finish(PSums S, double zr, double zi, d
     return u;
 }
 
+// A Newton step needs only its own root's sums, so a root the acceptance test
+// turns down takes its next step in the same pass (up to POLISH_STEPS),
+// instead of waiting for the whole front's next pass.
+//
+// Several rows per pass: once every root of the block is accepted in this
+// row, the block goes on through the next rows of its front by itself, each
+// root from the chain prediction of its own earlier rows, as the front's
+// first pass of that row would (a Newton step couples no roots).  A row
+// counts only when every root of the block is accepted in it: then its roots
+// and caustics are written and its row sums kept in slot x; the first row
+// that leaves a root open ends the pass, and nothing of it is kept.  The
+// front's last row is left to a pass of its own.
 template <bool EQUAL, bool FMM>
 __device__ __forceinline__ void polish_pass(const RoundArgs<typename StarRec<EQUAL>::T> &A,
                                             const BlockCtx<typename StarRec<EQUAL>::T> &B,
                                             double4 *tiles)
 {
     using T = typename StarRec<EQUAL>::T;
-    const int lane = B.lane, k0 = B.k0, k = B.k, n_stars = B.n_stars;
+    const int lane = B.lane, k = B.k;
     const bool valid = B.valid;
     const int64_t base_f = B.base_f;
-    const double2 *__restrict__ zsrc = B.zsrc;
-    const T *__restrict__ stars = B.stars;
-    double2 *__restrict__ nxt = B.nxt;
-    int32_t *__restrict__ flagrow = A.flagrow;
-    const double m0 = B.m0, gamma = B.gamma, a = B.a, a1 = B.a1;
-    const double tol_step2 = A.tol_step2, tol_mu = A.tol_mu;
-    double zr = 0.0, zi = 0.0;
+    double zr = 0.0, zi = 0.0;   // the root's value: start of the row, then its end
     bool act = false;
-    double er_ = 0.0;   // estimated error of the value this root ends the pass with
-    FmmTally ptl;       // multipole tallies of the whole pass, added once at its end
+    double er = 0.0;   // estimated error of that value
     if (valid) {
-        if (B.from_out) {
-            const int64_t o = B.out_off + (int64_t)(B.row - B.dir) * B.n_r + k;
-            zr = A.out_re[o];
-            zi = A.out_im[o];
-        } else {
-            const double2 z = zsrc[k];
-            zr = z.x;
-            zi = z.y;
-        }
-        act = flagrow[base_f + k] != B.stamp;
+        const double2 z = root_src(A, B)[k];
+        zr = z.x;
+        zi = z.y;
+        act = A.flagrow[base_f + k] != B.stamp;
         if (B.pred) predict(A, B, k, zr, zi);
-        if (!act) er_ = A.errbuf[base_f + k];   // accepted in an earlier pass of this row
+        if (!act) er = A.errbuf[base_f + k];   // accepted in an earlier pass of this row
     }
-    const unsigned long long amask = __ballot(act);
-    const int n_act = __popcll(amask);
-    const double2 e = B.e;
-    double fr_ = zr, fi_ = zi;   // value this root ends the pass with
-    int n_after = 0;
-    int n_steps = -1;   // Newton steps this lane took (-1: one per active root)
-    // (with multipole sums a root's star terms are a few near stars and one
-    // series, as cheap per lane as a wave's share of a direct sum, so the
-    // wave never takes its few roots one at a time)
-    if (n_act > 0 && n_act <= SPARSE_MAX && !FMM) {
-        unsigned long long mm = amask;
-        while (mm) {
-            const int l = __ffsll((long long)mm) - 1;
-            mm &= mm - 1;
-            const double xk = __shfl(zr, l, 64), yk = __shfl(zi, l, 64);
-            PSums S;
-            zero(S);
-#pragma unroll 4
-            for (int i = lane; i < n_stars; i += 64) add_star_polish<EQUAL>(S, xk, yk, stars[i]);
-            wave_sum(S.s0r); wave_sum(S.s0i); wave_sum(S.s2r); wave_sum(S.s2i);
-            wave_sum(S.s3r); wave_sum(S.s3i); wave_sum(S.q);
-            const int kk = k0 + l;
-            const Update u = polish_finish<EQUAL>(S, xk, yk, m0, e, gamma, a, a1, tol_step2, tol_mu, kk);
-            if (lane == l) {
-                nxt[base_f + kk] = make_double2(u.zr, u.zi);
-                fr_ = u.zr;
-                fi_ = u.zi;
-                if (u.flag) {
-                    er_ = u.err;
-                    A.errbuf[base_f + kk] = u.err;
-                    flagrow[base_f + kk] = B.stamp;
-                    put(A, B, kk, u);
-                }
-            }
-            n_after += u.flag ? 0 : 1;
+    const int xmax = A.xrows ? A.reals[B.r].xrows : 0;
+    const int xtop = (B.dir != 0 && A.predictor > 0) ? xmax : 0;
+    int done = 0;
+    for (int x = 0; x <= xtop; ++x) {
+        BlockCtx<T> C = B;
+        if (x > 0) {
+            C.row = B.row + x * B.dir;
+            // rows another block already stopped short of will not be kept
+            if ((C.row - B.end_row) * B.dir >= 0 || load_relaxed(&A.xrows[B.f]) < x) break;
+            C.boundary = false;
+            C.pred = min(A.predictor, min(B.hist + x, 3) - 1);
+            const double2 un = A.unit[C.row];
+            C.e = make_double2(B.a * un.x, B.a * un.y);
+            if (valid && C.pred) predict(A, C, k, zr, zi);
+            act = valid;
         }
-    } else if (n_act > 0) {
+        bool open = act;
         Update u{};
-        if constexpr (FMM) {
-            // A Newton step needs only its own root's sums, and with
-            // multipole sums those cost a few near stars and one series: a
-            // root the acceptance test turns down takes its next step in the
-            // same pass (up to FMM_POLISH_STEPS), instead of waiting a pass.
-            double xr = zr, xi = zi;
-            bool open = act;
-            n_steps = 0;
-            for (int it = 0; it < FMM_POLISH_STEPS; ++it) {
-                PSums S;
-                zero(S);
-                int cell;
-                double2 f, f1, f2, g;
-                double q;
-                fmm_far(A.fmm[B.r], xr, xi, cell, f, f1, f2, g, q, false);
-                const int n_near = fmm_near(A.fmm[B.r], cell, [&](const double4 &s4) {
-                    if constexpr (EQUAL)
-                        add_star_polish<EQUAL>(S, xr, xi, make_double2(s4.x, s4.y));
-                    else add_star_polish<EQUAL>(S, xr, xi, s4);
-                });
-                fmm_count(ptl, open, n_near, n_stars);
-                S.s0r += f.x; S.s0i += f.y;
-                S.s2r -= f1.x; S.s2i += 0.5 * f1.y;
-                S.s3r += 0.5 * f2.x; S.s3i += 0.5 * f2.y;
-                S.q += q;
-                const Update v = polish_finish<EQUAL>(S, xr, xi, m0, e, gamma, a, a1, tol_step2,
-                                                      tol_mu, k);
-                if (open) {
-                    u = v;
-                    n_steps += 1;
-                    if (v.flag) {
-                        open = false;
-                    } else {
-                        xr = v.zr;
-                        xi = v.zi;
-                    }
-                }
-                if (!__ballot(open)) break;
+        int n_steps = 0, n_near = 0;
+        double xr = zr, xi = zi;
+        for (int it = 0; it < POLISH_STEPS; ++it) {
+            const unsigned long long mask = __ballot(open);
+            if (!mask) break;
+            PSums S;
+            int near;
+            newton_sums<EQUAL, FMM>(A, B, mask, xr, xi, tiles, S, near);
+            const Update v = polish_finish<EQUAL>(S, xr, xi, B.m0, C.e, B.gamma, B.a, B.a1,
+                                                  A.tol_step2, A.tol_mu, k);
+            if (open) {
+                u = v;
+                n_steps += 1;
+                n_near += near;
+                open = !v.flag;
+                xr = v.zr;
+                xi = v.zi;
+            }
+        }
+        const int n_open = __popcll(__ballot(open));
+        const int n_upd = wave_count(n_steps), n_nr = FMM ? wave_count(n_near) : 0;
+        if (x > 0 && n_open) break;
+        if (act) {
+            zr = u.zr;
+            zi = u.zi;
+            if (u.flag) {
+                er = u.err;
+                put(A, C, k, u);
+            }
+        }
+        if (x == 0) {
+            if (valid) B.nxt[base_f + k] = make_double2(zr, zi);
+            if (act && u.flag) {
+                A.errbuf[base_f + k] = u.err;
+                A.flagrow[base_f + k] = B.stamp;
+            }
+            if (lane == 0) {
+                if (n_open) atomicAdd(B.count, n_open);
+                if (n_upd) atomicAdd(B.upd, n_upd);
+            }
+            if constexpr (FMM) {
+                FmmTally tl;
+                tl.near = (unsigned long long)n_nr;
+                tl.far = (unsigned long long)n_upd;
+                tl.far_n = (unsigned long long)n_upd * (unsigned long long)B.n_stars;
+                fmm_flush(A.fmm_tally, FMM_T_POLISH, tl);
             }
         } else {
-            PSums S;
-            zero(S);
-            stream_tiles_grouped(stars, n_stars, reinterpret_cast<T *>(tiles),
-                                 [&](auto g, const T *r) {
-                                     add_star_polish_group<EQUAL, decltype(g)::value>(S, zr, zi,
-                                                                                      r);
-                                 });
-            u = polish_finish<EQUAL>(S, zr, zi, m0, e, gamma, a, a1, tol_step2, tol_mu, k);
+            count_further(A, B.f, x, n_upd, n_nr);
+            done = x;
         }
-        if (act) {
-            nxt[base_f + k] = make_double2(u.zr, u.zi);
-            fr_ = u.zr;
-            fi_ = u.zi;
-            if (u.flag) {
-                er_ = u.err;
-                A.errbuf[base_f + k] = u.err;
-                flagrow[base_f + k] = B.stamp;
-                put(A, B, k, u);
-            }
+        // this block's share of the row sums sum r and sum r^2 (row identities),
+        // and of what bounds their error: the roots' own estimated errors, and
+        // sum |r|, sum |r|^2 for the rounding of the sums
+        double s1r = valid ? zr : 0.0, s1i = valid ? zi : 0.0;
+        double s2r = valid ? zr * zr - zi * zi : 0.0, s2i = valid ? 2.0 * zr * zi : 0.0;
+        const double ab2 = valid ? zr * zr + zi * zi : 0.0, ab = sqrt(ab2);
+        const double ev = valid ? er : 0.0;
+        double t_e = ev, t_e2 = ev * (2.0 * ab + ev), t_a = ab, t_a2 = ab2;
+        wave_sum(s1r); wave_sum(s1i); wave_sum(s2r); wave_sum(s2i);
+        wave_sum(t_e); wave_sum(t_e2); wave_sum(t_a); wave_sum(t_a2);
+        if (lane == 0) {
+            const int64_t sl = 2 * ((int64_t)x * A.nvslots + B.vslot);
+            A.vieta[sl] = make_double4(s1r, s1i, s2r, s2i);
+            A.vieta[sl + 1] = make_double4(t_e, t_e2, t_a, t_a2);
         }
-        n_after = __popcll(__ballot(act && !u.flag));
+        if (n_open) break;
     }
-    if (valid && !act) nxt[base_f + k] = make_double2(zr, zi);
-    // this block's share of the row sums sum r and sum r^2 (row identities),
-    // and of what bounds their error: the roots' own estimated errors, and
-    // sum |r|, sum |r|^2 for the rounding of the sums
-    double s1r = valid ? fr_ : 0.0, s1i = valid ? fi_ : 0.0;
-    double s2r = valid ? fr_ * fr_ - fi_ * fi_ : 0.0, s2i = valid ? 2.0 * fr_ * fi_ : 0.0;
-    const double ab2 = valid ? fr_ * fr_ + fi_ * fi_ : 0.0, ab = sqrt(ab2);
-    double t_e = er_, t_e2 = er_ * (2.0 * ab + er_), t_a = ab, t_a2 = ab2;
-    wave_sum(s1r); wave_sum(s1i); wave_sum(s2r); wave_sum(s2i);
-    wave_sum(t_e); wave_sum(t_e2); wave_sum(t_a); wave_sum(t_a2);
-    if (lane == 0) {
-        A.vieta[2 * B.vslot] = make_double4(s1r, s1i, s2r, s2i);
-        A.vieta[2 * B.vslot + 1] = make_double4(t_e, t_e2, t_a, t_a2);
-        if (n_after) atomicAdd(B.count, n_after);
-    }
-    int n_xsteps = 0;   // Newton steps this lane took in further rows
-    const int xmax = A.xrows ? A.reals[B.r].xrows : 0;
-    if (xmax > 0) {
-        // Several rows per pass: once every root of the block is accepted in
-        // this row, the block goes on through the next rows of its front by
-        // itself, each root from the chain prediction of its own earlier rows,
-        // as the front's first pass of that row would (a Newton step couples
-        // no roots).  A row counts only when every root of the block is
-        // accepted in it: then its roots and caustics are written and its row
-        // sums kept in slot x; the first row that leaves a root open ends the
-        // pass, and nothing of it is kept.  The front's last row is left to a
-        // pass of its own.
-        int done = 0;
-        if (B.dir != 0 && A.predictor > 0 && n_after == 0) {
-            double pr = fr_, pi = fi_;   // this root in the row before
-            const unsigned long long vmask = __ballot(valid);
-            for (int x = 1; x <= xmax; ++x) {
-                BlockCtx<T> C = B;
-                C.row = B.row + x * B.dir;
-                if ((C.row - B.end_row) * B.dir >= 0) break;
-                // another block of the front already stopped short of this row:
-                // the front will not keep it
-                if (load_relaxed(&A.xrows[B.f]) < x) break;
-                C.boundary = false;
-                C.pred = min(A.predictor, min(B.hist + x, 3) - 1);
-                const double2 un = A.unit[C.row];
-                const double2 ex = make_double2(a * un.x, a * un.y);
-                double xr = pr, xi = pi;
-                if (valid && C.pred) predict(A, C, k, xr, xi);
-                bool open = valid;
-                Update u{};
-                if constexpr (FMM) {
-                    for (int it = 0; it < FMM_POLISH_STEPS; ++it) {
-                        PSums S;
-                        zero(S);
-                        int cell;
-                        double2 f, f1, f2, g;
-                        double q;
-                        fmm_far(A.fmm[B.r], xr, xi, cell, f, f1, f2, g, q, false);
-                        const int n_near = fmm_near(A.fmm[B.r], cell, [&](const double4 &s4) {
-                            if constexpr (EQUAL)
-                                add_star_polish<EQUAL>(S, xr, xi, make_double2(s4.x, s4.y));
-                            else add_star_polish<EQUAL>(S, xr, xi, s4);
-                        });
-                        fmm_count(ptl, open, n_near, n_stars);
-                        S.s0r += f.x; S.s0i += f.y;
-                        S.s2r -= f1.x; S.s2i += 0.5 * f1.y;
-                        S.s3r += 0.5 * f2.x; S.s3i += 0.5 * f2.y;
-                        S.q += q;
-                        const Update v = polish_finish<EQUAL>(S, xr, xi, m0, ex, gamma, a, a1,
-                                                              tol_step2, tol_mu, k);
-                        if (open) {
-                            u = v;
-                            n_xsteps += 1;
-                            if (v.flag) {
-                                open = false;
-                            } else {
-                                xr = v.zr;
-                                xi = v.zi;
-                            }
-                        }
-                        if (!__ballot(open)) break;
-                    }
-                } else {
-                    // one Newton step per root from direct sums, exactly as
-                    // the first pass of the row takes it: the whole wave per
-                    // root when the block holds few roots, else one lane each
-                    if (__popcll(vmask) <= SPARSE_MAX) {
-                        unsigned long long mm = vmask;
-                        while (mm) {
-                            const int l = __ffsll((long long)mm) - 1;
-                            mm &= mm - 1;
-                            const double xk = __shfl(xr, l, 64), yk = __shfl(xi, l, 64);
-                            PSums S;
-                            zero(S);
-#pragma unroll 4
-                            for (int i = lane; i < n_stars; i += 64)
-                                add_star_polish<EQUAL>(S, xk, yk, stars[i]);
-                            wave_sum(S.s0r); wave_sum(S.s0i); wave_sum(S.s2r); wave_sum(S.s2i);
-                            wave_sum(S.s3r); wave_sum(S.s3i); wave_sum(S.q);
-                            const Update v = polish_finish<EQUAL>(S, xk, yk, m0, ex, gamma, a,
-                                                                  a1, tol_step2, tol_mu, k0 + l);
-                            if (lane == l) u = v;
-                        }
-                    } else {
-                        PSums S;
-                        zero(S);
-                        stream_tiles_grouped(stars, n_stars, reinterpret_cast<T *>(tiles),
-                                             [&](auto g, const T *r) {
-                                                 add_star_polish_group<EQUAL, decltype(g)::value>(
-                                                     S, xr, xi, r);
-                                             });
-                        u = polish_finish<EQUAL>(S, xr, xi, m0, ex, gamma, a, a1, tol_step2, tol_mu,
-                                                 k);
-                    }
-                    open = valid && !u.flag;
-                }
-                // (with direct sums the finisher counts the rows the front keeps)
-                if (__ballot(open)) {
-                    if (lane == 0) atomicMin(&A.xrows[B.f], done);   // tell the other blocks now
-                    break;
-                }
-                if (valid) put(A, C, k, u);
-                double t1r = valid ? u.zr : 0.0, t1i = valid ? u.zi : 0.0;
-                double t2r = valid ? u.zr * u.zr - u.zi * u.zi : 0.0;
-                double t2i = valid ? 2.0 * u.zr * u.zi : 0.0;
-                const double b2 = valid ? u.zr * u.zr + u.zi * u.zi : 0.0, b1 = sqrt(b2);
-                const double ue = valid ? u.err : 0.0;
-                double q_e = ue, q_e2 = ue * (2.0 * b1 + ue), q_a = b1, q_a2 = b2;
-                wave_sum(t1r); wave_sum(t1i); wave_sum(t2r); wave_sum(t2i);
-                wave_sum(q_e); wave_sum(q_e2); wave_sum(q_a); wave_sum(q_a2);
-                if (lane == 0) {
-                    const int64_t sl = 2 * ((int64_t)x * A.nvslots + B.vslot);
-                    A.vieta[sl] = make_double4(t1r, t1i, t2r, t2i);
-                    A.vieta[sl + 1] = make_double4(q_e, q_e2, q_a, q_a2);
-                }
-                pr = u.zr;
-                pi = u.zi;
-                done = x;
-            }
-        }
-        if (lane == 0) atomicMin(&A.xrows[B.f], done);
-    }
-    // updates of the pass: one per active root, or its Newton steps (those of
-    // further rows included)
-    int n_upd = (n_steps >= 0 ? n_steps : 0) + n_xsteps;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) n_upd += __shfl_xor(n_upd, off, 64);
-    if (n_steps < 0) n_upd += n_act;
-    if (lane == 0 && n_upd) atomicAdd(B.upd, n_upd);
-    if constexpr (FMM) fmm_flush(A.fmm_tally, FMM_T_POLISH, ptl);
+    // rows beyond `done` are not kept: tells the other blocks, and the finisher
+    if (xmax > 0 && lane == 0) atomicMin(&A.xrows[B.f], done);
 }
 
 template <bool EQUAL, bool FMM>
@@ -1713,7 +1876,11 @@ row_sums(const Front *__restrict__ fronts, const Real *__restrict__ reals,
 
 constexpr int CONTROL_THREADS = 256;
 constexpr int MAX_FRONTS = 1 << 16;
+// Polish passes a row may take before it is retried another way: a root with
+// direct sums is given POLISH_STEPS Newton steps in all, one with multipole
+// sums as many in each of three passes.
 constexpr int MAX_POLISH = 3;
+__host__ __device__ constexpr int max_polish_passes(bool fmm) { return fmm ? MAX_POLISH : 1; }
 constexpr int F32_STALL = 4;
 
 // Puts a front at the start of its (new) row.  Mixed mode: a row with a
@@ -1806,7 +1973,8 @@ __device__ __forceinline__ bool row_identities_hold(const Real &R, double2 u, co
 // `st` (the control kernel's LDS copy of the states) may be null.
 __device__ __attribute__((noinline)) int advance_front(Front &fr, int f, int32_t c, const double4 *rs, Front *fronts,
                              int32_t *st, int f0, Control *ctl, const Real *reals,
-                             const double2 *unit, int max_cold, int max_warm, int predictor)
+                             const double2 *unit, int max_cold, int max_warm, int predictor,
+                             int max_polish)
 {
     int partner = -1;
     fr.npass += 1;
@@ -1839,7 +2007,7 @@ __device__ __attribute__((noinline)) int advance_front(Front &fr, int f, int32_t
                 partner = row_converged(fr, f, fronts, st, f0, predictor);
             else
                 retry = true;
-        } else if (++fr.passes >= MAX_POLISH) {
+        } else if (++fr.passes >= max_polish) {
             retry = true;
         }
         if (retry) {
@@ -1918,11 +2086,13 @@ aberth_control(Front *__restrict__ fronts, int32_t *__restrict__ counts, int32_t
                Control *__restrict__ ctl, int32_t max_cold, int32_t max_warm,
                int32_t *__restrict__ workflag, const double4 *__restrict__ vsum,
                const Real *__restrict__ reals, const double2 *__restrict__ unit,
-               int32_t fronts_per_group, int32_t predictor, int32_t *__restrict__ passupd)
+               int32_t fronts_per_group, int32_t predictor, int32_t *__restrict__ passupd,
+               int32_t max_polish)
 {
     __shared__ int32_t st[4096];
     __shared__ int32_t s_active, s_live;
-    __shared__ unsigned long long s_upd[4], s_star[4];   // by phase; [3]: fast-root FP64 passes
+    // by phase; [3]: fast-root FP64 passes; [4]: FP64 updates without a root-root sum
+    __shared__ unsigned long long s_upd[5], s_star[5];
     const int tid = threadIdx.x;
     const int f0 = blockIdx.x * fronts_per_group;
     const int f1 = min(n_fronts, f0 + fronts_per_group);
@@ -1930,8 +2100,8 @@ aberth_control(Front *__restrict__ fronts, int32_t *__restrict__ counts, int32_t
         s_active = 0;
         s_live = 0;
     }
-    if (tid < 4) s_upd[tid] = s_star[tid] = 0ull;
-    unsigned long long my_upd[4] = {0ull, 0ull, 0ull, 0ull}, my_star[4] = {0ull, 0ull, 0ull, 0ull};
+    if (tid < 5) s_upd[tid] = s_star[tid] = 0ull;
+    unsigned long long my_upd[5] = {}, my_star[5] = {};
     for (int f = f0 + tid; f < f1; f += CONTROL_THREADS) st[f - f0] = fronts[f].state;
     __syncthreads();
     for (int f = f0 + tid; f < f1; f += CONTROL_THREADS) {
@@ -1939,23 +2109,27 @@ aberth_control(Front *__restrict__ fronts, int32_t *__restrict__ counts, int32_t
         Front fr = fronts[f];
         atomicOr(&s_live, 1 << fr.phase);
         {   // this round's updates of the front, by pass kind (FLOP counts weigh them by N)
-            const unsigned long long u = (unsigned)passupd[f];
-            passupd[f] = 0;
-            const unsigned long long us = u * (unsigned)reals[fr.real].n_stars;
+            const unsigned long long u = (unsigned)passupd[2 * f];
+            const unsigned long long up = (unsigned)passupd[2 * f + 1];
+            passupd[2 * f] = 0;
+            passupd[2 * f + 1] = 0;
+            const unsigned long long ns = (unsigned)reals[fr.real].n_stars;
             my_upd[fr.phase] += u;
-            my_star[fr.phase] += us;
+            my_star[fr.phase] += u * ns;
+            my_upd[4] += up;
+            my_star[4] += up * ns;
             if (fr.phase == PH_F64 && fast_roots_pass(fr, reals[fr.real])) {
-                my_upd[3] += u;
-                my_star[3] += us;
+                my_upd[3] += u - up;
+                my_star[3] += (u - up) * ns;
             }
         }
         const int32_t c = counts[f];
         counts[f] = 0;
         advance_front(fr, f, c, vsum + 2 * f, fronts, st, f0, ctl, reals, unit, max_cold,
-                      max_warm, predictor);
+                      max_warm, predictor, max_polish);
         fronts[f] = fr;
     }
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < 5; ++q) {
         if (my_upd[q]) {
             atomicAdd(&s_upd[q], my_upd[q]);
             atomicAdd(&s_star[q], my_star[q]);
@@ -1978,6 +2152,10 @@ aberth_control(Front *__restrict__ fronts, int32_t *__restrict__ counts, int32_t
         if (s_upd[3]) {
             atomicAdd(&ctl->updates_fast, s_upd[3]);
             atomicAdd(&ctl->star_updates_fast, s_star[3]);
+        }
+        if (s_upd[4]) {
+            atomicAdd(&ctl->updates_plain, s_upd[4]);
+            atomicAdd(&ctl->star_updates_plain, s_star[4]);
         }
     }
     int mine = 0;
@@ -2093,13 +2271,14 @@ struct WorkShare {
     Front fr;
     int32_t task_f, task_c;   // claimed task (task_f < 0: leave)
     int32_t begin, end;       // blocks of the task
-    int32_t count, upd;       // the pass's totals over this task
+    int32_t count, upd[2];    // the pass's totals over this task (BlockCtx)
     int32_t go;               // the work group owns the front and runs its next pass
     int32_t partner;          // front whose cold start just ended here (else -1)
     int64_t src_off, dst_off;
     int32_t src_par, dst_par;
-    // per phase, and [3] fast-root FP64 passes: updates, updates x N
-    unsigned long long upd_tot[4], star_tot[4];
+    // updates, and updates x N: per phase, [3] fast-root FP64 passes, [4] FP64
+    // updates without a root-root sum
+    unsigned long long upd_tot[5], star_tot[5];
 };
 
 // What bounds short passes is not their sums but what surrounds them: a
@@ -2127,7 +2306,7 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
     double4 *tiles = reinterpret_cast<double4 *>(reinterpret_cast<T *>(tiles_all) + wave * 128);
-    if (threadIdx.x < 4) W.upd_tot[threadIdx.x] = W.star_tot[threadIdx.x] = 0ull;
+    if (threadIdx.x < 5) W.upd_tot[threadIdx.x] = W.star_tot[threadIdx.x] = 0ull;
     for (;;) {
         if (threadIdx.x == 0) {
             int tf = -1, tq = 0;
@@ -2179,7 +2358,7 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
                     W.begin = tc * c;
                     W.end = min((tc + 1) * c, bpf);
                     W.count = 0;
-                    W.upd = 0;
+                    W.upd[0] = W.upd[1] = 0;
                 }
             }
             __syncthreads();
@@ -2187,7 +2366,7 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
             const int ph = __builtin_amdgcn_readfirstlane(W.fr.phase);
             for (int blk = __builtin_amdgcn_readfirstlane(W.begin) + wave; blk < end; blk += waves) {
                 BlockCtx<T> B;
-                enter_fq(A, &W.fr, tf, blk, &W.count, &W.upd, B);
+                enter_fq(A, &W.fr, tf, blk, &W.count, W.upd, B);
                 if (ph == PH_F64)
                     sweep_f64_pass<EQUAL, FMM>(A, B, tiles);
                 else if (ph == PH_F32)
@@ -2210,7 +2389,8 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
                     // every task publishes its writes before counting itself
                     if (lane == 0) {
                         if (W.count) atomicAdd(&A.counts[tf], W.count);
-                        if (W.upd) atomicAdd(&A.passupd[tf], W.upd);
+                        if (W.upd[0]) atomicAdd(&A.passupd[2 * tf], W.upd[0]);
+                        if (W.upd[1]) atomicAdd(&A.passupd[2 * tf + 1], W.upd[1]);
                     }
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
                     if (lane == 0) last = atomicAdd(&fdone[tf], 1) + 1 == nt;
@@ -2220,9 +2400,11 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
                         if (lane == 0) {
                             fdone[tf] = 0;
                             W.count = load_relaxed(&A.counts[tf]);
-                            W.upd = load_relaxed(&A.passupd[tf]);
+                            W.upd[0] = load_relaxed(&A.passupd[2 * tf]);
+                            W.upd[1] = load_relaxed(&A.passupd[2 * tf + 1]);
                             A.counts[tf] = 0;
-                            A.passupd[tf] = 0;
+                            A.passupd[2 * tf] = 0;
+                            A.passupd[2 * tf + 1] = 0;
                         }
                     }
                 }
@@ -2232,25 +2414,29 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
                     if (ph == PH_POLISH) sum_row(A.vieta + 2 * (int64_t)fr.blk0, bpf, rs);
                     int finished = 0, xr = 0, dir0 = 0;
                     if (lane == 0) {
-                        const unsigned long long u = (unsigned)W.upd;
-                        const unsigned long long us = u * (unsigned)R->n_stars;
+                        const unsigned long long u = (unsigned)W.upd[0], up = (unsigned)W.upd[1];
+                        const unsigned long long ns = (unsigned)R->n_stars;
                         W.upd_tot[ph] += u;
-                        W.star_tot[ph] += us;
+                        W.star_tot[ph] += u * ns;
+                        W.upd_tot[4] += up;
+                        W.star_tot[4] += up * ns;
                         if (ph == PH_F64 && fast_roots_pass(fr, *R)) {
-                            W.upd_tot[3] += u;
-                            W.star_tot[3] += us;
+                            W.upd_tot[3] += u - up;
+                            W.star_tot[3] += (u - up) * ns;
                         }
                         dir0 = fr.dir;
                         const int row0 = fr.row;
+                        const bool runs_on = ph == PH_POLISH || (ph == PH_F64 && chain_pass(A, fr));
                         partner = advance_front(fr, tf, W.count, rs, fronts_w, nullptr, 0, A.ctl,
-                                                A.reals, A.unit, max_cold, max_warm, A.predictor);
+                                                A.reals, A.unit, max_cold, max_warm, A.predictor,
+                                                max_polish_passes(FMM));
                         fr.par ^= 1;   // the pass wrote the other buffer
-                        if (A.xrows && ph == PH_POLISH) {
+                        if (A.xrows && runs_on) {
                             // further rows the pass finished in every block (see polish_pass)
                             xr = load_relaxed(&A.xrows[tf]);
                             __hip_atomic_store(&A.xrows[tf], R->xrows, __ATOMIC_RELAXED,
                                                __HIP_MEMORY_SCOPE_AGENT);
-                            if (!(dir0 != 0 && fr.state == FRONT_ACTIVE && fr.phase == PH_POLISH &&
+                            if (!(dir0 != 0 && fr.state == FRONT_ACTIVE && fr.phase == ph &&
                                   fr.row == row0 + dir0))
                                 xr = 0;
                         }
@@ -2260,9 +2446,11 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
                     int moved = 0;
                     for (int x = 1; x <= xr; ++x) {
                         double4 rx[2];
-                        sum_row(A.vieta + 2 * ((int64_t)x * A.nvslots + fr.blk0), bpf, rx);
+                        if (ph == PH_POLISH)
+                            sum_row(A.vieta + 2 * ((int64_t)x * A.nvslots + fr.blk0), bpf, rx);
                         int ok = 0;
-                        if (lane == 0 && row_identities_hold(*R, A.unit[fr.row], rx)) {
+                        if (lane == 0 &&
+                            (ph != PH_POLISH || row_identities_hold(*R, A.unit[fr.row], rx))) {
                             row_converged(fr, tf, fronts_w, nullptr, 0, A.predictor);
                             ok = 1;
                         }
@@ -2271,14 +2459,34 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
                         moved = x;
                     }
                     if (lane == 0) {
-                        if constexpr (!FMM) {
-                            // the further rows the front keeps, one Newton step per root
-                            // each, as the first pass of each row would have counted them
-                            if (moved) {
-                                const unsigned long long ux =
-                                    (unsigned long long)moved * (unsigned)R->n_r;
-                                W.upd_tot[PH_POLISH] += ux;
-                                W.star_tot[PH_POLISH] += ux * (unsigned)R->n_stars;
+                        if (A.xrows) {
+                            // what the further rows took: counted for those the front
+                            // keeps, cleared for its next pass
+                            unsigned long long *c =
+                                A.xcount + 2 * (int64_t)tf * (A.xrow_max + 1);
+                            unsigned long long nu = 0, nn = 0;
+                            for (int x = 1; x <= A.xrow_max; ++x) {
+                                if (x <= moved) {
+                                    nu += load_relaxed(&c[2 * x]);
+                                    nn += load_relaxed(&c[2 * x + 1]);
+                                }
+                                for (int v = 0; v < 2; ++v)
+                                    __hip_atomic_store(&c[2 * x + v], 0ull, __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_AGENT);
+                            }
+                            const unsigned long long ns = (unsigned)R->n_stars;
+                            W.upd_tot[ph] += nu;
+                            W.star_tot[ph] += nu * ns;
+                            if (ph == PH_F64) {
+                                W.upd_tot[4] += nu;
+                                W.star_tot[4] += nu * ns;
+                            }
+                            if constexpr (FMM) {
+                                FmmTally tl;
+                                tl.near = nn;
+                                tl.far = nu;
+                                tl.far_n = nu * ns;
+                                fmm_flush(A.fmm_tally, ph == PH_F64 ? FMM_T_F64 : FMM_T_POLISH, tl);
                             }
                         }
                         // its first pass takes the previous row from the output
@@ -2333,12 +2541,13 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
     }
     // the work group's share of the totals
     if (threadIdx.x == 0) {
-        unsigned long long *dst[4][2] = {{&A.ctl->updates, &A.ctl->star_updates},
+        unsigned long long *dst[5][2] = {{&A.ctl->updates, &A.ctl->star_updates},
                                          {&A.ctl->updates_f32, &A.ctl->star_updates_f32},
                                          {&A.ctl->polish_updates, &A.ctl->star_updates_polish},
-                                         {&A.ctl->updates_fast, &A.ctl->star_updates_fast}};
+                                         {&A.ctl->updates_fast, &A.ctl->star_updates_fast},
+                                         {&A.ctl->updates_plain, &A.ctl->star_updates_plain}};
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < 5; ++k) {
             if (!W.upd_tot[k]) continue;
             atomicAdd(dst[k][0], W.upd_tot[k]);
             atomicAdd(dst[k][1], W.star_tot[k]);
@@ -2701,7 +2910,8 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         // predictor): every field with multipole sums, small fields with direct
         // ones
         R.xrows = 0;
-        if (mixed && p->schedule == MLCC_SCHEDULE_PERSISTENT && p->predictor > 0) {
+        if (p->schedule == MLCC_SCHEDULE_PERSISTENT &&
+            (mixed ? p->predictor > 0 : p->predictor == 2)) {
             if (p->star_sums == MLCC_STARS_FMM) R.xrows = FMM_XROWS;
             else if (h.n <= XROWS_DIRECT_MAX_N) R.xrows = DIRECT_XROWS;
         }
@@ -2778,7 +2988,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
     MLCC_TRY(c->flagrow.reserve((size_t)it_total * sizeof(int32_t)));
     MLCC_TRY(c->fronts.reserve((size_t)(F + 1) * sizeof(Front)));
     MLCC_TRY(c->counts.reserve((size_t)F * sizeof(int32_t)));
-    MLCC_TRY(c->passupd.reserve((size_t)F * sizeof(int32_t)));
+    MLCC_TRY(c->passupd.reserve((size_t)2 * F * sizeof(int32_t)));
     MLCC_TRY(c->control.reserve(sizeof(Control)));
     MLCC_TRY(c->fmm_tally.reserve((size_t)FMM_STRIPES * FMM_STRIPE_U64 * sizeof(uint64_t)));
     MLCC_TRY(c->etab.reserve((size_t)(m + 1) * sizeof(double2)));
@@ -2791,6 +3001,10 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
     MLCC_TRY(c->vieta.reserve((size_t)2 * (xrow_max + 1) * nblocks * sizeof(double4)));
     MLCC_TRY(c->vsum.reserve((size_t)2 * F * sizeof(double4)));
     if (mixed) MLCC_TRY(c->errbuf.reserve((size_t)it_total * sizeof(double)));
+    // FP64 sweeps with the quadratic predictor: F' of the last rows
+    const bool chain_corr = !mixed && p->predictor == 2;
+    if (chain_corr)
+        MLCC_TRY(c->fprime.reserve((size_t)FP_RING * it_total * sizeof(double2)));
     MLCC_TRY(c->reals_d.reserve((size_t)n_real * sizeof(Real)));
     MLCC_TRY(c->sheet.reserve(std::max<size_t>(1, sheet_host.size()) * sizeof(double)));
     // With multipole sums the kernels take each field's stars in cell order,
@@ -2835,7 +3049,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
     MLCC_HIP(hipMemsetAsync(c->counts.p, 0, F * sizeof(int32_t), c->stream));
     MLCC_HIP(hipMemsetAsync(c->fmm_tally.p, 0,
                             (size_t)FMM_STRIPES * FMM_STRIPE_U64 * sizeof(uint64_t), c->stream));
-    MLCC_HIP(hipMemsetAsync(c->passupd.p, 0, F * sizeof(int32_t), c->stream));
+    MLCC_HIP(hipMemsetAsync(c->passupd.p, 0, 2 * F * sizeof(int32_t), c->stream));
     if (equal)
         hipLaunchKernelGGL(seed_centres<double2>, dim3((unsigned)ngrid), dim3(64), 0, c->stream,
                            stars2, c->reals_d.as<Real>(), c->fronts.as<Front>(),
@@ -2882,6 +3096,8 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         A.vieta = c->vieta.as<double4>();
         A.predictor = p->predictor;
         A.errbuf = mixed ? c->errbuf.as<double>() : nullptr;
+        A.fprime = chain_corr ? c->fprime.as<double2>() : nullptr;
+        A.fp_stride = it_total;
         A.sheet = c->sheet.as<double>();
         A.fmm = fmm_dev;
     };
@@ -2976,7 +3192,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
                                rs, c->fronts.as<Front>(), c->counts.as<int32_t>(), F, dctl,
                                max_cold, max_warm, wf, c->vsum.as<double4>(),
                                c->reals_d.as<Real>(), c->etab.as<double2>(), fronts_per_group,
-                               p->predictor, c->passupd.as<int32_t>());
+                               p->predictor, c->passupd.as<int32_t>(), max_polish_passes(fmm_on));
             hipLaunchKernelGGL(control_end, dim3(1), dim3(64), 0, rs, dctl, wf);
             parity ^= 1;
         }
@@ -3057,7 +3273,9 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         const size_t o_tasks = (sizeof(PQueue) + 255) & ~(size_t)255;
         const size_t o_seq = o_tasks + (size_t)cap * sizeof(int2);
         const size_t o_fdone = o_seq + (size_t)cap * SEQ_STRIDE * sizeof(unsigned long long);
-        const size_t o_xrows = o_fdone + (((size_t)F * sizeof(int32_t) + 255) & ~(size_t)255);
+        const size_t o_xcount = o_fdone + (((size_t)F * sizeof(int32_t) + 255) & ~(size_t)255);
+        const size_t o_xrows =
+            o_xcount + (xrows_on ? (size_t)F * (xrow_max + 1) * 2 * sizeof(unsigned long long) : 0);
         MLCC_TRY(c->pq.reserve(o_xrows + (size_t)F * sizeof(int32_t)));
         char *base = static_cast<char *>(c->pq.p);
         PQueue *dq = reinterpret_cast<PQueue *>(base);
@@ -3078,7 +3296,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         for (size_t i = 0; i < t0.size(); ++i) s0[i * SEQ_STRIDE] = i + 1;
         PQueue hq{};
         hq.tail = (unsigned long long)t0.size();
-        MLCC_HIP(hipMemsetAsync(base, 0, o_fdone + (size_t)F * sizeof(int32_t), rs));
+        MLCC_HIP(hipMemsetAsync(base, 0, o_xrows, rs));
         MLCC_HIP(hipMemcpyAsync(dq, &hq, sizeof hq, hipMemcpyHostToDevice, rs));
         MLCC_HIP(hipMemcpyAsync(dtasks, t0.data(), t0.size() * sizeof(int2), hipMemcpyHostToDevice,
                                 rs));
@@ -3090,6 +3308,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         auto set_xrows = [&](auto &A) {
             A.xrows = xrows_on ? dxrows : nullptr;
             A.xrow_max = xrow_max;
+            A.xcount = reinterpret_cast<unsigned long long *>(base + o_xcount);
             A.nvslots = (int32_t)nblocks;
         };
         const void *kfn =
@@ -3409,13 +3628,15 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
                 (int64_t)(fmm_far[0] + fmm_far_polish[0] + fmm_far_f32[0]);
         }
         stats->algorithmic_flop = 29.0 * star64 + far64 +
-                                  20.0 * (double)(h.star_updates - h.star_updates_fast) -
-                                  10.0 * (double)(h.updates - h.updates_fast);
+                                  20.0 * (double)(h.star_updates - h.star_updates_fast -
+                                                  h.star_updates_plain) -
+                                  10.0 * (double)(h.updates - h.updates_fast - h.updates_plain);
         stats->algorithmic_flop_sweep_roots =
             20.0 * (double)h.star_updates_fast - 10.0 * (double)h.updates_fast;
         if (n_real == 1) {   // a rectangular field's extra roots: 10 FLOP per root term each
             const double ex = 10.0 * (double)sheet_poly(c->reals[0]).n_extra;
-            stats->algorithmic_flop += ex * (double)(h.updates - h.updates_fast);
+            stats->algorithmic_flop +=
+                ex * (double)(h.updates - h.updates_fast - h.updates_plain);
             stats->algorithmic_flop_sweep_roots += ex * (double)h.updates_fast;
         }
         stats->algorithmic_flop_f32 =

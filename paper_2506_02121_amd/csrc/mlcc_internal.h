@@ -151,6 +151,8 @@ struct Control {
     unsigned long long star_updates_polish;
     unsigned long long updates_fast;      // FP64 Aberth updates of warm FP64-mode rows, whose
     unsigned long long star_updates_fast; // root-root terms run in FP32 (and their star counts)
+    unsigned long long updates_plain;     // FP64 Aberth updates that took the correction from the
+    unsigned long long star_updates_plain; // chain, without a root-root sum (and their star counts)
 };
 
 // Tallies of the fast-multipole star sums behind the algorithmic FLOP count,
@@ -188,7 +190,8 @@ struct Ctx {
     DevBuf flagrow;   // int32[F * n_r]: row at which the root was flagged
     DevBuf fronts;    // Front[F]
     DevBuf counts;    // int32[F]: unflagged roots after the last sweep
-    DevBuf passupd;   // int32[F]: roots updated by the last round's pass
+    DevBuf passupd;   // int32[2 * F]: roots updated by the last pass, and those of them
+                      // without a root-root sum
     DevBuf control;   // Control
     DevBuf fmm_tally; // uint64[FMM_STRIPES * FMM_STRIPE_U64]: multipole tallies
     DevBuf etab;      // double2[m + 1]: (1 - kappa_s) e^{-i phi_j}
@@ -199,6 +202,7 @@ struct Ctx {
     DevBuf workflags; // int32[poll batch]: phases active in round i
     DevBuf vieta;     // double4[2 * blocks]: per-block row sums and error terms (mixed mode)
     DevBuf errbuf;    // double[F * n_r]: estimated error of each polished root
+    DevBuf fprime;    // double2[FP_RING][F * n_r]: F' at the accepted roots of the last rows
     DevBuf vsum;      // double4[2 * F]: each front's row sums (mixed mode)
     DevBuf pq;        // persistent scheduler: queue header, task ring, slot sequence, pass counts
     DevBuf reals_d;   // Real[n_real]

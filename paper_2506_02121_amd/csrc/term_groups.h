@@ -82,9 +82,8 @@ __device__ __forceinline__ void wave_sync()
 // tile ends with groups of half, a quarter ... of that, so the terms meet the
 // sums in record order.  Indices past n-1 are clamped on load; `lds` holds
 // two tiles of the wave's own.
-template <class T, class Group>
-__device__ __forceinline__ void stream_tiles_grouped(const T *__restrict__ p, int n, T *lds,
-                                                     Group &&group)
+template <class Src, class T, class Group>
+__device__ __forceinline__ void stream_tiles_grouped(const Src p, int n, T *lds, Group &&group)
 {
     constexpr int G = MLCC_RCP_GROUP;
     static_assert(G == 1 || G == 2 || G == 4 || G == 8, "group of 1, 2, 4 or 8 terms");

@@ -1,0 +1,80 @@
+"""FP64 rows that take the Aberth correction from their chains (quadratic
+predictor) against the same rows with the root-root sum (linear predictor,
+which never does): same columns, same roots.  Sizes at the edges of a block of
+64 roots, subchains longer than the ring that keeps F' of the last rows and
+than the further rows of a pass, and coarse phase grids, whose predictions
+leave roots for the root-root sum.
+
+Tolerance: both forms accept a root once |step| < 1e-9 or |F| is below ~5e-10,
+and the value kept is one step further; on these fields that leaves less than
+1e-11 of the field's size."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2506_02121_amd import fields
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mlcc():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_2506_02121_amd import mlcc as m
+    return m
+
+
+def dev(a):
+    return torch.as_tensor(np.array(a, copy=True), dtype=torch.float64).cuda()
+
+
+def solve(ctx, m_steps, **kw):
+    r = ctx.find_critical_curves(m_steps, caustics=True, **kw)
+    torch.cuda.synchronize()
+    return [t.cpu().numpy() for t in r[:5]], r[5]
+
+
+# 1 and 8 stars: blocks of few roots; 9: the first above them; 31 .. 33 and 65:
+# around one block and two; 300: a front of ten blocks, through the queue
+@pytest.mark.parametrize("n", [1, 8, 9, 31, 32, 33, 65, 300])
+@pytest.mark.parametrize("star_sums,precision", [("direct", "fp64"), ("fmm", "fp64"),
+                                                 ("direct", "fp64_r32")])
+@pytest.mark.parametrize("m_steps,n_sub", [(400, 5), (240, 1), (48, 1)])
+def test_same_rows_as_with_root_sums(mlcc, n, star_sums, precision, m_steps, n_sub):
+    print("[case]", n, star_sums, precision, m_steps, n_sub, flush=True)
+    ctx = mlcc.Context(0)
+    f = fields.random_field(61, n, kappa_star=0.4, kappa_s=0.05, gamma=0.3,
+                            masses="equal" if n % 2 else "salpeter")
+    ctx.set_lenses(dev(f.x), dev(f.y), dev(f.m), f.kappa_s, f.gamma)
+    kw = dict(n_subchains=n_sub, precision=precision, star_sums=star_sums)
+    a, sa = solve(ctx, m_steps, **kw)
+    b, _ = solve(ctx, m_steps, predictor=1, **kw)
+    c, sc = solve(ctx, m_steps, schedule="rounds", **kw)
+    ctx.close()
+    for x, y in zip(a, c):
+        assert np.array_equal(x.view(np.uint8), y.view(np.uint8))
+    for k in ("root_updates", "polish_updates", "algorithmic_flop_sweep_roots"):
+        assert sa[k] == sc[k], k
+    # the coarse grid's columns may be continued differently by the two predictors
+    size = 1.0 + np.abs(b[0]).max() + np.abs(b[1]).max()
+    za, zb = a[0] + 1j * a[1], b[0] + 1j * b[1]
+    if m_steps > 48:
+        assert np.array_equal(a[4], b[4])
+        assert np.abs(za - zb).max() < 1e-11 * size
+    else:
+        for p, q in zip(za, zb):
+            assert np.abs(p[:, None] - q[None, :]).min(axis=1).max() < 1e-11 * size
+
+
+def test_rectangular_sheet(mlcc):
+    """The sheet's share of F' enters the divided differences too."""
+    ctx = mlcc.Context(0)
+    f = fields.make_rect_field(np.random.default_rng(5), 70, 0.5, 0.0, 0.3, 13.0 / 7.0, 21, "equal")
+    ctx.set_lenses_rect(dev(f.x), dev(f.y), dev(f.m), f.kappa_s, f.gamma, *f.sheet)
+    a, _ = solve(ctx, 800, n_subchains=5)
+    b, _ = solve(ctx, 800, n_subchains=5, predictor=1)
+    ctx.close()
+    size = 1.0 + np.abs(b[0]).max() + np.abs(b[1]).max()
+    assert np.array_equal(a[4], b[4])
+    assert np.abs((a[0] - b[0]) + 1j * (a[1] - b[1])).max() < 1e-11 * size
