@@ -51,16 +51,13 @@ typedef enum {
                       2^-53 for a correctly rounded division); consecutive star terms,
                       and consecutive root-root terms, are taken in groups of eight that
                       share one refined reciprocal of the product of their eight |d|^2.
-                      With predictor = 2, a warm row with three finished rows behind it
-                      takes the correction 2 S1 - R, which equals -F''/(2 F') at a root,
-                      from F' along the root's chain (second divided differences over
-                      this iterate and the last two rows) in place of the root-root sum R,
-                      as long as the step stays within a twentieth of the root's basin and
-                      the correction's error moves the root by less than 1e-16; every
-                      other root takes the step with R.  With the persistent schedule such
-                      a pass goes on through up to 7 further rows of its front (multipole
-                      star sums; direct sums for fields of at most 160 stars); the results
-                      are those of one row per pass */
+                      With predictor > 0, warm rows with three finished rows behind them
+                      are solved from the star field's Taylor expansion about a point of
+                      each root's chain (14 moments sum m_i u_i^k, every star entering them
+                      directly; used only where the terms left out stay below the sums'
+                      rounding), with the correction -F''/(2 F') that 2 S1 - R equals at a
+                      root, as long as |F F''/(2 F'^2)| < 0.05; every other root takes Aberth
+                      steps with the root-root sum */
     MLCC_MIXED = 1,/* Aberth sweeps in FP32 (FP64 star distances, FP32 sums per tile of
                       64 stars carried in FP64), every root finished by FP64 Newton
                       polish passes that accept a root on the same cutoffs as the
@@ -70,12 +67,11 @@ typedef enum {
                       the polish straight from the chain prediction (predictor > 0),
                       else after one FP32 sweep.  A row the polish does not settle
                       gets one FP32 sweep and the polish again, then restarts from
-                      its start values with FP64 Aberth sweeps.  With the persistent
-                      schedule and the chain predictor a polish pass whose roots are
-                      all accepted goes on through up to 7 further rows of its front
-                      (multipole star sums; direct sums for fields of at most 160
-                      stars); the results are those of one row per pass.  Results
-                      meet the same cutoffs as MLCC_FP64. */
+                      its start values with FP64 Aberth sweeps.  Warm rows with a chain
+                      prediction come from the expansions described for MLCC_FP64 (Newton
+                      steps where a root starts far from its zero), their row identities
+                      checked like a polish's; roots these leave open are polished.
+                      Results meet the same cutoffs as MLCC_FP64. */
     MLCC_FP64_R32 = 2 /* not the paper's precision: MLCC_FP64, except that in warm rows
                       the root-root sum R = sum_{r != k} 1/(z_k - z_r) of the Aberth
                       correction is formed in FP32 (each coordinate split into an FP32
@@ -91,8 +87,9 @@ typedef enum {
     MLCC_SCHEDULE_ROUNDS = 0,     /* global rounds: every front's pass, then a control kernel
                                      advancing all fronts; batches of rounds run as hipGraphs;
                                      per-kind kernel times in the stats */
-    MLCC_SCHEDULE_PERSISTENT = 1  /* the default: one persistent launch (captured into a
-                                     hipGraph and run from it), passes over runs of a front's
+    MLCC_SCHEDULE_PERSISTENT = 1  /* the default: a persistent launch (captured into a
+                                     hipGraph and run from it, again for the roots each run of
+                                     the expansions leaves open), passes over runs of a front's
                                      blocks from a device-side queue, each front advanced by the
                                      work group that finishes its pass, no global rounds.  Same
                                      results bit for bit; no front waits for the slowest pass
@@ -250,7 +247,8 @@ typedef struct {
     int64_t sweeps;          /* MLCC_SCHEDULE_ROUNDS: rounds that did work (one round = every
                                 pass kind once); MLCC_SCHEDULE_PERSISTENT: passes of the
                                 front that made the most */
-    int64_t root_updates;    /* FP64 Aberth root updates */
+    int64_t root_updates;    /* FP64 Aberth root updates; a root accepted from its expansion
+                                counts as one (in polish_updates for MLCC_MIXED) */
     int64_t root_updates_f32;/* FP32 Aberth root updates (MLCC_MIXED) */
     int64_t polish_updates;  /* FP64 Newton polish updates (MLCC_MIXED) */
     int64_t unconverged;     /* roots still unflagged in rows that hit a cap */
@@ -266,13 +264,15 @@ typedef struct {
     double polish_ms;        /* same, polish launches */
     int64_t sweep_launches, sweep_f32_launches, polish_launches;   /* launches that did work */
     double algorithmic_flop; /* FP64 sweeps, FP64 part: root_updates * 29 N (star terms) plus
-                                10 (2N - 1) per update that sums its root-root terms in FP64
-                                (not those that take the correction from the chain, nor warm
-                                rows of MLCC_FP64_R32); FMA = 2, add/mul/reciprocal = 1 */
+                                10 (2N - 1) per update that sums its root-root terms in FP64;
+                                rows from expansions: their star moments (per star term 133,
+                                with multipole sums per near star, plus 112 p for the series)
+                                and 508 per step; FMA = 2, add/mul/reciprocal = 1 */
     double algorithmic_flop_f32;    /* FP32 sweeps: root_updates_f32 * (29 N + 10 (2N - 1)) */
     double algorithmic_flop_polish; /* polish: polish_updates * 29 N (star terms only) */
-    double persistent_ms;    /* MLCC_SCHEDULE_PERSISTENT: GPU time of the one launch that runs
-                                every pass (timing != 0); the per-kind times above stay 0 */
+    double persistent_ms;    /* MLCC_SCHEDULE_PERSISTENT: GPU time of the launches that run the
+                                passes and the expansions, from the first to the end of the last
+                                (timing != 0); the per-kind times above stay 0 */
     int64_t persistent_launches;    /* 1 with MLCC_SCHEDULE_PERSISTENT, else 0 */
     double algorithmic_flop_sweep_roots; /* FP64 sweeps, FP32 part: 10 (2N - 1) per update of
                                 a warm MLCC_FP64_R32 row that sums its root-root terms (they

@@ -20,9 +20,11 @@
 //    polish again, then FP64 Aberth sweeps.
 //  * A warm row's first pass may start each root from an extrapolation
 //    along its chain instead of its previous-row value.
-//  * FP64 rows with enough rows behind them take the Aberth correction from
-//    their chains' F' instead of the O(N) sum over the other roots, and finish
-//    in one pass, or several rows in one (chain_rows).
+//  * Warm rows with a chain prediction, in either form, are solved from the
+//    star field's Taylor expansion about a point of each root's chain by a
+//    kernel of their own, in which every block of 64 roots goes through the
+//    rows of its front by itself (expand_rows); passes take the cold starts,
+//    the rows next to them and the roots an expansion leaves open.
 //  * A single-work-group control kernel after every round advances the
 //    fronts (device-side; the host polls a status block one batch ahead).
 //  * Converged roots are mapped to the caustic in the same kernel.
@@ -275,7 +277,6 @@ struct Update {
     double wr, wi;   // its image under the lens map
     bool flag;       // converged
     double err;      // Newton polish: estimated error of the new iterate
-    double dr, di;   // F' at the iterate the step was taken from (Aberth sweep)
 };
 
 // Degenerate iterate (on a star, or two iterates equal): nudge it off.
@@ -383,8 +384,6 @@ __device__ __forceinline__ Update take_step(const Sums &S, const FieldAt &Q, dou
     const double stepr = (Fr * Dr + Fi * Di) / den;
     const double stepi = (Fi * Dr - Fr * Di) / den;
     Update u;
-    u.dr = Q.Fpr;
-    u.di = Q.Fpi;
     u.zr = zr - stepr;
     u.zi = zi - stepi;
     const double aF = sqrt(Fr * Fr + Fi * Fi);
@@ -417,47 +416,11 @@ __device__ __forceinline__ Update finish(Sums S, double zr, double zi, double m0
                      tol_step2, tol_mu, k, sheet, n_poly);
 }
 
-// The Aberth correction without the root-root sum.  At a simple zero of F,
-// G = 2 S1 - R equals -F''/(2 F') (both are half the logarithmic derivative
-// of F'/F's deflation there), and F' depends on z alone, so its values at
-// this iterate and at the roots of the two rows before give F'' by second
-// divided differences: error O(h^2) for a row step h, where the sum over the
-// other roots' previous-row values is off by O(h).  `f1` and `f2` are F' at
-// z1 and z2, the chain's last two roots; `last` receives the size of the
-// second difference's share of G, which bounds what the third would add.
 __device__ __forceinline__ double2 cdiv(double2 p, double2 q)
 {
     const double inv = rcp_refined<2>(fma(q.x, q.x, q.y * q.y));
     return make_double2(fma(p.x, q.x, p.y * q.y) * inv, fma(p.y, q.x, -(p.x * q.y)) * inv);
 }
-
-__device__ __forceinline__ double2 chain_correction(double2 z, double2 f, double2 z1, double2 f1,
-                                                    double2 z2, double2 f2, double &last2)
-{
-    const double2 h1 = make_double2(z.x - z1.x, z.y - z1.y);
-    const double2 a = cdiv(make_double2(f.x - f1.x, f.y - f1.y), h1);
-    const double2 b = cdiv(make_double2(f1.x - f2.x, f1.y - f2.y),
-                           make_double2(z1.x - z2.x, z1.y - z2.y));
-    const double2 c = cdiv(make_double2(a.x - b.x, a.y - b.y),
-                           make_double2(z.x - z2.x, z.y - z2.y));
-    const double2 t = make_double2(h1.x * c.x - h1.y * c.y, h1.x * c.y + h1.y * c.x);
-    const double2 g = cdiv(make_double2(a.x + t.x, a.y + t.y), f);
-    last2 = 0.25 * (t.x * t.x + t.y * t.y) / (f.x * f.x + f.y * f.y);
-    return make_double2(-0.5 * g.x, -0.5 * g.y);
-}
-
-// A root takes steps D with the correction G from the chain while
-// |D G| < CHAIN_BASIN, which keeps it deep inside its zero's basin, and is
-// accepted when it is flagged and its G can be off by no more than moves the
-// new iterate by CHAIN_ERR (|D|^2 times the second difference's share of G),
-// far below the rounding of its sums.  A root this does not settle in
-// CHAIN_STEPS steps starts over with the Aberth step.
-constexpr double CHAIN_BASIN = 0.05;
-constexpr double CHAIN_ERR = 1e-16;
-constexpr int CHAIN_STEPS = 3;
-// F' of a front's last rows: rows are kept in a ring, so that the rows a pass
-// runs ahead leave the last two that its front keeps.
-constexpr int FP_RING = 16;
 
 // Resident waves per SIMD the sweep and polish kernels are compiled for
 // (register budget 512 / waves); the loops keep their instruction counts.
@@ -493,30 +456,18 @@ constexpr int STALL_START = 100;
 // Newton steps a root may take within one polish pass.
 constexpr int POLISH_STEPS = 3;
 
-// Further rows a polish pass with multipole sums may finish after its own
-// (persistent schedule; see polish_pass).
-#ifndef MLCC_FMM_XROWS
-#define MLCC_FMM_XROWS 7
+// Rows by which the blocks of a front of the mixed form may be ahead of its row
+// in expand_rows: their row sums wait there for the slowest block.
+#ifndef MLCC_AHEAD
+#define MLCC_AHEAD 1024
 #endif
-constexpr int FMM_XROWS = MLCC_FMM_XROWS;
+constexpr int AHEAD = MLCC_AHEAD;
 
-// With direct star sums a pass over a few dozen stars is short, and the
-// queue claim, the fences and the front's advance cost more than its sums:
-// fields of at most XROWS_DIRECT_MAX_N stars also let a polish pass go on
-// through up to DIRECT_XROWS further rows.  Larger fields keep one row per
-// pass: the front keeps only the rows every one of its blocks finished, so
-// with more blocks per front more of the further rows are thrown away, and
-// their passes are long enough to pay for the queue (measured on batches of
-// equal fields: 2.4x faster at N = 50, 1.7x at 100, 1.1x at 200, 3x slower
-// at 500).
-#ifndef MLCC_XROWS_DIRECT_MAX_N
-#define MLCC_XROWS_DIRECT_MAX_N 160
+// Resident waves per SIMD the expansion kernel is compiled for: its 28 moment
+// sums and the terms of four stars need more than the 168 registers of three.
+#ifndef MLCC_EXPAND_WAVES
+#define MLCC_EXPAND_WAVES 2
 #endif
-#ifndef MLCC_DIRECT_XROWS
-#define MLCC_DIRECT_XROWS 7
-#endif
-constexpr int XROWS_DIRECT_MAX_N = MLCC_XROWS_DIRECT_MAX_N;
-constexpr int DIRECT_XROWS = MLCC_DIRECT_XROWS;
 
 // ---------------------------------------------------------------------------
 // Fast multipole star sums (Sec. 4.1: near stars directly, far stars through
@@ -829,33 +780,22 @@ template <class T> struct RoundArgs {
     double *out_re, *out_im, *caus_re, *caus_im;
     double2 *bnd;
     int32_t *counts;
-    int32_t *passupd;  // per front, two counts of the pass: updates, and those of them that
-                       // took no root-root sum
+    int32_t *passupd;  // per front: roots updated by this round's pass (the control kernel sums them)
     Control *ctl;
     unsigned long long *fmm_tally;   // multipole tallies (FMM_STRIPES copies)
     double4 *vieta;    // two per block: row sums, and their error terms
     double *errbuf;    // estimated error of each polished root
-    // F' at the accepted roots of the front's last rows, row j in slot
-    // j mod FP_RING of fp_stride elements (null: the sweeps always form the
-    // root-root sums)
-    double2 *fprime;
-    int64_t fp_stride;
     int32_t predictor;
+    int32_t xfrom;      // finished rows a warm row needs behind it to be expanded (0: none is)
     int32_t persistent; // the persistent scheduler: iterates by per-front parity
     double2 *iter0, *iter1;
     const double *sheet; // rectangular fields' sheet records (Real::sheet_off)
     const FmmArgs *fmm;  // fast multipole star sums: one record per field (kernels built with them)
-    // Several rows per polish pass (persistent schedule, mixed form; null
-    // otherwise): per front the fewest further rows any block of the pass
-    // finished (reset to its field's Real::xrows by the front's finisher), the
-    // largest Real::xrows of the call, and the stride of the row-sum slots
-    // (the launch's block count).
-    int32_t *xrows;
-    int32_t xrow_max;
-    int32_t nvslots;
-    // and per front and further row: the row's updates and near-star terms
-    // (the front's finisher counts those of the rows it keeps)
-    unsigned long long *xcount;
+    // expand_rows: per block its next row and whether it is stuck there, the
+    // rows a block may be ahead of its front (row sums go to slot row mod
+    // ahead), and the stride of the row-sum slots (the launch's block count)
+    int32_t *next_row, *stuck;
+    int32_t ahead, nvslots;
 };
 
 // What one block knows about its front and star field.
@@ -863,16 +803,15 @@ template <class T> struct BlockCtx {
     int f, q, r, k0, k, lane, n_r, n_stars, row, stamp, dir, pred;
     int n_poly, n_extra;   // rectangular field: sheet terms and extra roots (else 0)
     const double *sheet;   // its record: d_2k, then d_2k / (2k + 1), then extra seeds
+    double sheet_c;        // |c|, the distance of its corners
     int vslot;   // this block's slot in the per-block row sums (front order)
     int hist, end_row;   // finished rows behind the current one (<= 3); the front's last row
     bool valid, boundary;
-    bool from_out;   // first pass of a row after a pass that ran several: the previous
-                     // row's roots come from the output, not the iterate buffer
     bool reseed, second;   // restart the row from its start values; from the second seeds
     bool fast;       // root-root terms in FP32 (fast_roots_pass)
-    bool chain;      // the pass takes the Aberth correction from the chain (chain_pass)
-    int32_t *count, *upd;   // the pass's totals: roots left open (or moving); updates made,
-                            // and those of them without a root-root sum
+    bool fresh;      // first pass over the row (roots flagged by then: expand_rows)
+    bool has_bnd;    // the front's end row is a duplicate boundary row
+    int32_t *count, *upd;   // the pass's totals: roots left open (or moving), updates made
     int64_t base_f, out_off, bnd_row_off;
     const T *stars;
     const double2 *zsrc;
@@ -888,15 +827,6 @@ template <class T> struct BlockCtx {
 __device__ __forceinline__ bool fast_roots_pass(const Front &fr, const Real &r)
 {
     return r.root32 && fr.dir != 0 && fr.mode == PH_F64;
-}
-
-// Whether this pass takes the Aberth correction from the chain: the first
-// pass of a row of a plain FP64 field whose front has three finished rows
-// behind it, two of them its own (the centre row's F' is not kept).
-template <class T>
-__device__ __forceinline__ bool chain_pass(const RoundArgs<T> &A, const Front &fr)
-{
-    return A.fprime && fr.fresh && fr.dir != 0 && fr.hist >= 3;
 }
 
 // Context of block q of front f, whose record is F (in LDS under the
@@ -917,17 +847,18 @@ __device__ __forceinline__ void enter_fq(const RoundArgs<T> &A, const Front *F, 
     B.reseed = F->reseed != 0;
     B.second = F->seedvar > 0;
     B.fast = fast_roots_pass(*F, *R);
-    B.chain = chain_pass(A, *F);
+    B.fresh = F->fresh != 0;
+    B.has_bnd = F->bnd_slot >= 0;
     B.count = count;
     B.upd = upd;
     B.hist = F->hist;
     B.end_row = F->end_row;
-    B.from_out = F->fresh == 2 && F->dir != 0;
     B.n_r = R->n_r;
     B.n_stars = R->n_stars;
     B.n_poly = R->n_poly;
     B.n_extra = R->n_extra;
     B.sheet = R->n_poly > 0 ? A.sheet + R->sheet_off : nullptr;
+    B.sheet_c = R->sheet_c;
     B.stars = A.stars + R->star_off;
     B.m0 = R->m0;
     B.gamma = R->gamma;
@@ -942,7 +873,7 @@ __device__ __forceinline__ void enter_fq(const RoundArgs<T> &A, const Front *F, 
         B.nxt = A.nxt;
     }
     B.out_off = R->out_off;
-    B.boundary = F->bnd_slot >= 0 && B.row == F->end_row;
+    B.boundary = B.has_bnd && B.row == F->end_row;
     B.bnd_row_off = R->bnd_off + (int64_t)max(F->bnd_slot, 0) * R->n_r;
     const double2 u = A.unit[B.row];
     B.e = make_double2(B.a * u.x, B.a * u.y);
@@ -959,7 +890,7 @@ __device__ __forceinline__ bool enter(const RoundArgs<T> &A, int phase, BlockCtx
     const int2 fq = A.bmap[blockIdx.x];
     const Front *F = A.fronts + fq.x;
     if (F->state != FRONT_ACTIVE || F->phase != phase) return false;
-    enter_fq(A, F, fq.x, fq.y, A.counts + fq.x, A.passupd + 2 * fq.x, B);
+    enter_fq(A, F, fq.x, fq.y, A.counts + fq.x, A.passupd + fq.x, B);
     return true;
 }
 
@@ -983,29 +914,6 @@ __device__ __forceinline__ void predict(const RoundArgs<T> &A, const BlockCtx<T>
     }
 }
 
-// The other roots' values a pass reads: the iterate buffer, or, on the first
-// pass after one that finished several rows, the previous row of the output.
-struct RootSrc {
-    const double2 *it;
-    const double *re, *im;
-    __device__ __forceinline__ double2 operator[](int64_t j) const
-    {
-        return re ? make_double2(re[j], im[j]) : it[j];
-    }
-    __device__ __forceinline__ RootSrc operator+(int64_t o) const
-    {
-        return RootSrc{it + o, re ? re + o : nullptr, re ? im + o : nullptr};
-    }
-};
-
-template <class T>
-__device__ __forceinline__ RootSrc root_src(const RoundArgs<T> &A, const BlockCtx<T> &B)
-{
-    if (!B.from_out) return RootSrc{B.zsrc, nullptr, nullptr};
-    const int64_t o = B.out_off + (int64_t)(B.row - B.dir) * B.n_r;
-    return RootSrc{B.zsrc, A.out_re + o, A.out_im + o};
-}
-
 // Write-back of a converged root: its row of the output (or the duplicate
 // boundary row of a subchain) and its caustic image.
 template <class T>
@@ -1023,6 +931,15 @@ __device__ __forceinline__ void put(const RoundArgs<T> &A, const BlockCtx<T> &B,
         A.caus_re[o] = u.wr;
         A.caus_im[o] = u.wi;
     }
+}
+
+// Root k of the current row where it is accepted already.
+template <class T>
+__device__ __forceinline__ double2 accepted_root(const RoundArgs<T> &A, const BlockCtx<T> &B, int k)
+{
+    if (B.boundary) return A.bnd[B.bnd_row_off + k];
+    const int64_t o = B.out_off + (int64_t)B.row * B.n_r + k;
+    return make_double2(A.out_re[o], A.out_im[o]);
 }
 
 // ---------------------------------------------------------------------------
@@ -1161,95 +1078,450 @@ __device__ __forceinline__ int wave_count(int v)
     return __builtin_amdgcn_readfirstlane(v);
 }
 
-// Adds a further row's work to its front's counts (see RoundArgs::xcount).
-template <class T>
-__device__ __forceinline__ void count_further(const RoundArgs<T> &A, int f, int x, int n_upd,
-                                              int n_near)
+// ---------------------------------------------------------------------------
+// Rows from expansions
+// ---------------------------------------------------------------------------
+
+// A row moves each root by about half a phase step (in units of its distance
+// to the nearest star), so the star field around a root is the same function
+// row after row, and its Taylor expansion about one point z0 of the chain
+// serves many rows:
+//   f(z) = sum m_i / (z - z_i) = sum_k s_{k+1} (z0 - z)^k,   s_k = sum m_i u_i^k,
+//   u_i = 1 / (z0 - z_i),
+// whose derivatives give the other sums (sum m u^2 = -f', sum m u^3 = f''/2,
+// sum m u^4 = -f'''/6).  Every star enters the moments s_k directly (with
+// multipole sums: the near stars, and the cell's series re-centred on z0), in
+// FP64.  With x = |z - z0| max|u_i|, the terms left out of sum m u^2 are at
+// most M x^(M-1) sum m |u|^4 / max|u|^2 / (1 - x)^2 for M moments; the
+// expansion is used where that is below EXP_TAIL, under the rounding of the
+// sum itself (~1e-16 sum m |u|^2).
+//
+// A direct star term costs ~80 instructions against ~19 (23 for unequal
+// masses) for the sums of one row, and a row from the expansion ~600
+// instructions a root, whatever N.  14 moments let x reach ~0.04 (each row
+// moves x by 1/2 to 3 phase steps): tens of rows at 10,000 phase steps, ~6 at
+// 1,000.  Measured with 10 / 12 / 14 / 16 / 20 moments, ms a call: N = 6,000
+// FP64 131 / 109 / 102 / 102 / 109; 40 fields mixed 152 / 75 / 65 / 61 / 59;
+// N = 10,000 mixed with multipole sums 71 / 66 / 67 / 72 / 79.
+#ifndef MLCC_MOMENTS
+#define MLCC_MOMENTS 14
+#endif
+constexpr int NMOM = MLCC_MOMENTS;
+constexpr double EXP_TAIL = 2e-17;
+// A root takes steps D with the correction G = -F''/(2 F') (what the Aberth
+// correction 2 S1 - R equals at a simple zero) while |G F/F'| < EXP_BASIN, deep
+// inside its zero's basin; farther out, the mixed form takes plain Newton
+// steps (its row identities tell when two columns end at one root) and FP64
+// leaves the root to Aberth steps.  It is accepted inside the basin, when it is
+// flagged and the step leaves less than EXP_ERR (of the order of |D|^3 |G|^2).
+// A root this does not settle in EXP_STEPS steps is left to the row's passes.
+constexpr double EXP_BASIN = 0.05;
+constexpr double EXP_ERR = 1e-16;
+constexpr int EXP_STEPS = 4;
+
+struct Moments {
+    double r[NMOM], i[NMOM];   // s_1 .. s_M
+    double q, u2;              // sum m |u|^4, max |u|^2
+};
+
+__device__ __forceinline__ void zero(Moments &S)
 {
-    unsigned long long *c = A.xcount + 2 * ((int64_t)f * (A.xrow_max + 1) + x);
-    if ((threadIdx.x & 63) == 0) {
-        atomicAdd(&c[0], (unsigned long long)n_upd);
-        if (n_near) atomicAdd(&c[1], (unsigned long long)n_near);
+#pragma unroll
+    for (int k = 0; k < NMOM; ++k) S.r[k] = S.i[k] = 0.0;
+    S.q = S.u2 = 0.0;
+}
+
+__device__ __forceinline__ void cfma(double &ar, double &ai, double br, double bi, double cr,
+                                     double ci)
+{
+    ar = fma(br, cr, fma(-bi, ci, ar));
+    ai = fma(br, ci, fma(bi, cr, ai));
+}
+
+// One star's term.  u .. u^4 are formed from |u|^2 as in add_star_inv; the
+// higher powers go in fours, m u^(4j) times u, u^2, u^3 being added straight
+// into the sums.
+template <bool EQUAL>
+__device__ __forceinline__ void add_moments(Moments &S, double dx, double dy, double inv, double m)
+{
+    const double ur = dx * inv, ui = -dy * inv;
+    const double b = ui * ui, t = ur * ui;
+    const double v2r = fma(-2.0, b, inv), v2i = t + t;
+    const double v3r = ur * fma(-2.0, b, v2r), v3i = ui * fma(2.0, v2r, inv);
+    const double inv2 = inv * inv;
+    const double v4r = fma(-2.0 * v2i, v2i, inv2), v4i = 2.0 * v2r * v2i;
+    S.u2 = fmax(S.u2, inv);
+    double pr, pi;   // m u^(4j)
+    if (EQUAL) {
+        S.r[0] += ur;  S.i[0] += ui;
+        S.r[1] += v2r; S.i[1] += v2i;
+        S.r[2] += v3r; S.i[2] += v3i;
+        S.q += inv2;
+        pr = v4r; pi = v4i;
+    } else {
+        S.r[0] = fma(m, ur, S.r[0]);  S.i[0] = fma(m, ui, S.i[0]);
+        S.r[1] = fma(m, v2r, S.r[1]); S.i[1] = fma(m, v2i, S.i[1]);
+        S.r[2] = fma(m, v3r, S.r[2]); S.i[2] = fma(m, v3i, S.i[2]);
+        S.q = fma(m, inv2, S.q);
+        pr = m * v4r; pi = m * v4i;
+    }
+#pragma unroll
+    for (int k = 3; k < NMOM; k += 4) {
+        S.r[k] += pr;
+        S.i[k] += pi;
+        if (k + 1 < NMOM) cfma(S.r[k + 1], S.i[k + 1], pr, pi, ur, ui);
+        if (k + 2 < NMOM) cfma(S.r[k + 2], S.i[k + 2], pr, pi, v2r, v2i);
+        if (k + 3 < NMOM) cfma(S.r[k + 3], S.i[k + 3], pr, pi, v3r, v3i);
+        if (k + 4 < NMOM) {
+            const double tr = fma(pr, v4r, -pi * v4i);
+            pi = fma(pr, v4i, pi * v4r);
+            pr = tr;
+        }
     }
 }
 
-// Rows of a plain FP64 field from their chains (see chain_correction): each
-// root of the block starts from the quadratic extrapolation of its last three
-// rows and takes steps whose correction comes from the chain, with no sum over
-// the other roots.  Roots accepted in the pass's row are stored; `open` tells
-// which the caller still has to step from (zr, zi).  Once every root of the
-// block is accepted the block goes on through the next rows of its front by
-// itself, as polish_pass does: nothing couples its roots to other blocks.
-// Direct star sums bound it: ~19 instructions a term against ~19 and twice 9
-// for a star and two root terms of the Aberth step, and one pass a row where
-// the stragglers of a row took a second one.  Whole calls before and after:
-// N = 6,000 FP64 1041 -> 547 ms, N = 1,000 44.3 -> 27.4, rectangular N = 437
-// 17.0 -> 10.5, N = 3,000 with multipole sums, whose rows keep no O(N) part,
-// 129.0 -> 28.4 ms.  Against 80-bit roots of 8 fields of 10 to 3,000 stars the
-// errors are those of the rows with the root-root sum (rms 2e-16 to 2.7e-15,
-// within 1% of each other).
+// Four consecutive star terms at most, sharing one refined reciprocal.
+template <bool EQUAL, int G, class T>
+__device__ __forceinline__ void add_moments_group(Moments &S, double zr, double zi, const T *r)
+{
+    if constexpr (G > 4) {
+        add_moments_group<EQUAL, G / 2>(S, zr, zi, r);
+        add_moments_group<EQUAL, G / 2>(S, zr, zi, r + G / 2);
+    } else {
+        double dx[G], dy[G], q[G], iq[G];
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            dx[j] = zr - r[j].x;
+            dy[j] = zi - r[j].y;
+            q[j] = fma(dx[j], dx[j], dy[j] * dy[j]);
+        }
+        rcp_group<G, RCP_STAR>(q, iq);
+#pragma unroll
+        for (int j = 0; j < G; ++j)
+            add_moments<EQUAL>(S, dx[j], dy[j], iq[j], StarRec<EQUAL>::mass(r[j]));
+    }
+}
+
+template <bool EQUAL, class T>
+__device__ __forceinline__ void add_moments_star(Moments &S, double zr, double zi, const T &s)
+{
+    const double dx = zr - s.x, dy = zi - s.y;
+    add_moments<EQUAL>(S, dx, dy, rcp_refined<RCP_STAR>(fma(dx, dx, dy * dy)),
+                       StarRec<EQUAL>::mass(s));
+}
+
+// The far stars of a point inside the grid, which set the moments: the cell's
+// series re-centred on the point (M Horner levels over one read of the row;
+// far stars are at least w away).
+__device__ __forceinline__ void set_moments_far(Moments &S, const FmmArgs &M, int cell, double tr,
+                                                double ti)
+{
+    const double2 *a = M.cf + (int64_t)cell * M.stride;
+    for (int c = M.stride - 8; c >= 0; c -= 8) {
+        const double4 *a4 = reinterpret_cast<const double4 *>(a + c);
+        double2 w[8];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const double4 v = a4[j];
+            w[2 * j] = make_double2(v.x, v.y);
+            w[2 * j + 1] = make_double2(v.z, v.w);
+        }
+#pragma unroll
+        for (int j = 7; j >= 0; --j) {
+#pragma unroll
+            for (int k = NMOM - 1; k >= 0; --k) {
+                const double xr = k ? S.r[k - 1] : w[j].x, xi = k ? S.i[k - 1] : w[j].y;
+                const double nr = fma(S.r[k], tr, fma(-S.i[k], ti, xr));
+                S.i[k] = fma(S.r[k], ti, fma(S.i[k], tr, xi));
+                S.r[k] = nr;
+            }
+        }
+    }
+    double sc = 1.0;   // (-1 / w)^k
+#pragma unroll
+    for (int k = 0; k < NMOM; ++k) {
+        S.r[k] *= sc;
+        S.i[k] *= sc;
+        sc *= -M.inv_w;
+    }
+    S.q = M.qfar[cell];
+    S.u2 = M.inv_w * M.inv_w;
+}
+
+// A rectangular field's sheet adds the polynomial p(z) = sum_k dmap_k
+// z^(2k+1) to f (its map term; the sheet's share of F is -P = -p', as the
+// stars' is sum m u^2 = -f').  Its Taylor terms about z0 by synthetic
+// division; a second division with |dmap| at max(|z0|, |c| / 2) bounds the
+// first one left out, and the ratio of those that follow is at most
+// t / (M |z0|).
+__device__ __forceinline__ void add_moments_sheet(Moments &S, const double *__restrict__ dmap,
+                                                  int n, double cabs, double zr, double zi)
+{
+    double br[NMOM], bi[NMOM], g[NMOM];
+#pragma unroll
+    for (int k = 0; k < NMOM; ++k) br[k] = bi[k] = g[k] = 0.0;
+    const double az = fmax(sqrt(fma(zr, zr, zi * zi)), 0.5 * cabs);
+    for (int d = 2 * n + 1; d >= 0; --d) {
+        const double cf = (d & 1) && d >= 3 ? dmap[(d - 3) >> 1] : 0.0;
+#pragma unroll
+        for (int k = NMOM - 1; k >= 0; --k) {
+            const double xr = k ? br[k - 1] : cf, xi = k ? bi[k - 1] : 0.0;
+            const double nr = fma(br[k], zr, fma(-bi[k], zi, xr));
+            bi[k] = fma(br[k], zi, fma(bi[k], zr, xi));
+            br[k] = nr;
+            g[k] = fma(g[k], az, k ? g[k - 1] : fabs(cf));
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < NMOM; ++k) {
+        S.r[k] += (k & 1) ? -br[k] : br[k];
+        S.i[k] += (k & 1) ? -bi[k] : bi[k];
+    }
+    const double u = fmax((2.0 * n + 2.0) / (NMOM * az), sqrt(S.u2));
+    double q = g[NMOM - 1];
+#pragma unroll
+    for (int k = 0; k < NMOM - 4; ++k) q /= u;
+    S.q += q;
+    S.u2 = u * u;
+}
+
+// Moments about (zr, zi) for the lanes of `mask`; the other lanes keep theirs
+// where the mask holds few lanes and no multipole sums are on, and receive
+// moments about their own (zr, zi) otherwise.  Direct sums: the whole wave one
+// root after another when the mask holds few, else the star tiles for every
+// lane.  Multipole sums: each lane its cell's series and near stars; a lane
+// outside the grid sums over all stars.
 template <bool EQUAL, bool FMM>
-__device__ __forceinline__ void chain_rows(const RoundArgs<typename StarRec<EQUAL>::T> &A,
-                                           const BlockCtx<typename StarRec<EQUAL>::T> &B,
-                                           double4 *tiles, double &zr, double &zi, bool &open)
+__device__ __forceinline__ void sum_moments(const RoundArgs<typename StarRec<EQUAL>::T> &A,
+                                            const BlockCtx<typename StarRec<EQUAL>::T> &B,
+                                            unsigned long long mask, double zr, double zi,
+                                            double4 *tiles, Moments &S, int &n_near)
 {
     using T = typename StarRec<EQUAL>::T;
+    auto masses = [&](Moments &C) {   // the common mass
+        if (!EQUAL) return;
+#pragma unroll
+        for (int j = 0; j < NMOM; ++j) {
+            C.r[j] *= B.m0;
+            C.i[j] *= B.m0;
+        }
+        C.q *= B.m0;
+    };
+    if (!FMM && __popcll(mask) > SPARSE_MAX) {
+        zero(S);
+        stream_tiles_grouped(B.stars, B.n_stars, reinterpret_cast<T *>(tiles),
+                             [&](auto g, const T *r) {
+                                 add_moments_group<EQUAL, decltype(g)::value>(S, zr, zi, r);
+                             });
+        masses(S);
+        return;
+    }
+    if constexpr (FMM) {
+        const FmmArgs &M = A.fmm[B.r];
+        const double fx = floor((zr - M.x0) / M.w), fy = floor((zi - M.y0) / M.w);
+        const bool in = fx >= 0.0 && fy >= 0.0 && fx < (double)M.G && fy < (double)M.G;
+        zero(S);
+        n_near = B.n_stars;
+        if (in) {
+            const int ix = (int)fx, iy = (int)fy, cell = iy * M.G + ix;
+            set_moments_far(S, M, cell, (zr - (M.x0 + (ix + 0.5) * M.w)) * M.inv_w,
+                            (zi - (M.y0 + (iy + 0.5) * M.w)) * M.inv_w);
+            n_near = fmm_near(M, cell, [&](const double4 &s4) {
+                if constexpr (EQUAL) add_moments_star<EQUAL>(S, zr, zi, make_double2(s4.x, s4.y));
+                else add_moments_star<EQUAL>(S, zr, zi, s4);
+            });
+            masses(S);
+        }
+        mask &= __ballot(!in);
+    }
+    while (mask) {
+        const int l = __ffsll((long long)mask) - 1;
+        mask &= mask - 1;
+        const double xk = __shfl(zr, l, 64), yk = __shfl(zi, l, 64);
+        Moments C;
+        zero(C);
+        for (int i = B.lane; i < B.n_stars; i += 64)
+            add_moments_star<EQUAL>(C, xk, yk, B.stars[i]);
+#pragma unroll
+        for (int k = 0; k < NMOM; ++k) {
+            wave_sum(C.r[k]);
+            wave_sum(C.i[k]);
+        }
+        wave_sum(C.q);
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) C.u2 = fmax(C.u2, __shfl_xor(C.u2, off, 64));
+        masses(C);
+        if (B.lane == l) S = C;
+    }
+}
+
+// Square of the distance from its centre to which an expansion serves.
+__device__ __forceinline__ double moments_reach2(const Moments &S)
+{
+    // M x^(M-1) q / u2 < EXP_TAIL, x = |z - z0| u, less a share for 1/(1 - x)^2
+    const float c = (float)(EXP_TAIL / NMOM * S.u2 / S.q);
+    const float x = 0.95f * exp2f(log2f(c) * (1.0f / (NMOM - 1)));
+    const float xm = fminf(x, 0.25f);
+    const double r2 = (double)(xm * xm) / S.u2;
+    return r2 > 0.0 ? r2 : 0.0;   // also an expansion that is not finite
+}
+
+// A block's share of a row's sums sum r and sum r^2 (row identities), and of
+// what bounds their error: the roots' own estimated errors, and sum |r|,
+// sum |r|^2 for the rounding of the sums.
+template <class T>
+__device__ __forceinline__ void put_row_sums(const RoundArgs<T> &A, const BlockCtx<T> &B, int row,
+                                             double zr, double zi, double er)
+{
+    const bool valid = B.valid;
+    double s1r = valid ? zr : 0.0, s1i = valid ? zi : 0.0;
+    double s2r = valid ? zr * zr - zi * zi : 0.0, s2i = valid ? 2.0 * zr * zi : 0.0;
+    const double ab2 = valid ? zr * zr + zi * zi : 0.0, ab = sqrt(ab2);
+    const double ev = valid ? er : 0.0;
+    double t_e = ev, t_e2 = ev * (2.0 * ab + ev), t_a = ab, t_a2 = ab2;
+    wave_sum(s1r); wave_sum(s1i); wave_sum(s2r); wave_sum(s2i);
+    wave_sum(t_e); wave_sum(t_e2); wave_sum(t_a); wave_sum(t_a2);
+    if (B.lane == 0) {
+        const int64_t sl = 2 * ((int64_t)(row % A.ahead) * A.nvslots + B.vslot);
+        A.vieta[sl] = make_double4(s1r, s1i, s2r, s2i);
+        A.vieta[sl + 1] = make_double4(t_e, t_e2, t_a, t_a2);
+    }
+}
+
+// Work of the expansion kernel, added to the striped tallies from FMM_T_EXP on:
+// near stars (multipole sums), steps on expansions, expansions formed, and
+// those weighted by their fields' star counts.
+enum { EXP_NEAR = 0, EXP_STEPS_DONE = 1, EXP_FORMED = 2, EXP_STARS = 3 };
+
+// Rows of a parked front by expansions, one block of 64 roots a work group:
+// each root starts a row from the extrapolation of its chain and steps on its
+// expansion, which is formed anew about that start once it lies too far from
+// the last centre.  Nothing couples the block's roots to other blocks, so it
+// goes on through its front's rows by itself, from where it stopped last; a
+// row counts when every root of the block is accepted in it.  The first row
+// that leaves a root open ends the block's run (it is stuck): the accepted
+// roots of that row are stored, and the row's passes step the others once
+// every other block has come to it (expand_control).
+//
+// A kernel of its own at two waves per SIMD, so that the moments stay in
+// registers.  Whole calls, with one sum over the stars per row and with this:
+// N = 6,000 FP64 547 -> 101 ms, N = 1,000 27.4 -> 12.9, N = 4,099 mixed 184 ->
+// 55, rectangular N = 437 10.5 -> 5.6, N = 3,000 FP64 with multipole sums 28.4 ->
+// 22.7, N = 10,000 mixed with them 150 -> 70, 40 fields mixed 130 -> 64 ms.
+// Errors against 80-bit roots of 8 fields of 10 to 3,000 stars: FP64 as before
+// (rms 2e-16 to 2.7e-15), mixed rms 2e-16 to 8e-15 against 2e-14 to
+// 2e-13.
+template <bool EQUAL, bool FMM>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MLCC_EXPAND_WAVES, 8)))
+expand_rows(RoundArgs<typename StarRec<EQUAL>::T> A)
+{
+    __shared__ typename StarRec<EQUAL>::T star_tiles[128];
+    double4 *tiles = reinterpret_cast<double4 *>(star_tiles);
+    const int2 fq = A.bmap[blockIdx.x];
+    const Front *F = A.fronts + fq.x;
+    if (F->state != FRONT_PARKED) return;
+    BlockCtx<typename StarRec<EQUAL>::T> B;
+    enter_fq(A, F, fq.x, fq.y, (int32_t *)nullptr, (int32_t *)nullptr, B);
+    const bool polish = F->phase == PH_POLISH;
+    const int front_row = F->row;
+    if (!F->redo) {   // on from where the block stopped, or past the row passes finished since
+        const int next = A.next_row[B.vslot];
+        if ((next - front_row) * B.dir > 0) B.row = next;
+    }
     const int k = B.k, n_r = B.n_r;
+    const int hist0 = B.hist - front_row * B.dir;   // finished rows behind row j: hist0 + j dir
     const int64_t base_f = B.base_f;
     const bool valid = B.valid;
-    double2 z1 = make_double2(0.0, 0.0), z2 = z1, z3 = z1, f1 = z1, f2 = z1;
-    auto fp = [&](int row) { return A.fprime + (row % FP_RING) * A.fp_stride + base_f; };
-    if (valid) {
-        const int64_t o1 = B.out_off + (int64_t)(B.row - B.dir) * n_r + k;
-        const int64_t o2 = o1 - (int64_t)B.dir * n_r, o3 = o2 - (int64_t)B.dir * n_r;
+    double2 z1 = make_double2(0.0, 0.0), z2 = z1, z3 = z1;
+    if (valid && (B.row - B.end_row) * B.dir <= 0) {
+        const int hist = hist0 + B.row * B.dir;
+        const int64_t d = (int64_t)B.dir * n_r, o1 = B.out_off + (int64_t)B.row * n_r + k - d;
         z1 = make_double2(A.out_re[o1], A.out_im[o1]);
-        z2 = make_double2(A.out_re[o2], A.out_im[o2]);
-        z3 = make_double2(A.out_re[o3], A.out_im[o3]);
-        f1 = fp(B.row - B.dir)[k];
-        f2 = fp(B.row - 2 * B.dir)[k];
+        if (hist >= 2) z2 = make_double2(A.out_re[o1 - d], A.out_im[o1 - d]);
+        if (hist >= 3) z3 = make_double2(A.out_re[o1 - 2 * d], A.out_im[o1 - 2 * d]);
     }
-    const int xmax = A.xrows ? A.reals[B.r].xrows : 0;
-    int done = 0;
-    for (int x = 0; x <= xmax; ++x) {
-        BlockCtx<T> C = B;
-        C.row = B.row + x * B.dir;
-        if (x > 0) {
-            // the front's last row is left to a pass of its own; rows another
-            // block already stopped short of will not be kept
-            if ((C.row - B.end_row) * B.dir >= 0 || load_relaxed(&A.xrows[B.f]) < x) break;
-            C.boundary = false;
-        }
-        const double2 un = A.unit[C.row];
+    Moments Mo;
+    zero(Mo);
+    double cr = 0.0, ci = 0.0, reach2 = -1.0;   // centre of the expansion, and its reach
+    unsigned long long t_steps = 0, t_exp = 0, t_near = 0;   // per lane
+    bool is_stuck = false;
+    for (; (B.row - B.end_row) * B.dir <= 0; B.row += B.dir) {
+        // row sums of the mixed form wait for the front's slowest block
+        if (polish && (B.row - front_row) * B.dir >= A.ahead) break;
+        B.boundary = B.has_bnd && B.row == B.end_row;
+        const double2 un = A.unit[B.row];
         const double2 e = make_double2(B.a * un.x, B.a * un.y);
-        const double pr = fma(3.0, z1.x - z2.x, z3.x), pi = fma(3.0, z1.y - z2.y, z3.y);
-        double xr = pr, xi = pi;
+        const int pred = min(A.predictor, min(hist0 + B.row * B.dir, 3) - 1);
+        double pr = z1.x, pi = z1.y;
+        if (pred == 1) {
+            pr = 2.0 * z1.x - z2.x;
+            pi = 2.0 * z1.y - z2.y;
+        } else if (pred == 2) {
+            pr = fma(3.0, z1.x - z2.x, z3.x);
+            pi = fma(3.0, z1.y - z2.y, z3.y);
+        }
         bool going = valid, left = valid;   // left: not accepted in this row
+        double xr = pr, xi = pi, err = 0.0;
         Update u{};
-        int n_steps = 0, n_near = 0;
-        for (int it = 0; it < CHAIN_STEPS; ++it) {
-            const unsigned long long mask = __ballot(going);
-            if (!mask) break;
-            PSums P;
-            int near;
-            newton_sums<EQUAL, FMM>(A, B, mask, xr, xi, tiles, P, near);
+        for (int it = 0; it < EXP_STEPS; ++it) {
+            if (!__ballot(going)) break;
+            const double ox = xr - cr, oy = xi - ci;
+            bool fresh = going && !(ox * ox + oy * oy <= reach2);
+            const unsigned long long mask = __ballot(fresh);
+            if (mask) {
+                if (FMM || __popcll(mask) > SPARSE_MAX) fresh = valid;
+                int near = 0;
+                sum_moments<EQUAL, FMM>(A, B, __ballot(fresh), xr, xi, tiles, Mo, near);
+                if (fresh) {
+                    if (B.n_poly > 0)
+                        add_moments_sheet(Mo, B.sheet + B.n_poly, B.n_poly, B.sheet_c, xr, xi);
+                    cr = xr;
+                    ci = xi;
+                    reach2 = moments_reach2(Mo);
+                    t_exp += 1;
+                    t_near += near;
+                }
+            }
+            // f, f', f''/2 and f'''/6 in h = z0 - z by Horner's rule
+            const double hr = cr - xr, hi = ci - xi;
+            double g0r = 0, g0i = 0, g1r = 0, g1i = 0, g2r = 0, g2i = 0, g3r = 0, g3i = 0;
+#pragma unroll
+            for (int j = NMOM - 1; j >= 0; --j) {
+                double nr, ni;
+                nr = fma(g3r, hr, fma(-g3i, hi, g2r)); ni = fma(g3r, hi, fma(g3i, hr, g2i));
+                g3r = nr; g3i = ni;
+                nr = fma(g2r, hr, fma(-g2i, hi, g1r)); ni = fma(g2r, hi, fma(g2i, hr, g1i));
+                g2r = nr; g2i = ni;
+                nr = fma(g1r, hr, fma(-g1i, hi, g0r)); ni = fma(g1r, hi, fma(g1i, hr, g0i));
+                g1r = nr; g1i = ni;
+                nr = fma(g0r, hr, fma(-g0i, hi, Mo.r[j])); ni = fma(g0r, hi, fma(g0i, hr, Mo.i[j]));
+                g0r = nr; g0i = ni;
+            }
             Sums S;
             zero(S);
-            S.s0r = P.s0r; S.s0i = P.s0i;
-            S.s1r = P.s0r; S.s1i = P.s0i;   // what s0 is formed from when the masses are equal
-            S.s2r = P.s2r; S.s2i = P.s2i; S.s3r = P.s3r; S.s3i = P.s3i;
-            const FieldAt Q = field_at<EQUAL>(S, xr, xi, B.m0, e, B.gamma, B.sheet, B.n_poly);
-            double last2;
-            const double2 G = chain_correction(make_double2(xr, xi), make_double2(Q.Fpr, Q.Fpi), z1,
-                                               f1, z2, f2, last2);
-            const Update v = take_step(S, Q, G.x, G.y, xr, xi, B.gamma, B.a, B.a1, A.tol_step2,
-                                       A.tol_mu, k, B.sheet, B.n_poly);
+            S.s0r = g0r; S.s0i = g0i; S.s2r = g1r; S.s2i = g1i; S.s3r = g2r; S.s3i = g2i;
+            FieldAt Q;
+            Q.Fr = B.gamma + g1r - e.x;
+            Q.Fi = g1i - e.y;
+            Q.Fpr = -2.0 * g2r;
+            Q.Fpi = -2.0 * g2i;
+            // G = -F''/(2 F') with F'' = 6 sum m u^4
+            const double2 G = cdiv(make_double2(1.5 * g3r, 1.5 * g3i), make_double2(g2r, g2i));
+            // far from its zero a root of the mixed form takes Newton's step, as
+            // the polish would
+            const double2 n = cdiv(make_double2(Q.Fr, Q.Fi), make_double2(Q.Fpr, Q.Fpi));
+            const double g2 = G.x * G.x + G.y * G.y;
+            const bool basin = (n.x * n.x + n.y * n.y) * g2 < EXP_BASIN * EXP_BASIN;
+            const bool corr = basin || !polish;
+            const Update v = take_step(S, Q, corr ? G.x : 0.0, corr ? G.y : 0.0, xr, xi, B.gamma, B.a,
+                                       B.a1, A.tol_step2, A.tol_mu, k, nullptr, 0);
             const double sr = xr - v.zr, si = xi - v.zi, d2 = sr * sr + si * si;
             if (going) {
-                n_steps += 1;
-                n_near += near;
-                going = d2 * (G.x * G.x + G.y * G.y) < CHAIN_BASIN * CHAIN_BASIN;
-                if (going && v.flag && d2 * d2 * last2 < CHAIN_ERR * CHAIN_ERR) {
+                t_steps += 1;
+                going = basin || polish;
+                if (basin && v.flag && (d2 * g2) * (d2 * g2) * d2 < EXP_ERR * EXP_ERR) {
                     u = v;
+                    err = sqrt(g2) * d2;
                     left = false;
                     going = false;
                 }
@@ -1257,49 +1529,38 @@ __device__ __forceinline__ void chain_rows(const RoundArgs<typename StarRec<EQUA
                 xi = v.zi;
             }
         }
-        const bool all = !__ballot(left);
-        if (x == 0) {
-            zr = pr;
-            zi = pi;
-            open = left;
-            if (valid && !left) {
-                B.nxt[base_f + k] = make_double2(u.zr, u.zi);
-                A.flagrow[base_f + k] = B.stamp;
+        is_stuck = __ballot(left) != 0;
+        if (valid && !left) put(A, B, k, u);
+        if (is_stuck) {
+            if (valid) {
+                const int64_t i = base_f + k;
+                A.flagrow[i] = left ? -1 : 4 * B.row;
+                if (polish) A.errbuf[i] = err;
             }
-        }
-        if (x == 0 || all) {
-            if (valid && !left) {
-                fp(C.row)[k] = make_double2(u.dr, u.di);
-                put(A, C, k, u);
-            }
-            const int n_upd = wave_count(n_steps), n_nr = FMM ? wave_count(n_near) : 0;
-            if (x > 0) {
-                count_further(A, B.f, x, n_upd, n_nr);
-                done = x;
-            } else {
-                if (B.lane == 0) {
-                    atomicAdd(&B.upd[0], n_upd);
-                    atomicAdd(&B.upd[1], n_upd);
-                }
-                if constexpr (FMM) {
-                    FmmTally tl;
-                    tl.near = (unsigned long long)n_nr;
-                    tl.far = (unsigned long long)n_upd;
-                    tl.far_n = (unsigned long long)n_upd * (unsigned long long)B.n_stars;
-                    fmm_flush(A.fmm_tally, FMM_T_F64, tl);
-                }
-            }
-        }
-        if (!all) {
-            // tell the other blocks now
-            if (xmax > 0 && B.lane == 0) atomicMin(&A.xrows[B.f], done);
             break;
         }
-        z3 = z2; z2 = z1; f2 = f1;
+        if (polish) put_row_sums(A, B, B.row, u.zr, u.zi, err);
+        z3 = z2;
+        z2 = z1;
         z1 = make_double2(u.zr, u.zi);
-        f1 = make_double2(u.dr, u.di);
     }
-    if (xmax > 0 && B.lane == 0) atomicMin(&A.xrows[B.f], done);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        t_steps += __shfl_xor(t_steps, off, 64);
+        t_exp += __shfl_xor(t_exp, off, 64);
+        t_near += __shfl_xor(t_near, off, 64);
+    }
+    if (B.lane == 0) {
+        A.next_row[B.vslot] = B.row;
+        A.stuck[B.vslot] = is_stuck;
+        unsigned long long *s = A.fmm_tally + (blockIdx.x % FMM_STRIPES) * FMM_STRIPE_U64 + FMM_T_EXP;
+        if (t_steps) atomicAdd(&s[EXP_STEPS_DONE], t_steps);
+        if (t_exp) {
+            atomicAdd(&s[EXP_FORMED], t_exp);
+            atomicAdd(&s[EXP_STARS], t_exp * (unsigned long long)B.n_stars);
+        }
+        if (t_near) atomicAdd(&s[EXP_NEAR], t_near);
+    }
 }
 
 // One FP64 Aberth pass of a block (the block context is set by enter()).
@@ -1343,7 +1604,7 @@ __device__ __forceinline__ void sweep_f64_pass(const RoundArgs<typename StarRec<
     const int lane = B.lane, k0 = B.k0, k = B.k, n_r = B.n_r, n_stars = B.n_stars;
     const bool valid = B.valid;
     const int64_t base_f = B.base_f;
-    const RootSrc zsrc = root_src(A, B);
+    const double2 *__restrict__ zsrc = B.zsrc;
     const T *__restrict__ stars = B.stars;
     double2 *__restrict__ nxt = B.nxt;
     int32_t *__restrict__ flagrow = A.flagrow;
@@ -1351,14 +1612,18 @@ __device__ __forceinline__ void sweep_f64_pass(const RoundArgs<typename StarRec<
     const double tol_step2 = A.tol_step2, tol_mu = A.tol_mu;
     double zr = 0.0, zi = 0.0;
     bool act = false;
-    if (B.chain) {
-        chain_rows<EQUAL, FMM>(A, B, tiles, zr, zi, act);
-    } else if (valid) {
+    if (valid) {
         const double2 z = zsrc[k];
         zr = z.x;
         zi = z.y;
         act = flagrow[base_f + k] != B.stamp;
-        if (B.pred) predict(A, B, k, zr, zi);
+        if (!act && B.fresh) {   // accepted by the expansions
+            const double2 w = accepted_root(A, B, k);
+            zr = w.x;
+            zi = w.y;
+        } else if (B.pred) {
+            predict(A, B, k, zr, zi);
+        }
         if (!act) nxt[base_f + k] = make_double2(zr, zi);   // carried forward
     }
     const unsigned long long amask = __ballot(act);
@@ -1366,12 +1631,10 @@ __device__ __forceinline__ void sweep_f64_pass(const RoundArgs<typename StarRec<
     if (n_act == 0) return;
 
     const double2 e = B.e;
-    double2 *fp = A.fprime ? A.fprime + (B.row % FP_RING) * A.fp_stride : nullptr;
     auto store = [&](int kk, const Update &u) {
         nxt[base_f + kk] = make_double2(u.zr, u.zi);
         if (!u.flag) return;
         flagrow[base_f + kk] = B.stamp;
-        if (fp) fp[base_f + kk] = make_double2(u.dr, u.di);
         put(A, B, kk, u);
     };
 
@@ -1693,21 +1956,11 @@ __device__ __forceinline__ Update polish_finish(PSums S, double zr, double zi, d
 // A Newton step needs only its own root's sums, so a root the acceptance test
 // turns down takes its next step in the same pass (up to POLISH_STEPS),
 // instead of waiting for the whole front's next pass.
-//
-// Several rows per pass: once every root of the block is accepted in this
-// row, the block goes on through the next rows of its front by itself, each
-// root from the chain prediction of its own earlier rows, as the front's
-// first pass of that row would (a Newton step couples no roots).  A row
-// counts only when every root of the block is accepted in it: then its roots
-// and caustics are written and its row sums kept in slot x; the first row
-// that leaves a root open ends the pass, and nothing of it is kept.  The
-// front's last row is left to a pass of its own.
 template <bool EQUAL, bool FMM>
 __device__ __forceinline__ void polish_pass(const RoundArgs<typename StarRec<EQUAL>::T> &A,
                                             const BlockCtx<typename StarRec<EQUAL>::T> &B,
                                             double4 *tiles)
 {
-    using T = typename StarRec<EQUAL>::T;
     const int lane = B.lane, k = B.k;
     const bool valid = B.valid;
     const int64_t base_f = B.base_f;
@@ -1715,101 +1968,65 @@ __device__ __forceinline__ void polish_pass(const RoundArgs<typename StarRec<EQU
     bool act = false;
     double er = 0.0;   // estimated error of that value
     if (valid) {
-        const double2 z = root_src(A, B)[k];
+        const double2 z = B.zsrc[k];
         zr = z.x;
         zi = z.y;
         act = A.flagrow[base_f + k] != B.stamp;
-        if (B.pred) predict(A, B, k, zr, zi);
-        if (!act) er = A.errbuf[base_f + k];   // accepted in an earlier pass of this row
+        if (!act && B.fresh) {   // accepted by the expansions
+            const double2 w = accepted_root(A, B, k);
+            zr = w.x;
+            zi = w.y;
+        } else if (B.pred) {
+            predict(A, B, k, zr, zi);
+        }
+        if (!act) er = A.errbuf[base_f + k];   // accepted earlier in this row
     }
-    const int xmax = A.xrows ? A.reals[B.r].xrows : 0;
-    const int xtop = (B.dir != 0 && A.predictor > 0) ? xmax : 0;
-    int done = 0;
-    for (int x = 0; x <= xtop; ++x) {
-        BlockCtx<T> C = B;
-        if (x > 0) {
-            C.row = B.row + x * B.dir;
-            // rows another block already stopped short of will not be kept
-            if ((C.row - B.end_row) * B.dir >= 0 || load_relaxed(&A.xrows[B.f]) < x) break;
-            C.boundary = false;
-            C.pred = min(A.predictor, min(B.hist + x, 3) - 1);
-            const double2 un = A.unit[C.row];
-            C.e = make_double2(B.a * un.x, B.a * un.y);
-            if (valid && C.pred) predict(A, C, k, zr, zi);
-            act = valid;
+    bool open = act;
+    Update u{};
+    int n_steps = 0, n_near = 0;
+    double xr = zr, xi = zi;
+    for (int it = 0; it < POLISH_STEPS; ++it) {
+        const unsigned long long mask = __ballot(open);
+        if (!mask) break;
+        PSums S;
+        int near;
+        newton_sums<EQUAL, FMM>(A, B, mask, xr, xi, tiles, S, near);
+        const Update v = polish_finish<EQUAL>(S, xr, xi, B.m0, B.e, B.gamma, B.a, B.a1, A.tol_step2,
+                                              A.tol_mu, k);
+        if (open) {
+            u = v;
+            n_steps += 1;
+            n_near += near;
+            open = !v.flag;
+            xr = v.zr;
+            xi = v.zi;
         }
-        bool open = act;
-        Update u{};
-        int n_steps = 0, n_near = 0;
-        double xr = zr, xi = zi;
-        for (int it = 0; it < POLISH_STEPS; ++it) {
-            const unsigned long long mask = __ballot(open);
-            if (!mask) break;
-            PSums S;
-            int near;
-            newton_sums<EQUAL, FMM>(A, B, mask, xr, xi, tiles, S, near);
-            const Update v = polish_finish<EQUAL>(S, xr, xi, B.m0, C.e, B.gamma, B.a, B.a1,
-                                                  A.tol_step2, A.tol_mu, k);
-            if (open) {
-                u = v;
-                n_steps += 1;
-                n_near += near;
-                open = !v.flag;
-                xr = v.zr;
-                xi = v.zi;
-            }
-        }
-        const int n_open = __popcll(__ballot(open));
-        const int n_upd = wave_count(n_steps), n_nr = FMM ? wave_count(n_near) : 0;
-        if (x > 0 && n_open) break;
-        if (act) {
-            zr = u.zr;
-            zi = u.zi;
-            if (u.flag) {
-                er = u.err;
-                put(A, C, k, u);
-            }
-        }
-        if (x == 0) {
-            if (valid) B.nxt[base_f + k] = make_double2(zr, zi);
-            if (act && u.flag) {
-                A.errbuf[base_f + k] = u.err;
-                A.flagrow[base_f + k] = B.stamp;
-            }
-            if (lane == 0) {
-                if (n_open) atomicAdd(B.count, n_open);
-                if (n_upd) atomicAdd(B.upd, n_upd);
-            }
-            if constexpr (FMM) {
-                FmmTally tl;
-                tl.near = (unsigned long long)n_nr;
-                tl.far = (unsigned long long)n_upd;
-                tl.far_n = (unsigned long long)n_upd * (unsigned long long)B.n_stars;
-                fmm_flush(A.fmm_tally, FMM_T_POLISH, tl);
-            }
-        } else {
-            count_further(A, B.f, x, n_upd, n_nr);
-            done = x;
-        }
-        // this block's share of the row sums sum r and sum r^2 (row identities),
-        // and of what bounds their error: the roots' own estimated errors, and
-        // sum |r|, sum |r|^2 for the rounding of the sums
-        double s1r = valid ? zr : 0.0, s1i = valid ? zi : 0.0;
-        double s2r = valid ? zr * zr - zi * zi : 0.0, s2i = valid ? 2.0 * zr * zi : 0.0;
-        const double ab2 = valid ? zr * zr + zi * zi : 0.0, ab = sqrt(ab2);
-        const double ev = valid ? er : 0.0;
-        double t_e = ev, t_e2 = ev * (2.0 * ab + ev), t_a = ab, t_a2 = ab2;
-        wave_sum(s1r); wave_sum(s1i); wave_sum(s2r); wave_sum(s2i);
-        wave_sum(t_e); wave_sum(t_e2); wave_sum(t_a); wave_sum(t_a2);
-        if (lane == 0) {
-            const int64_t sl = 2 * ((int64_t)x * A.nvslots + B.vslot);
-            A.vieta[sl] = make_double4(s1r, s1i, s2r, s2i);
-            A.vieta[sl + 1] = make_double4(t_e, t_e2, t_a, t_a2);
-        }
-        if (n_open) break;
     }
-    // rows beyond `done` are not kept: tells the other blocks, and the finisher
-    if (xmax > 0 && lane == 0) atomicMin(&A.xrows[B.f], done);
+    const int n_open = __popcll(__ballot(open));
+    const int n_upd = wave_count(n_steps);
+    if (act) {
+        zr = u.zr;
+        zi = u.zi;
+        if (u.flag) {
+            er = u.err;
+            A.errbuf[base_f + k] = u.err;
+            A.flagrow[base_f + k] = B.stamp;
+            put(A, B, k, u);
+        }
+    }
+    if (valid) B.nxt[base_f + k] = make_double2(zr, zi);
+    if (lane == 0) {
+        if (n_open) atomicAdd(B.count, n_open);
+        if (n_upd) atomicAdd(B.upd, n_upd);
+    }
+    if constexpr (FMM) {
+        FmmTally tl;
+        tl.near = (unsigned long long)wave_count(n_near);
+        tl.far = (unsigned long long)n_upd;
+        tl.far_n = (unsigned long long)n_upd * (unsigned long long)B.n_stars;
+        fmm_flush(A.fmm_tally, FMM_T_POLISH, tl);
+    }
+    put_row_sums(A, B, B.row, zr, zi, er);
 }
 
 template <bool EQUAL, bool FMM>
@@ -1854,12 +2071,14 @@ __global__ void seed_centres(const T *__restrict__ stars, const Real *__restrict
 // a butterfly), so the control kernel reads eight numbers per front.
 __global__ void __launch_bounds__(64)
 row_sums(const Front *__restrict__ fronts, const Real *__restrict__ reals,
-         const double4 *__restrict__ vieta, double4 *__restrict__ vsum)
+         const double4 *__restrict__ vieta, double4 *__restrict__ vsum,
+         int32_t ahead, int32_t nvslots)
 {
     const int f = blockIdx.x;
     const Front *F = fronts + f;
     if (F->state != FRONT_ACTIVE || F->phase != PH_POLISH) return;
     const int bpf = (reals[F->real].n_r + 63) / 64;
+    vieta += 2 * (int64_t)(F->row % ahead) * nvslots;
     double v0 = 0, v1 = 0, v2 = 0, v3 = 0, v4 = 0, v5 = 0, v6 = 0, v7 = 0;
     for (int b = threadIdx.x; b < bpf; b += 64) {
         const double4 t = vieta[2 * (F->blk0 + b)], q = vieta[2 * (F->blk0 + b) + 1];
@@ -1875,6 +2094,21 @@ row_sums(const Front *__restrict__ fronts, const Real *__restrict__ reals,
 }
 
 constexpr int CONTROL_THREADS = 256;
+
+// Adds a pass's updates to the call's totals, plain and weighted by the
+// field's star count.
+__device__ __forceinline__ void tally_updates(unsigned long long *upd, unsigned long long *star,
+                                              int ph, bool fast, unsigned long long u,
+                                              unsigned long long ns)
+{
+    upd[ph] += u;
+    star[ph] += u * ns;
+    if (ph == PH_F64 && fast) {
+        upd[TALLY_FAST] += u;
+        star[TALLY_FAST] += u * ns;
+    }
+}
+
 constexpr int MAX_FRONTS = 1 << 16;
 // Polish passes a row may take before it is retried another way: a root with
 // direct sums is given POLISH_STEPS Newton steps in all, one with multipole
@@ -1886,7 +2120,7 @@ constexpr int F32_STALL = 4;
 // Puts a front at the start of its (new) row.  Mixed mode: a row with a
 // chain prediction goes straight to the FP64 polish; one without (the two
 // rows next to a subchain centre, or predictor 0) starts with an FP32 sweep.
-__device__ __forceinline__ void start_row(Front &fr, int predictor)
+__device__ __forceinline__ void start_row(Front &fr, int predictor, int xfrom)
 {
     fr.sweeps = 0;
     fr.passes = 0;
@@ -1902,9 +2136,12 @@ __device__ __forceinline__ void start_row(Front &fr, int predictor)
         fr.phase = PH_F64;
     else
         fr.phase = (predictor > 0 && fr.hist >= 2) ? PH_POLISH : PH_F32;
+    // rows with enough rows behind them wait for the expansion kernel
+    if (xfrom > 0 && fr.dir != 0 && fr.hist >= xfrom && fr.phase != PH_F32)
+        fr.state = FRONT_PARKED;
 }
 
-__device__ __forceinline__ void row_done(Front &fr, int32_t *st, int f, int predictor)
+__device__ __forceinline__ void row_done(Front &fr, int32_t *st, int f, int predictor, int xfrom)
 {
     if (fr.row == fr.end_row) {
         fr.state = FRONT_DONE;
@@ -1912,7 +2149,8 @@ __device__ __forceinline__ void row_done(Front &fr, int32_t *st, int f, int pred
     } else {
         fr.row += fr.dir;
         fr.hist = min(fr.hist + 1, 3);
-        start_row(fr, predictor);
+        start_row(fr, predictor, xfrom);
+        if (st) st[f] = fr.state;
     }
 }
 
@@ -1920,7 +2158,7 @@ __device__ __forceinline__ void row_done(Front &fr, int32_t *st, int f, int pred
 // half of its subchain to its partner front and turns downward itself; a
 // warm row moves one row on or finishes at its end row.
 __device__ __forceinline__ int row_converged(Front &fr, int f, Front *fronts, int32_t *st,
-                                             int f0, int predictor)
+                                             int f0, int predictor, int xfrom)
 {
     if (fr.dir == 0) {
         fr.cold = fr.passes_row;
@@ -1932,17 +2170,18 @@ __device__ __forceinline__ int row_converged(Front &fr, int f, Front *fronts, in
         pr.dir = 1;
         pr.src = f;    // first pass reads the converged centre row
         pr.hist = 1;   // the centre row
-        start_row(pr, predictor);
+        start_row(pr, predictor, xfrom);
         fronts[p] = pr;
-        if (st) st[p - f0] = FRONT_ACTIVE;
+        if (st) st[p - f0] = pr.state;
         fr.dir = -1;
         fr.row = centre - 1;
         fr.hist = 1;
-        start_row(fr, predictor);
+        start_row(fr, predictor, xfrom);
+        if (st) st[f - f0] = fr.state;
         return p;
     }
     fr.max_warm = max(fr.max_warm, fr.passes_row);
-    row_done(fr, st, f - f0, predictor);
+    row_done(fr, st, f - f0, predictor, xfrom);
     return -1;
 }
 
@@ -1967,14 +2206,36 @@ __device__ __forceinline__ bool row_identities_hold(const Real &R, double2 u, co
     return sqrt(e1r * e1r + e1i * e1i) <= tol1 && sqrt(e2r * e2r + e2i * e2i) <= tol2;
 }
 
+// A row the polish did not settle: once an FP32 sweep of the whole row, then
+// FP64 sweeps.  What blocks ahead of the row found is done anew.
+__device__ __forceinline__ void retry_row(Front &fr, Control *ctl, bool count)
+{
+    fr.tried |= TRIED_POLISH;
+    fr.redo = 1;
+    if (!(fr.tried & TRIED_F32)) {
+        fr.phase = PH_F32;
+    } else {
+        // plain FP64 Aberth sweeps over every root from the row's
+        // start values: Newton steps may have sent two columns to
+        // one root, which Aberth steps from there would not undo
+        fr.stamp += 1;
+        fr.reseed = 1;
+        fr.phase = PH_F64;
+        fr.sweeps = 0;
+        if (count) atomicAdd((unsigned long long *)&ctl->rows_fallback, 1ull);
+    }
+}
+
 // One front after its pass (c = its roots still unconverged, or, after an
 // FP32 sweep, still moving; rs = its row sums when the pass was a polish).
 // Returns the partner front a finished cold start activated, else -1.
 // `st` (the control kernel's LDS copy of the states) may be null.
-__device__ __attribute__((noinline)) int advance_front(Front &fr, int f, int32_t c, const double4 *rs, Front *fronts,
+// (Inlined, so that the record stays in registers: through a call it would be
+// reached by flat accesses, in LDS or scratch memory.)
+__device__ __forceinline__ int advance_front(Front &fr, int f, int32_t c, const double4 *rs, Front *fronts,
                              int32_t *st, int f0, Control *ctl, const Real *reals,
                              const double2 *unit, int max_cold, int max_warm, int predictor,
-                             int max_polish)
+                             int max_polish, int xfrom)
 {
     int partner = -1;
     fr.npass += 1;
@@ -2004,30 +2265,17 @@ __device__ __attribute__((noinline)) int advance_front(Front &fr, int f, int32_t
         bool retry = false;
         if (c == 0) {
             if (row_identities_hold(reals[fr.real], unit[fr.row], rs))
-                partner = row_converged(fr, f, fronts, st, f0, predictor);
+                partner = row_converged(fr, f, fronts, st, f0, predictor, xfrom);
             else
                 retry = true;
         } else if (++fr.passes >= max_polish) {
             retry = true;
         }
-        if (retry) {
-            if (!(fr.tried & TRIED_F32)) {
-                fr.phase = PH_F32;
-            } else {
-                // plain FP64 Aberth sweeps over every root from the row's
-                // start values: Newton steps may have sent two columns to
-                // one root, which Aberth steps from there would not undo
-                fr.stamp += 1;
-                fr.reseed = 1;
-                fr.phase = PH_F64;
-                fr.sweeps = 0;
-                atomicAdd((unsigned long long *)&ctl->rows_fallback, 1ull);
-            }
-        }
+        if (retry) retry_row(fr, ctl, true);
     } else if (fr.reseed) {
         fr.reseed = 0;   // the restart pass only reloaded the start values
     } else if (c == 0) {
-        partner = row_converged(fr, f, fronts, st, f0, predictor);
+        partner = row_converged(fr, f, fronts, st, f0, predictor, xfrom);
     } else {
         fr.sweeps += 1;
         if (fr.dir == 0 && fr.phase == PH_F64 && fr.seedvar == 0 &&
@@ -2087,12 +2335,11 @@ aberth_control(Front *__restrict__ fronts, int32_t *__restrict__ counts, int32_t
                int32_t *__restrict__ workflag, const double4 *__restrict__ vsum,
                const Real *__restrict__ reals, const double2 *__restrict__ unit,
                int32_t fronts_per_group, int32_t predictor, int32_t *__restrict__ passupd,
-               int32_t max_polish)
+               int32_t max_polish, int32_t xfrom)
 {
     __shared__ int32_t st[4096];
     __shared__ int32_t s_active, s_live;
-    // by phase; [3]: fast-root FP64 passes; [4]: FP64 updates without a root-root sum
-    __shared__ unsigned long long s_upd[5], s_star[5];
+    __shared__ unsigned long long s_upd[TALLIES], s_star[TALLIES];
     const int tid = threadIdx.x;
     const int f0 = blockIdx.x * fronts_per_group;
     const int f1 = min(n_fronts, f0 + fronts_per_group);
@@ -2100,63 +2347,36 @@ aberth_control(Front *__restrict__ fronts, int32_t *__restrict__ counts, int32_t
         s_active = 0;
         s_live = 0;
     }
-    if (tid < 5) s_upd[tid] = s_star[tid] = 0ull;
-    unsigned long long my_upd[5] = {}, my_star[5] = {};
+    if (tid < TALLIES) s_upd[tid] = s_star[tid] = 0ull;
+    unsigned long long my_upd[TALLIES] = {}, my_star[TALLIES] = {};
     for (int f = f0 + tid; f < f1; f += CONTROL_THREADS) st[f - f0] = fronts[f].state;
     __syncthreads();
     for (int f = f0 + tid; f < f1; f += CONTROL_THREADS) {
         if (st[f - f0] != FRONT_ACTIVE) continue;
         Front fr = fronts[f];
         atomicOr(&s_live, 1 << fr.phase);
-        {   // this round's updates of the front, by pass kind (FLOP counts weigh them by N)
-            const unsigned long long u = (unsigned)passupd[2 * f];
-            const unsigned long long up = (unsigned)passupd[2 * f + 1];
-            passupd[2 * f] = 0;
-            passupd[2 * f + 1] = 0;
-            const unsigned long long ns = (unsigned)reals[fr.real].n_stars;
-            my_upd[fr.phase] += u;
-            my_star[fr.phase] += u * ns;
-            my_upd[4] += up;
-            my_star[4] += up * ns;
-            if (fr.phase == PH_F64 && fast_roots_pass(fr, reals[fr.real])) {
-                my_upd[3] += u - up;
-                my_star[3] += (u - up) * ns;
-            }
-        }
+        const Real &R = reals[fr.real];
+        const int ph = fr.phase;
+        const bool fast = fast_roots_pass(fr, R);
+        const unsigned long long u = (unsigned)passupd[f];   // this round's updates of the front
+        passupd[f] = 0;
         const int32_t c = counts[f];
         counts[f] = 0;
         advance_front(fr, f, c, vsum + 2 * f, fronts, st, f0, ctl, reals, unit, max_cold,
-                      max_warm, predictor, max_polish);
+                      max_warm, predictor, max_polish, xfrom);
+        tally_updates(my_upd, my_star, ph, fast, u, (unsigned)R.n_stars);
         fronts[f] = fr;
     }
-    for (int q = 0; q < 5; ++q) {
+    for (int q = 0; q < TALLIES; ++q) {
         if (my_upd[q]) {
             atomicAdd(&s_upd[q], my_upd[q]);
             atomicAdd(&s_star[q], my_star[q]);
         }
     }
     __syncthreads();
-    if (tid == 0) {
-        if (s_upd[PH_F64]) {
-            atomicAdd(&ctl->updates, s_upd[PH_F64]);
-            atomicAdd(&ctl->star_updates, s_star[PH_F64]);
-        }
-        if (s_upd[PH_F32]) {
-            atomicAdd(&ctl->updates_f32, s_upd[PH_F32]);
-            atomicAdd(&ctl->star_updates_f32, s_star[PH_F32]);
-        }
-        if (s_upd[PH_POLISH]) {
-            atomicAdd(&ctl->polish_updates, s_upd[PH_POLISH]);
-            atomicAdd(&ctl->star_updates_polish, s_star[PH_POLISH]);
-        }
-        if (s_upd[3]) {
-            atomicAdd(&ctl->updates_fast, s_upd[3]);
-            atomicAdd(&ctl->star_updates_fast, s_star[3]);
-        }
-        if (s_upd[4]) {
-            atomicAdd(&ctl->updates_plain, s_upd[4]);
-            atomicAdd(&ctl->star_updates_plain, s_star[4]);
-        }
+    if (tid < TALLIES && s_upd[tid]) {
+        atomicAdd(&ctl->upd[tid], s_upd[tid]);
+        atomicAdd(&ctl->star[tid], s_star[tid]);
     }
     int mine = 0;
     for (int f = f0 + tid; f < f1; f += CONTROL_THREADS)
@@ -2213,15 +2433,16 @@ struct PQueue {
     unsigned long long pad1[31];
     unsigned long long progress;  // passes completed
     unsigned long long pad2[31];
-    int32_t done;                 // fronts finished (DONE or FAILED)
+    int32_t done;                 // fronts finished (DONE, FAILED or PARKED)
     int32_t pad3[63];
     int32_t abort;                // a worker saw no progress for too long
-    int32_t pad4[63];
+    int32_t target;               // fronts the launch has to finish
+    int32_t pad4[62];
 };
 // Slot sequence numbers are spread one per 64-byte line.
 constexpr int SEQ_STRIDE = 8;
 // Most waves of a work group of the persistent launch.
-constexpr int MAX_WORK_WAVES = 16;
+constexpr int MAX_WORK_WAVES = 8;
 
 // Tasks of a pass over a front of field r.
 __device__ __forceinline__ int task_count(const Real &r)
@@ -2265,20 +2486,156 @@ __device__ __forceinline__ void sum_row(const double4 *__restrict__ v, int bpf, 
     rs[1] = make_double4(v4, v5, v6, v7);
 }
 
+// ---------------------------------------------------------------------------
+// Fronts between the expansions and the passes
+// ---------------------------------------------------------------------------
+
+// Before the expansions: no front counted, and an empty queue, whose slots go
+// on being numbered (workers of the last launch claimed beyond its tail).
+__global__ void expand_begin(Control *__restrict__ ctl, PQueue *q)
+{
+    ctl->active_fronts = 0;
+    ctl->parked_fronts = 0;
+    if (q) {
+        q->head = q->tail;
+        q->done = 0;
+        q->target = 0;
+    }
+}
+
+// After the expansions, one work group per parked front: the front moves past the
+// rows all its blocks have settled (in the mixed form while their row
+// identities hold).  If a block is stuck at the row it comes to, the front is
+// active again: the row's first pass steps the roots left open, from their
+// extrapolation, the others entering at the previous row's roots.  If a row's
+// identities fail it goes the way of a polish that does, and what blocks ahead
+// of it found is done anew.  Otherwise the front stays parked, or is done.
+// (Each wave checks the identities of one row at a time: the sums of a row are
+// a few dependent loads, and one wave for all rows took 3.4 us a row.)
+constexpr int CHECK_WAVES = 16;
+
+__global__ void __launch_bounds__(64 * CHECK_WAVES)
+expand_control(Front *__restrict__ fronts, const Real *__restrict__ reals,
+               const double2 *__restrict__ unit, const double4 *__restrict__ vieta,
+               const int32_t *__restrict__ next_row, const int32_t *__restrict__ stuck,
+               int32_t ahead, int32_t nvslots, int32_t predictor, int32_t xfrom,
+               Control *__restrict__ ctl, PQueue *q, int2 *tasks, unsigned long long *seq,
+               unsigned long long mask)
+{
+    __shared__ int row_ok[CHECK_WAVES];
+    const int f = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    Front fr = fronts[f];   // every thread advances a copy of its own
+    if (fr.state != FRONT_PARKED) return;
+    const Real &R = reals[fr.real];
+    const int bpf = (R.n_r + 63) >> 6;
+    const bool polish = fr.phase == PH_POLISH;
+    int h = 0x7fffffff;   // rows settled by every block
+    for (int b = lane; b < bpf; b += 64) h = min(h, (next_row[fr.blk0 + b] - fr.row) * fr.dir);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) h = min(h, __shfl_xor(h, off, 64));
+    const int row0 = fr.row, dir = fr.dir;
+    fr.redo = 0;
+    fr.npass += 1;
+    bool failed = false;
+    int moved = 0;
+    for (; moved < h; ++moved) {
+        if (polish) {
+            const int c = moved % CHECK_WAVES;
+            if (c == 0) {   // the next rows, one a wave
+                const int row = fr.row + wave * dir;
+                __syncthreads();
+                if (moved + wave < h) {
+                    double4 rs[2];
+                    sum_row(vieta + 2 * ((int64_t)(row % ahead) * nvslots + fr.blk0), bpf, rs);
+                    if (lane == 0) row_ok[wave] = row_identities_hold(R, unit[row], rs);
+                }
+                __syncthreads();
+            }
+            failed = !row_ok[c];
+            if (failed) break;
+        }
+        fr.max_warm = max(fr.max_warm, 1);
+        row_done(fr, nullptr, f, predictor, xfrom);
+    }
+    bool any = false;
+    if (fr.state == FRONT_PARKED && !failed)
+        for (int b = lane; b < bpf; b += 64)
+            any |= stuck[fr.blk0 + b] && next_row[fr.blk0 + b] == row0 + moved * dir;
+    const bool held = __ballot(any) != 0;
+    if (fr.state == FRONT_PARKED && (failed || held)) {
+        fr.state = FRONT_ACTIVE;
+        fr.src = f;
+        fr.passes_row = 1;
+        if (failed) {
+            fr.fresh = 0;
+            retry_row(fr, ctl, threadIdx.x == 0);
+        }
+    }
+    __syncthreads();   // the record is read by every wave before it is written
+    if (threadIdx.x == 0) {
+        fronts[f] = fr;
+        const unsigned long long up = (unsigned long long)moved * (unsigned)R.n_r;
+        if (up) atomicAdd(&ctl->upd[polish ? TALLY_ROOTS + 1 : TALLY_ROOTS], up);
+        if (fr.state == FRONT_ACTIVE) atomicAdd(&ctl->active_fronts, 1);
+        if (fr.state == FRONT_PARKED) atomicAdd(&ctl->parked_fronts, 1);
+    }
+    if (q && wave == 0 && fr.state == FRONT_ACTIVE) {   // persistent schedule: the next launch's work
+        push_front(q, tasks, seq, mask, f, task_count(R));
+        if (lane == 0) atomicAdd(&q->target, 1);
+    }
+}
+
+// Iterates of the fronts expand_control made active: the previous row's roots
+// for a row's first pass, the row's own for one that is retried; roots of
+// blocks that had settled the row are flagged (the stuck ones' flags are in
+// place).  Counts the accepted roots.
+__global__ void __launch_bounds__(64)
+expand_gather(const Front *__restrict__ fronts, const Real *__restrict__ reals,
+              const int2 *__restrict__ bmap, const int32_t *__restrict__ next_row,
+              const double *__restrict__ out_re, const double *__restrict__ out_im,
+              const double2 *__restrict__ bnd, double2 *__restrict__ iter0,
+              double2 *__restrict__ iter1, int32_t *__restrict__ flagrow,
+              double *__restrict__ errbuf, Control *__restrict__ ctl)
+{
+    const int2 fq = bmap[blockIdx.x];
+    const Front *F = fronts + fq.x;
+    if (F->state != FRONT_ACTIVE) return;
+    const Real *R = reals + F->real;
+    const int k = fq.y * 64 + threadIdx.x;
+    const bool valid = k < R->n_r;
+    const int64_t i = F->it_off + k;
+    bool flagged = false;
+    if (valid) {
+        const int row = F->fresh ? F->row - F->dir : F->row;
+        const int64_t o = R->out_off + (int64_t)row * R->n_r + k;
+        const bool b = F->bnd_slot >= 0 && row == F->end_row;
+        (F->par ? iter1 : iter0)[i] =
+            b ? bnd[R->bnd_off + (int64_t)F->bnd_slot * R->n_r + k] : make_double2(out_re[o], out_im[o]);
+        if (next_row[F->blk0 + fq.y] != F->row) {
+            flagrow[i] = F->stamp;
+            if (errbuf) errbuf[i] = 0.0;
+            flagged = true;
+        } else {
+            flagged = flagrow[i] == F->stamp;
+        }
+    }
+    const unsigned long long n = __popcll(__ballot(flagged));
+    if (threadIdx.x == 0 && n && !(F->tried & TRIED_POLISH))
+        atomicAdd(&ctl->upd[F->phase == PH_F64 ? TALLY_ROOTS : TALLY_ROOTS + 1], n);
+}
+
 // What the waves of a work group share: the front it works on, the pass's
 // block cursor and totals, and what its first wave decided after the pass.
 struct WorkShare {
     Front fr;
     int32_t task_f, task_c;   // claimed task (task_f < 0: leave)
     int32_t begin, end;       // blocks of the task
-    int32_t count, upd[2];    // the pass's totals over this task (BlockCtx)
+    int32_t count, upd;       // the pass's totals over this task
     int32_t go;               // the work group owns the front and runs its next pass
     int32_t partner;          // front whose cold start just ended here (else -1)
     int64_t src_off, dst_off;
     int32_t src_par, dst_par;
-    // updates, and updates x N: per phase, [3] fast-root FP64 passes, [4] FP64
-    // updates without a root-root sum
-    unsigned long long upd_tot[5], star_tot[5];
+    unsigned long long upd_tot[TALLIES], star_tot[TALLIES];   // the work group's (tally_work)
 };
 
 // What bounds short passes is not their sums but what surrounds them: a
@@ -2297,8 +2654,8 @@ __attribute__((amdgpu_waves_per_eu(FMM ? MLCC_FMM_WAVES : MLCC_SWEEP_WAVES, 8)))
 aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ fronts_w,
                   PQueue *__restrict__ q, int2 *__restrict__ tasks,
                   unsigned long long *__restrict__ seq, unsigned long long mask,
-                  int32_t *__restrict__ fdone, int32_t n_fronts, int32_t max_cold,
-                  int32_t max_warm, unsigned long long stall_ticks)
+                  int32_t *__restrict__ fdone, int32_t max_cold, int32_t max_warm,
+                  unsigned long long stall_ticks)
 {
     using T = typename StarRec<EQUAL>::T;
     extern __shared__ double4 tiles_all[];   // two tiles of 64 records per wave
@@ -2306,7 +2663,7 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
     double4 *tiles = reinterpret_cast<double4 *>(reinterpret_cast<T *>(tiles_all) + wave * 128);
-    if (threadIdx.x < 5) W.upd_tot[threadIdx.x] = W.star_tot[threadIdx.x] = 0ull;
+    if (threadIdx.x < TALLIES) W.upd_tot[threadIdx.x] = W.star_tot[threadIdx.x] = 0ull;
     for (;;) {
         if (threadIdx.x == 0) {
             int tf = -1, tq = 0;
@@ -2324,7 +2681,7 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
                 }
                 if ((it & 31) == 0) {   // the shared counters, now and then
                     if (load_relaxed(&q->abort)) break;
-                    if (load_relaxed(&q->done) >= n_fronts) break;
+                    if (load_relaxed(&q->done) >= load_relaxed(&q->target)) break;
                     const unsigned long long pnow = load_relaxed(&q->progress);
                     const unsigned long long now = wall_clock64();
                     if (pnow != seen) {
@@ -2358,7 +2715,7 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
                     W.begin = tc * c;
                     W.end = min((tc + 1) * c, bpf);
                     W.count = 0;
-                    W.upd[0] = W.upd[1] = 0;
+                    W.upd = 0;
                 }
             }
             __syncthreads();
@@ -2366,7 +2723,7 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
             const int ph = __builtin_amdgcn_readfirstlane(W.fr.phase);
             for (int blk = __builtin_amdgcn_readfirstlane(W.begin) + wave; blk < end; blk += waves) {
                 BlockCtx<T> B;
-                enter_fq(A, &W.fr, tf, blk, &W.count, W.upd, B);
+                enter_fq(A, &W.fr, tf, blk, &W.count, &W.upd, B);
                 if (ph == PH_F64)
                     sweep_f64_pass<EQUAL, FMM>(A, B, tiles);
                 else if (ph == PH_F32)
@@ -2379,7 +2736,7 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
             wait_stores();
             __syncthreads();
             if (wave == 0) {
-                Front &fr = W.fr;
+                Front fr = W.fr;   // lane 0's copy is the one that is advanced
                 const Real *R = A.reals + fr.real;
                 const int bpf = (R->n_r + 63) >> 6;
                 const int nt = task_count(*R);
@@ -2389,8 +2746,7 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
                     // every task publishes its writes before counting itself
                     if (lane == 0) {
                         if (W.count) atomicAdd(&A.counts[tf], W.count);
-                        if (W.upd[0]) atomicAdd(&A.passupd[2 * tf], W.upd[0]);
-                        if (W.upd[1]) atomicAdd(&A.passupd[2 * tf + 1], W.upd[1]);
+                        if (W.upd) atomicAdd(&A.passupd[tf], W.upd);
                     }
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
                     if (lane == 0) last = atomicAdd(&fdone[tf], 1) + 1 == nt;
@@ -2400,102 +2756,38 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
                         if (lane == 0) {
                             fdone[tf] = 0;
                             W.count = load_relaxed(&A.counts[tf]);
-                            W.upd[0] = load_relaxed(&A.passupd[2 * tf]);
-                            W.upd[1] = load_relaxed(&A.passupd[2 * tf + 1]);
                             A.counts[tf] = 0;
-                            A.passupd[2 * tf] = 0;
-                            A.passupd[2 * tf + 1] = 0;
+                            W.upd = load_relaxed(&A.passupd[tf]);
+                            A.passupd[tf] = 0;
                         }
                     }
                 }
                 int go = 0, partner = -1;
                 if (last) {
                     double4 rs[2] = {make_double4(0, 0, 0, 0), make_double4(0, 0, 0, 0)};
-                    if (ph == PH_POLISH) sum_row(A.vieta + 2 * (int64_t)fr.blk0, bpf, rs);
-                    int finished = 0, xr = 0, dir0 = 0;
+                    if (ph == PH_POLISH)
+                        sum_row(A.vieta + 2 * ((int64_t)(fr.row % A.ahead) * A.nvslots + fr.blk0),
+                                bpf, rs);
+                    int finished = 0;
                     if (lane == 0) {
-                        const unsigned long long u = (unsigned)W.upd[0], up = (unsigned)W.upd[1];
-                        const unsigned long long ns = (unsigned)R->n_stars;
-                        W.upd_tot[ph] += u;
-                        W.star_tot[ph] += u * ns;
-                        W.upd_tot[4] += up;
-                        W.star_tot[4] += up * ns;
-                        if (ph == PH_F64 && fast_roots_pass(fr, *R)) {
-                            W.upd_tot[3] += u - up;
-                            W.star_tot[3] += (u - up) * ns;
-                        }
-                        dir0 = fr.dir;
-                        const int row0 = fr.row;
-                        const bool runs_on = ph == PH_POLISH || (ph == PH_F64 && chain_pass(A, fr));
+                        const int dir0 = fr.dir;
+                        tally_updates(W.upd_tot, W.star_tot, ph, fast_roots_pass(fr, *R),
+                                      (unsigned)W.upd, (unsigned)R->n_stars);
                         partner = advance_front(fr, tf, W.count, rs, fronts_w, nullptr, 0, A.ctl,
                                                 A.reals, A.unit, max_cold, max_warm, A.predictor,
-                                                max_polish_passes(FMM));
+                                                max_polish_passes(FMM), A.xfrom);
                         fr.par ^= 1;   // the pass wrote the other buffer
-                        if (A.xrows && runs_on) {
-                            // further rows the pass finished in every block (see polish_pass)
-                            xr = load_relaxed(&A.xrows[tf]);
-                            __hip_atomic_store(&A.xrows[tf], R->xrows, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT);
-                            if (!(dir0 != 0 && fr.state == FRONT_ACTIVE && fr.phase == ph &&
-                                  fr.row == row0 + dir0))
-                                xr = 0;
-                        }
-                    }
-                    // the further rows, in order, while their row identities hold
-                    xr = __shfl(xr, 0, 64);
-                    int moved = 0;
-                    for (int x = 1; x <= xr; ++x) {
-                        double4 rx[2];
-                        if (ph == PH_POLISH)
-                            sum_row(A.vieta + 2 * ((int64_t)x * A.nvslots + fr.blk0), bpf, rx);
-                        int ok = 0;
-                        if (lane == 0 &&
-                            (ph != PH_POLISH || row_identities_hold(*R, A.unit[fr.row], rx))) {
-                            row_converged(fr, tf, fronts_w, nullptr, 0, A.predictor);
-                            ok = 1;
-                        }
-                        ok = __shfl(ok, 0, 64);
-                        if (!ok) break;
-                        moved = x;
-                    }
-                    if (lane == 0) {
-                        if (A.xrows) {
-                            // what the further rows took: counted for those the front
-                            // keeps, cleared for its next pass
-                            unsigned long long *c =
-                                A.xcount + 2 * (int64_t)tf * (A.xrow_max + 1);
-                            unsigned long long nu = 0, nn = 0;
-                            for (int x = 1; x <= A.xrow_max; ++x) {
-                                if (x <= moved) {
-                                    nu += load_relaxed(&c[2 * x]);
-                                    nn += load_relaxed(&c[2 * x + 1]);
-                                }
-                                for (int v = 0; v < 2; ++v)
-                                    __hip_atomic_store(&c[2 * x + v], 0ull, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT);
-                            }
-                            const unsigned long long ns = (unsigned)R->n_stars;
-                            W.upd_tot[ph] += nu;
-                            W.star_tot[ph] += nu * ns;
-                            if (ph == PH_F64) {
-                                W.upd_tot[4] += nu;
-                                W.star_tot[4] += nu * ns;
-                            }
-                            if constexpr (FMM) {
-                                FmmTally tl;
-                                tl.near = nn;
-                                tl.far = nu;
-                                tl.far_n = nu * ns;
-                                fmm_flush(A.fmm_tally, ph == PH_F64 ? FMM_T_F64 : FMM_T_POLISH, tl);
-                            }
-                        }
-                        // its first pass takes the previous row from the output
-                        if (moved) fr.fresh = 2;
-                        const int state = fr.state;
+                        const int state = fr.state;   // finished: done, failed or parked
                         if (state != FRONT_ACTIVE)
                             finished = (state == FRONT_FAILED && dir0 == 0) ? 2 : 1;
                         else
                             go = task_count(*R) == 1 ? 1 : 2;
+                        // a partner that waits for the expansions from its first row on
+                        if (partner >= 0 && fronts_w[partner].state != FRONT_ACTIVE) {
+                            finished += 1;
+                            partner = -1;
+                        }
+                        W.fr = fr;
                         if (partner >= 0) {
                             W.src_par = fr.par;
                             W.src_off = fr.it_off;
@@ -2540,18 +2832,9 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
         __syncthreads();   // the claim below overwrites what the waves just read
     }
     // the work group's share of the totals
-    if (threadIdx.x == 0) {
-        unsigned long long *dst[5][2] = {{&A.ctl->updates, &A.ctl->star_updates},
-                                         {&A.ctl->updates_f32, &A.ctl->star_updates_f32},
-                                         {&A.ctl->polish_updates, &A.ctl->star_updates_polish},
-                                         {&A.ctl->updates_fast, &A.ctl->star_updates_fast},
-                                         {&A.ctl->updates_plain, &A.ctl->star_updates_plain}};
-#pragma unroll
-        for (int k = 0; k < 5; ++k) {
-            if (!W.upd_tot[k]) continue;
-            atomicAdd(dst[k][0], W.upd_tot[k]);
-            atomicAdd(dst[k][1], W.star_tot[k]);
-        }
+    if (threadIdx.x < TALLIES && W.upd_tot[threadIdx.x]) {
+        atomicAdd(&A.ctl->upd[threadIdx.x], W.upd_tot[threadIdx.x]);
+        atomicAdd(&A.ctl->star[threadIdx.x], W.star_tot[threadIdx.x]);
     }
 }
 
@@ -2862,6 +3145,11 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
     std::vector<int2> bmap;
     int64_t it_total = 0, bnd_total = 0, max_nr = 0;
     const int32_t warm_phase = mixed ? PH_F32 : PH_F64;
+    // finished rows a warm row needs behind it to be solved by expansions: in
+    // FP64 as many as the quadratic extrapolation takes (from a poorer start many
+    // roots are left to Aberth steps, which then start from a row part old, part
+    // new), in the mixed form the two after which rows start with a polish
+    const int32_t xfrom = p->predictor > 0 ? (mixed ? 2 : 3) : 0;
     for (int r = 0; r < n_real; ++r) {
         const RealHost &h = c->reals[r];
         const SheetPoly sp = sheet_poly(h);
@@ -2879,6 +3167,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         R.gamma = h.gamma - sp.d0;   // a rectangular sheet's constant term joins the shear
         R.n_poly = sp.n;
         R.n_extra = sp.n_extra;
+        R.sheet_c = sp.seed_r;
         R.sheet_off = (int64_t)sheet_host.size();
         if (sp.n > 0) {
             // d_2k, then the lens-map terms, then the extra roots' start values:
@@ -2906,15 +3195,6 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         R.tol2 = 16.0 * u_ro * h.sum_abs_z2;
         R.root32 = p->precision == MLCC_FP64_R32 ? 1 : 0;
         R.restart = p->cold_restart_sweeps > 0 ? p->cold_restart_sweeps : STALL_START;
-        // further rows per polish pass (persistent mixed form with the chain
-        // predictor): every field with multipole sums, small fields with direct
-        // ones
-        R.xrows = 0;
-        if (p->schedule == MLCC_SCHEDULE_PERSISTENT &&
-            (mixed ? p->predictor > 0 : p->predictor == 2)) {
-            if (p->star_sums == MLCC_STARS_FMM) R.xrows = FMM_XROWS;
-            else if (h.n <= XROWS_DIRECT_MAX_N) R.xrows = DIRECT_XROWS;
-        }
         const int bpf = (int)ceil_div(n_r, 64);
         for (int s = 0; s < S; ++s) {
             const int32_t lo = (int32_t)(s * L), hi = (int32_t)(lo + L), cen = (int32_t)(lo + L / 2);
@@ -2926,11 +3206,13 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
             d.phase = warm_phase; d.mode = warm_phase; d.stamp = 4 * cen;
             d.best = 0x7fffffff;
             d.real = r;
+            d.redo = 1;
             Front u{};
             u.row = cen + 1; u.dir = 1; u.end_row = hi; u.state = FRONT_IDLE;
             u.src = fd + 1; u.partner = -1; u.bnd_slot = -1; u.lo = lo; u.hi = hi;
             u.phase = warm_phase; u.mode = warm_phase; u.stamp = 4 * (cen + 1);
             u.real = r;
+            u.redo = 1;
             for (Front *x : {&d, &u}) {
                 x->it_off = it_total;
                 it_total += n_r;
@@ -2988,23 +3270,23 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
     MLCC_TRY(c->flagrow.reserve((size_t)it_total * sizeof(int32_t)));
     MLCC_TRY(c->fronts.reserve((size_t)(F + 1) * sizeof(Front)));
     MLCC_TRY(c->counts.reserve((size_t)F * sizeof(int32_t)));
-    MLCC_TRY(c->passupd.reserve((size_t)2 * F * sizeof(int32_t)));
+    MLCC_TRY(c->passupd.reserve((size_t)F * sizeof(int32_t)));
     MLCC_TRY(c->control.reserve(sizeof(Control)));
     MLCC_TRY(c->fmm_tally.reserve((size_t)FMM_STRIPES * FMM_STRIPE_U64 * sizeof(uint64_t)));
     MLCC_TRY(c->etab.reserve((size_t)(m + 1) * sizeof(double2)));
     MLCC_TRY(c->bnd.reserve((size_t)std::max<int64_t>(bnd_total, 1) * sizeof(double2)));
-    // several rows per polish pass: row sums for the most further rows any
-    // field takes
-    int xrow_max = 0;
-    for (const Real &R : rd) xrow_max = std::max(xrow_max, (int)R.xrows);
-    const bool xrows_on = xrow_max > 0;
-    MLCC_TRY(c->vieta.reserve((size_t)2 * (xrow_max + 1) * nblocks * sizeof(double4)));
+    // row sums of the rows a block may be ahead of its front (mixed form; fewer
+    // rows where those would pass 512 MiB)
+    const int ahead = mixed && xfrom > 0
+                          ? (int)std::max<int64_t>(1, std::min<int64_t>(AHEAD, ((int64_t)1 << 29) /
+                                                                                   (64 * nblocks)))
+                          : 1;
+    MLCC_TRY(c->next_row.reserve((size_t)2 * nblocks * sizeof(int32_t)));
+    if (mixed) {
+        MLCC_TRY(c->vieta.reserve((size_t)2 * ahead * nblocks * sizeof(double4)));
+        MLCC_TRY(c->errbuf.reserve((size_t)it_total * sizeof(double)));
+    }
     MLCC_TRY(c->vsum.reserve((size_t)2 * F * sizeof(double4)));
-    if (mixed) MLCC_TRY(c->errbuf.reserve((size_t)it_total * sizeof(double)));
-    // FP64 sweeps with the quadratic predictor: F' of the last rows
-    const bool chain_corr = !mixed && p->predictor == 2;
-    if (chain_corr)
-        MLCC_TRY(c->fprime.reserve((size_t)FP_RING * it_total * sizeof(double2)));
     MLCC_TRY(c->reals_d.reserve((size_t)n_real * sizeof(Real)));
     MLCC_TRY(c->sheet.reserve(std::max<size_t>(1, sheet_host.size()) * sizeof(double)));
     // With multipole sums the kernels take each field's stars in cell order,
@@ -3049,7 +3331,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
     MLCC_HIP(hipMemsetAsync(c->counts.p, 0, F * sizeof(int32_t), c->stream));
     MLCC_HIP(hipMemsetAsync(c->fmm_tally.p, 0,
                             (size_t)FMM_STRIPES * FMM_STRIPE_U64 * sizeof(uint64_t), c->stream));
-    MLCC_HIP(hipMemsetAsync(c->passupd.p, 0, 2 * F * sizeof(int32_t), c->stream));
+    MLCC_HIP(hipMemsetAsync(c->passupd.p, 0, F * sizeof(int32_t), c->stream));
     if (equal)
         hipLaunchKernelGGL(seed_centres<double2>, dim3((unsigned)ngrid), dim3(64), 0, c->stream,
                            stars2, c->reals_d.as<Real>(), c->fronts.as<Front>(),
@@ -3096,8 +3378,14 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         A.vieta = c->vieta.as<double4>();
         A.predictor = p->predictor;
         A.errbuf = mixed ? c->errbuf.as<double>() : nullptr;
-        A.fprime = chain_corr ? c->fprime.as<double2>() : nullptr;
-        A.fp_stride = it_total;
+        A.xfrom = xfrom;
+        A.next_row = c->next_row.as<int32_t>();
+        A.stuck = c->next_row.as<int32_t>() + nblocks;
+        A.ahead = ahead;
+        A.nvslots = (int32_t)nblocks;
+        A.persistent = p->schedule == MLCC_SCHEDULE_PERSISTENT;
+        A.iter0 = c->iter[0].as<double2>();
+        A.iter1 = c->iter[1].as<double2>();
         A.sheet = c->sheet.as<double>();
         A.fmm = fmm_dev;
     };
@@ -3171,6 +3459,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
     const int64_t launch_cap =
         (int64_t)max_cold + (L / 2 + 2) * (int64_t)(max_warm + MAX_POLISH + 2) + 4 * MAX_BATCH;
     int64_t launched = 0;
+    int rounds_runs = 0;   // the first run of rounds (the cold starts) is replayed from graphs
     // One round: every pass kind once over every block (blocks whose front is
     // in another phase return at once), then the control kernel.
     auto enqueue_rounds = [&](int slot, int g, bool timed) -> mlcc_status {
@@ -3184,7 +3473,8 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
                 if (kind == 2)
                     hipLaunchKernelGGL(row_sums, dim3((unsigned)F), dim3(64), 0, rs,
                                        c->fronts.as<Front>(), c->reals_d.as<Real>(),
-                                       c->vieta.as<double4>(), c->vsum.as<double4>());
+                                       c->vieta.as<double4>(), c->vsum.as<double4>(), ahead,
+                                       (int32_t)nblocks);
             }
             int32_t *wf = c->workflags.as<int32_t>() + slot * MAX_BATCH + i;
             hipLaunchKernelGGL(control_begin, dim3(1), dim3(64), 0, rs, dctl, wf);
@@ -3192,7 +3482,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
                                rs, c->fronts.as<Front>(), c->counts.as<int32_t>(), F, dctl,
                                max_cold, max_warm, wf, c->vsum.as<double4>(),
                                c->reals_d.as<Real>(), c->etab.as<double2>(), fronts_per_group,
-                               p->predictor, c->passupd.as<int32_t>(), max_polish_passes(fmm_on));
+                               p->predictor, c->passupd.as<int32_t>(), max_polish_passes(fmm_on), xfrom);
             hipLaunchKernelGGL(control_end, dim3(1), dim3(64), 0, rs, dctl, wf);
             parity ^= 1;
         }
@@ -3204,7 +3494,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         return MLCC_OK;
     };
     auto enqueue_batch = [&](int slot, int g) -> mlcc_status {
-        if (gexec[slot]) {
+        if (gexec[slot] && rounds_runs == 0) {
             MLCC_HIP(hipGraphLaunch(gexec[slot], rs));
             g = graph_len;
         } else {
@@ -3257,8 +3547,13 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         }
     };
 
-    // The persistent scheduler: one launch, fronts advance independently.
-    auto run_persistent = [&]() -> mlcc_status {
+    // The persistent scheduler: one launch at a time, fronts advance independently.
+    PQueue *dq = nullptr;
+    int2 *dtasks = nullptr;
+    unsigned long long *dseq = nullptr;
+    unsigned long long qmask = 0;
+    hipGraphExec_t pgraph = nullptr;
+    auto setup_persistent = [&]() -> mlcc_status {
         int cus = 0, clock_khz = 0;
         MLCC_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
         MLCC_HIP(hipDeviceGetAttribute(&clock_khz, hipDeviceAttributeWallClockRate, c->device));
@@ -3273,18 +3568,14 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         const size_t o_tasks = (sizeof(PQueue) + 255) & ~(size_t)255;
         const size_t o_seq = o_tasks + (size_t)cap * sizeof(int2);
         const size_t o_fdone = o_seq + (size_t)cap * SEQ_STRIDE * sizeof(unsigned long long);
-        const size_t o_xcount = o_fdone + (((size_t)F * sizeof(int32_t) + 255) & ~(size_t)255);
-        const size_t o_xrows =
-            o_xcount + (xrows_on ? (size_t)F * (xrow_max + 1) * 2 * sizeof(unsigned long long) : 0);
-        MLCC_TRY(c->pq.reserve(o_xrows + (size_t)F * sizeof(int32_t)));
+        const size_t pq_bytes = o_fdone + (size_t)F * sizeof(int32_t);
+        MLCC_TRY(c->pq.reserve(pq_bytes));
         char *base = static_cast<char *>(c->pq.p);
-        PQueue *dq = reinterpret_cast<PQueue *>(base);
-        int2 *dtasks = reinterpret_cast<int2 *>(base + o_tasks);
-        unsigned long long *dseq = reinterpret_cast<unsigned long long *>(base + o_seq);
+        dq = reinterpret_cast<PQueue *>(base);
+        dtasks = reinterpret_cast<int2 *>(base + o_tasks);
+        dseq = reinterpret_cast<unsigned long long *>(base + o_seq);
+        qmask = (unsigned long long)(cap - 1);
         int32_t *dfdone = reinterpret_cast<int32_t *>(base + o_fdone);
-        int32_t *dxrows = reinterpret_cast<int32_t *>(base + o_xrows);
-        std::vector<int32_t> xr0((size_t)F, 0);
-        for (int f = 0; f < F; ++f) xr0[f] = rd[fr[f].real].xrows;
         std::vector<int2> t0;
         for (int f = 0; f < F; ++f) {
             if (fr[f].state != FRONT_ACTIVE) continue;
@@ -3296,21 +3587,13 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         for (size_t i = 0; i < t0.size(); ++i) s0[i * SEQ_STRIDE] = i + 1;
         PQueue hq{};
         hq.tail = (unsigned long long)t0.size();
-        MLCC_HIP(hipMemsetAsync(base, 0, o_xrows, rs));
+        hq.target = F;
+        MLCC_HIP(hipMemsetAsync(base, 0, pq_bytes, rs));
         MLCC_HIP(hipMemcpyAsync(dq, &hq, sizeof hq, hipMemcpyHostToDevice, rs));
         MLCC_HIP(hipMemcpyAsync(dtasks, t0.data(), t0.size() * sizeof(int2), hipMemcpyHostToDevice,
                                 rs));
         MLCC_HIP(hipMemcpyAsync(dseq, s0.data(), s0.size() * sizeof(unsigned long long),
                                 hipMemcpyHostToDevice, rs));
-        if (xrows_on)
-            MLCC_HIP(hipMemcpyAsync(dxrows, xr0.data(), xr0.size() * sizeof(int32_t),
-                                    hipMemcpyHostToDevice, rs));
-        auto set_xrows = [&](auto &A) {
-            A.xrows = xrows_on ? dxrows : nullptr;
-            A.xrow_max = xrow_max;
-            A.xcount = reinterpret_cast<unsigned long long *>(base + o_xcount);
-            A.nvslots = (int32_t)nblocks;
-        };
         const void *kfn =
             equal ? (fmm_on ? reinterpret_cast<const void *>(&aberth_persistent<true, true>)
                             : reinterpret_cast<const void *>(&aberth_persistent<true, false>))
@@ -3338,40 +3621,31 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         auto launch = [&]() {
             if (equal) {
                 fill(A2, stars2, cur0, c->iter[1].as<double2>());
-                set_xrows(A2);
-                A2.persistent = 1;
-                A2.iter0 = c->iter[0].as<double2>();
-                A2.iter1 = c->iter[1].as<double2>();
                 if (fmm_on)
                     hipLaunchKernelGGL((aberth_persistent<true, true>), dim3(workers), dim3(threads), lds,
                                        rs, A2, c->fronts.as<Front>(), dq, dtasks, dseq,
-                                       (unsigned long long)(cap - 1), dfdone, F, max_cold, max_warm,
+                                       (unsigned long long)(cap - 1), dfdone, max_cold, max_warm,
                                        stall);
                 else
                     hipLaunchKernelGGL((aberth_persistent<true, false>), dim3(workers), dim3(threads), lds,
                                        rs, A2, c->fronts.as<Front>(), dq, dtasks, dseq,
-                                       (unsigned long long)(cap - 1), dfdone, F, max_cold, max_warm,
+                                       (unsigned long long)(cap - 1), dfdone, max_cold, max_warm,
                                        stall);
             } else {
                 fill(A4, stars4, cur0, c->iter[1].as<double2>());
-                set_xrows(A4);
-                A4.persistent = 1;
-                A4.iter0 = c->iter[0].as<double2>();
-                A4.iter1 = c->iter[1].as<double2>();
                 if (fmm_on)
                     hipLaunchKernelGGL((aberth_persistent<false, true>), dim3(workers), dim3(threads), lds,
                                        rs, A4, c->fronts.as<Front>(), dq, dtasks, dseq,
-                                       (unsigned long long)(cap - 1), dfdone, F, max_cold, max_warm,
+                                       (unsigned long long)(cap - 1), dfdone, max_cold, max_warm,
                                        stall);
                 else
                     hipLaunchKernelGGL((aberth_persistent<false, false>), dim3(workers), dim3(threads), lds,
                                        rs, A4, c->fronts.as<Front>(), dq, dtasks, dseq,
-                                       (unsigned long long)(cap - 1), dfdone, F, max_cold, max_warm,
+                                       (unsigned long long)(cap - 1), dfdone, max_cold, max_warm,
                                        stall);
             }
         };
         hipGraph_t graph = nullptr;
-        hipGraphExec_t gx = nullptr;
         MLCC_HIP(hipStreamBeginCapture(rs, hipStreamCaptureModeThreadLocal));
         launch();
         const hipError_t le = hipGetLastError();
@@ -3381,80 +3655,140 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
             MLCC_HIP(le);
             MLCC_HIP(e);
         }
-        e = hipGraphInstantiate(&gx, graph, nullptr, nullptr, 0);
+        e = hipGraphInstantiate(&pgraph, graph, nullptr, nullptr, 0);
         (void)hipGraphDestroy(graph);
         MLCC_HIP(e);
-        hipEvent_t e0 = nullptr, e1 = nullptr;
-        if (p->timing) {
-            MLCC_HIP(hipEventCreate(&e0));
-            MLCC_HIP(hipEventCreate(&e1));
-            MLCC_HIP(hipEventRecord(e0, rs));
-        }
-        e = hipGraphLaunch(gx, rs);
-        if (e == hipSuccess && p->timing) e = hipEventRecord(e1, rs);
-        if (e == hipSuccess) e = hipStreamSynchronize(rs);
-        (void)hipGraphExecDestroy(gx);
-        MLCC_HIP(e);
-        if (p->timing) {
-            float ms = 0.f;
-            (void)hipEventElapsedTime(&ms, e0, e1);
-            (void)hipEventDestroy(e0);
-            (void)hipEventDestroy(e1);
-            persistent_ms = ms;
-        }
-        persistent_launches = 1;
-        MLCC_HIP(hipMemcpy(&hq, dq, sizeof hq, hipMemcpyDeviceToHost));
-        if (hq.abort)
+        // host vectors must outlive the copies above
+        MLCC_HIP(hipStreamSynchronize(rs));
+        return MLCC_OK;
+    };
+    auto run_persistent = [&]() -> mlcc_status {
+        MLCC_HIP(hipGraphLaunch(pgraph, rs));
+        PQueue *hq = static_cast<PQueue *>(c->pinned);
+        MLCC_HIP(hipMemcpyAsync(hq, dq, sizeof *hq, hipMemcpyDeviceToHost, rs));
+        MLCC_HIP(hipStreamSynchronize(rs));
+        if (hq->abort)
             return fail(MLCC_ERR_HIP, "persistent scheduler: no pass finished for %d ms "
                                       "(%d of %d fronts done)",
-                        p->watchdog_ms > 0 ? p->watchdog_ms : 5000, hq.done, F);
+                        p->watchdog_ms > 0 ? p->watchdog_ms : 5000, hq->done, hq->target);
         return MLCC_OK;
     };
 
-    mlcc_status st = MLCC_OK;
-    int slot = 0;
-    auto t_last = std::chrono::steady_clock::now();
-    if (persistent) st = run_persistent();
-    else st = enqueue_batch(slot, G);
-    while (!persistent && st == MLCC_OK) {
-        // keep one batch queued behind the one being polled
-        const int next = slot ^ 1;
-        if (use_graphs && !gexec[0] && polls == 1 && parity == 0) {
-            // G now holds the batch length that takes ~4 ms
-            st = build_graphs(std::min(G, 64));
+    // The expansions over every parked front, and what comes of them: fronts
+    // that passes take over, and fronts still parked.
+    auto run_expansions = [&](int &active, int &parked) -> mlcc_status {
+        hipLaunchKernelGGL(expand_begin, dim3(1), dim3(1), 0, rs, dctl, dq);
+        auto go = [&](auto &A, auto eq, auto fm) {
+            constexpr bool E = decltype(eq)::value, M = decltype(fm)::value;
+            hipLaunchKernelGGL((expand_rows<E, M>), grid, dim3(64), 0, rs, A);
+        };
+        using T_ = std::true_type;
+        using F_ = std::false_type;
+        if (equal) {
+            fill(A2, stars2, c->iter[0].as<double2>(), c->iter[1].as<double2>());
+            if (fmm_on) go(A2, T_{}, T_{}); else go(A2, T_{}, F_{});
+        } else {
+            fill(A4, stars4, c->iter[0].as<double2>(), c->iter[1].as<double2>());
+            if (fmm_on) go(A4, F_{}, T_{}); else go(A4, F_{}, F_{});
+        }
+        hipLaunchKernelGGL(expand_control, dim3((unsigned)F), dim3(64 * CHECK_WAVES), 0, rs,
+                           c->fronts.as<Front>(), c->reals_d.as<Real>(), c->etab.as<double2>(),
+                           c->vieta.as<double4>(), c->next_row.as<int32_t>(),
+                           c->next_row.as<int32_t>() + nblocks, ahead, (int32_t)nblocks,
+                           p->predictor, xfrom, dctl, dq, dtasks, dseq, qmask);
+        hipLaunchKernelGGL(expand_gather, grid, dim3(64), 0, rs, c->fronts.as<Front>(),
+                           c->reals_d.as<Real>(), c->bmap.as<int2>(), c->next_row.as<int32_t>(),
+                           roots_re, roots_im, c->bnd.as<double2>(), c->iter[0].as<double2>(),
+                           c->iter[1].as<double2>(), c->flagrow.as<int32_t>(),
+                           mixed ? c->errbuf.as<double>() : nullptr, dctl);
+        MLCC_HIP(hipGetLastError());
+        Control *h = static_cast<Control *>(c->pinned);
+        MLCC_HIP(hipMemcpyAsync(h, dctl, sizeof *h, hipMemcpyDeviceToHost, rs));
+        MLCC_HIP(hipStreamSynchronize(rs));
+        active = h->active_fronts;
+        parked = h->parked_fronts;
+        return MLCC_OK;
+    };
+
+    // The round schedule: rounds until no front is active.
+    auto run_rounds = [&]() -> mlcc_status {
+        mlcc_status st = MLCC_OK;
+        int slot = 0;
+        launched = 0;
+        G = 4;
+        auto t_last = std::chrono::steady_clock::now();
+        st = enqueue_batch(slot, G);
+        while (st == MLCC_OK) {
+            // keep one batch queued behind the one being polled
+            const int next = slot ^ 1;
+            if (use_graphs && rounds_runs == 0 && !gexec[0] && polls == 1 && parity == 0) {
+                // G now holds the batch length that takes ~4 ms
+                st = build_graphs(std::min(G, 64));
+                if (st != MLCC_OK) break;
+            }
+            st = enqueue_batch(next, G);
             if (st != MLCC_OK) break;
-        }
-        st = enqueue_batch(next, G);
-        if (st != MLCC_OK) break;
-        if (hipEventSynchronize(done_ev[slot]) != hipSuccess) {
-            st = fail(MLCC_ERR_HIP, "sweep batch failed: %s", hipGetErrorString(hipGetLastError()));
-            break;
-        }
-        ++polls;
-        const Control h = *pin_ctl(slot);
-        harvest(slot);
-        if (h.active_fronts == 0) {
-            // drain the batch queued ahead (it found nothing to do)
-            if (hipEventSynchronize(done_ev[next]) != hipSuccess) {
-                st = fail(MLCC_ERR_HIP, "sweep batch failed");
+            if (hipEventSynchronize(done_ev[slot]) != hipSuccess) {
+                st = fail(MLCC_ERR_HIP, "sweep batch failed: %s",
+                          hipGetErrorString(hipGetLastError()));
                 break;
             }
-            harvest(next);
-            break;
+            ++polls;
+            const Control h = *pin_ctl(slot);
+            harvest(slot);
+            if (h.active_fronts == 0) {
+                // drain the batch queued ahead (it found nothing to do)
+                if (hipEventSynchronize(done_ev[next]) != hipSuccess) {
+                    st = fail(MLCC_ERR_HIP, "sweep batch failed");
+                    break;
+                }
+                harvest(next);
+                break;
+            }
+            if (launched > launch_cap) {
+                st = fail(MLCC_ERR_HIP, "root finder exceeded %lld rounds", (long long)launch_cap);
+                break;
+            }
+            // poll roughly every 4 ms of GPU work
+            auto now = std::chrono::steady_clock::now();
+            const double dt = std::chrono::duration<double, std::milli>(now - t_last).count();
+            t_last = now;
+            const double per = dt / std::max(1, batch_len[slot]);
+            G = (int)std::min<double>(MAX_BATCH, std::max<double>(2.0, 4.0 / std::max(per, 1e-3)));
+            G &= ~1;   // even batches keep the ping-pong parity at 0 between batches
+            slot = next;
         }
-        if (launched > launch_cap) {
-            st = fail(MLCC_ERR_HIP, "root finder exceeded %lld rounds", (long long)launch_cap);
-            break;
-        }
-        // poll roughly every 4 ms of GPU work
-        auto now = std::chrono::steady_clock::now();
-        const double dt = std::chrono::duration<double, std::milli>(now - t_last).count();
-        t_last = now;
-        const double per = dt / std::max(1, batch_len[slot]);
-        G = (int)std::min<double>(MAX_BATCH, std::max<double>(2.0, 4.0 / std::max(per, 1e-3)));
-        G &= ~1;   // even batches keep the ping-pong parity at 0 between batches
-        slot = next;
+        ++rounds_runs;
+        return st;
+    };
+
+    // Passes (cold starts, the rows next to them, roots the expansions left
+    // open) and expansions in turn until every front is done.
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (persistent && p->timing) {
+        MLCC_HIP(hipEventCreate(&e0));
+        MLCC_HIP(hipEventCreate(&e1));
     }
+    mlcc_status st = persistent ? setup_persistent() : MLCC_OK;
+    if (st == MLCC_OK && e0) (void)hipEventRecord(e0, rs);
+    int active = F, parked = 0;
+    while (st == MLCC_OK) {
+        if (active > 0) st = persistent ? run_persistent() : run_rounds();
+        if (st != MLCC_OK || xfrom == 0) break;
+        st = run_expansions(active, parked);
+        if (active == 0 && parked == 0) break;
+    }
+    if (e0) {
+        float ms = 0.f;
+        (void)hipEventRecord(e1, rs);
+        (void)hipEventSynchronize(e1);
+        (void)hipEventElapsedTime(&ms, e0, e1);
+        (void)hipEventDestroy(e0);
+        (void)hipEventDestroy(e1);
+        persistent_ms = ms;
+    }
+    if (persistent) persistent_launches = 1;
+    if (pgraph) (void)hipGraphExecDestroy(pgraph);
     (void)hipStreamSynchronize(rs);
     cleanup();
     if (st != MLCC_OK) return st;
@@ -3469,14 +3803,15 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
                             c->stream));
     MLCC_HIP(hipStreamSynchronize(c->stream));
     // the multipole tallies, summed over their copies
-    uint64_t ft[9] = {};
+    uint64_t ft[FMM_T_ALL] = {};
     for (int q = 0; q < FMM_STRIPES; ++q)
-        for (int v = 0; v < 9; ++v) ft[v] += tally[(size_t)q * FMM_STRIPE_U64 + v];
+        for (int v = 0; v < FMM_T_ALL; ++v) ft[v] += tally[(size_t)q * FMM_STRIPE_U64 + v];
     const uint64_t fmm_near = ft[FMM_T_F64], fmm_far[2] = {ft[FMM_T_F64 + 1], ft[FMM_T_F64 + 2]};
     const uint64_t fmm_near_polish = ft[FMM_T_POLISH],
                    fmm_far_polish[2] = {ft[FMM_T_POLISH + 1], ft[FMM_T_POLISH + 2]};
     const uint64_t fmm_near_f32 = ft[FMM_T_F32],
                    fmm_far_f32[2] = {ft[FMM_T_F32 + 1], ft[FMM_T_F32 + 2]};
+    const uint64_t fmm_near_exp = ft[FMM_T_EXP + EXP_NEAR];
 
     mlcc_status result = MLCC_OK;
     double maxdist = 0.0;
@@ -3570,9 +3905,9 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         } else {
             stats->sweeps = h.live_sweeps;
         }
-        stats->root_updates = (int64_t)h.updates;
-        stats->root_updates_f32 = (int64_t)h.updates_f32;
-        stats->polish_updates = (int64_t)h.polish_updates;
+        stats->root_updates = (int64_t)(h.upd[PH_F64] + h.upd[TALLY_ROOTS]);
+        stats->root_updates_f32 = (int64_t)h.upd[PH_F32];
+        stats->polish_updates = (int64_t)(h.upd[PH_POLISH] + h.upd[TALLY_ROOTS + 1]);
         stats->unconverged = h.unconverged;
         stats->rows_capped = h.failed_rows;
         stats->cold_restarts = h.cold_restarts;
@@ -3611,7 +3946,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         // expansion, rarely taken, is counted the same.
         // The FP32 sweeps take such sums in FP64: their star terms move from
         // the FP32 count to the FP64 one.
-        double star64 = (double)h.star_updates, starpol = (double)h.star_updates_polish;
+        double star64 = (double)h.star[PH_F64], starpol = (double)h.star[PH_POLISH];
         double far64 = 0.0, farpol = 0.0, star32_off = 0.0;
         if (fmm_on) {
             const double pf = (double)fmm_recs[0].p;
@@ -3623,25 +3958,37 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
             star64 += (double)fmm_near - (double)fmm_far[1];
             starpol += (double)fmm_near_polish - (double)fmm_far_polish[1];
             star32_off = 29.0 * (double)fmm_far_f32[1];
-            stats->fmm_near_terms = (int64_t)(fmm_near + fmm_near_polish + fmm_near_f32);
-            stats->fmm_far_evals =
-                (int64_t)(fmm_far[0] + fmm_far_polish[0] + fmm_far_f32[0]);
+            stats->fmm_near_terms =
+                (int64_t)(fmm_near + fmm_near_polish + fmm_near_f32 + fmm_near_exp);
+            stats->fmm_far_evals = (int64_t)(fmm_far[0] + fmm_far_polish[0] + fmm_far_f32[0] +
+                                             ft[FMM_T_EXP + EXP_FORMED]);
         }
-        stats->algorithmic_flop = 29.0 * star64 + far64 +
-                                  20.0 * (double)(h.star_updates - h.star_updates_fast -
-                                                  h.star_updates_plain) -
-                                  10.0 * (double)(h.updates - h.updates_fast - h.updates_plain);
+        // Updates from expansions: a step is Horner's rule for f and three
+        // derivatives (32 FLOP per moment) and the step itself; an expansion
+        // MOMENT_FLOP per star term, or per near star and 8 M per order of the
+        // cell's series.
+        constexpr double STEP_FLOP = 32.0 * NMOM + 60.0;
+        constexpr double MOMENT_FLOP = 6.0 + 28.0 + 9.0 * (NMOM - 3);
+        static_assert(NMOM != 14 || (STEP_FLOP == 508.0 && MOMENT_FLOP == 133.0), "as in mlcc.h");
+        const uint64_t *fx = ft + FMM_T_EXP;
+        const double sums = fmm_on ? MOMENT_FLOP * (double)fx[EXP_NEAR] +
+                                         (double)fx[EXP_FORMED] * 8.0 * NMOM * (double)fmm_recs[0].p
+                                   : MOMENT_FLOP * (double)fx[EXP_STARS];
+        const double exp_flop = sums + STEP_FLOP * (double)fx[EXP_STEPS_DONE];
+        const double exp64 = mixed ? 0.0 : exp_flop, exppol = mixed ? exp_flop : 0.0;
+        stats->algorithmic_flop = 29.0 * star64 + far64 + exp64 +
+                                  20.0 * (double)(h.star[PH_F64] - h.star[TALLY_FAST]) -
+                                  10.0 * (double)(h.upd[PH_F64] - h.upd[TALLY_FAST]);
         stats->algorithmic_flop_sweep_roots =
-            20.0 * (double)h.star_updates_fast - 10.0 * (double)h.updates_fast;
+            20.0 * (double)h.star[TALLY_FAST] - 10.0 * (double)h.upd[TALLY_FAST];
         if (n_real == 1) {   // a rectangular field's extra roots: 10 FLOP per root term each
             const double ex = 10.0 * (double)sheet_poly(c->reals[0]).n_extra;
-            stats->algorithmic_flop +=
-                ex * (double)(h.updates - h.updates_fast - h.updates_plain);
-            stats->algorithmic_flop_sweep_roots += ex * (double)h.updates_fast;
+            stats->algorithmic_flop += ex * (double)(h.upd[PH_F64] - h.upd[TALLY_FAST]);
+            stats->algorithmic_flop_sweep_roots += ex * (double)h.upd[TALLY_FAST];
         }
         stats->algorithmic_flop_f32 =
-            49.0 * (double)h.star_updates_f32 - 10.0 * (double)h.updates_f32 - star32_off;
-        stats->algorithmic_flop_polish = 29.0 * starpol + farpol;
+            49.0 * (double)h.star[PH_F32] - 10.0 * (double)h.upd[PH_F32] - star32_off;
+        stats->algorithmic_flop_polish = 29.0 * starpol + farpol + exppol;
     }
     return result;
 }

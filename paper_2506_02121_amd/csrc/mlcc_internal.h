@@ -75,6 +75,7 @@ struct Front {
     int32_t reseed;   // 1: the next FP64 pass restarts the row from its start values
     int32_t par;      // persistent scheduler: which iterate buffer holds the current values
     int32_t npass;    // passes run by this front (all rows)
+    int32_t redo;     // 1: blocks ahead of its row start over from it (expand_rows)
     int32_t seedvar;  // cold start: 0 = the seeds z_i +- 1; 1 = the second set (after a stall)
     int64_t it_off;   // first element of its roots in the iterate and flag arrays
 };
@@ -98,8 +99,8 @@ struct Real {
     int32_t n_extra;    // roots beyond 2 N: t - 1 for a rectangular field
     int32_t root32;     // MLCC_FP64_R32: warm FP64 rows take the root-root sum in FP32
     int32_t restart;    // FP64 sweeps after which an unsettled cold start begins again
-    int32_t xrows;      // persistent mixed form: further rows a polish pass may finish (0: none)
     int32_t chunk;      // persistent schedule: blocks of a front per task
+    double sheet_c;     // |c| of a rectangular sheet
     int64_t sheet_off;  // its record in the sheet array: d_2..d_{t-1} (n_poly), the lens-map
                         // terms d_2k / (2k + 1) (n_poly), start values of the extra roots
                         // (2 n_extra: re, im)
@@ -131,28 +132,29 @@ struct SheetPoly {
     double dmap[MAX_SHEET_TERMS] = {};   // d[k-1] / (2k + 1)
 };
 SheetPoly sheet_poly(const RealHost &h);
-enum { FRONT_IDLE = 0, FRONT_ACTIVE = 1, FRONT_DONE = 2, FRONT_FAILED = 3 };
+enum { FRONT_IDLE = 0, FRONT_ACTIVE = 1, FRONT_DONE = 2, FRONT_FAILED = 3,
+       FRONT_PARKED = 4 /* its next rows are the expansion kernel's */ };
 enum { PH_F64 = 0, PH_F32 = 1, PH_POLISH = 2 };
 enum { TRIED_F32 = 1, TRIED_POLISH = 2 };
 
 // Device-side totals of the root finder.
+// Control's tallies: updates with sums over the stars by phase (PH_F64,
+// PH_F32, PH_POLISH); those of warm MLCC_FP64_R32 rows, whose root-root terms
+// run in FP32; roots accepted from expansions, in FP64 rows and in the mixed
+// form's.
+enum { TALLY_FAST = 3, TALLY_ROOTS = 4, TALLIES = 6 };
+
 struct Control {
     int32_t active_fronts;            // fronts still IDLE or ACTIVE
+    int32_t parked_fronts;            // fronts that wait for the expansions
+    int32_t pad;
     int32_t failed_rows;
     int64_t unconverged;
-    unsigned long long updates;       // FP64 Aberth root updates
-    unsigned long long updates_f32;   // FP32 Aberth root updates
-    unsigned long long polish_updates;
     int64_t rows_fallback;            // rows that fell back to FP64 sweeps
     int64_t live_sweeps;              // rounds that found an active front
     int64_t cold_restarts;            // FP64 cold starts begun again from the second seeds
-    unsigned long long star_updates;  // sum over FP64 updates of the field's star count
-    unsigned long long star_updates_f32;
-    unsigned long long star_updates_polish;
-    unsigned long long updates_fast;      // FP64 Aberth updates of warm FP64-mode rows, whose
-    unsigned long long star_updates_fast; // root-root terms run in FP32 (and their star counts)
-    unsigned long long updates_plain;     // FP64 Aberth updates that took the correction from the
-    unsigned long long star_updates_plain; // chain, without a root-root sum (and their star counts)
+    // root updates by TALLY, and the same weighted by their fields' star counts
+    unsigned long long upd[TALLIES], star[TALLIES];
 };
 
 // Tallies of the fast-multipole star sums behind the algorithmic FLOP count,
@@ -163,7 +165,7 @@ struct Control {
 // do not queue on one address; the host sums the copies.
 constexpr int FMM_STRIPES = 16;
 constexpr int FMM_STRIPE_U64 = 16;   // 128 bytes per copy
-enum { FMM_T_F64 = 0, FMM_T_POLISH = 3, FMM_T_F32 = 6 };
+enum { FMM_T_F64 = 0, FMM_T_POLISH = 3, FMM_T_F32 = 6, FMM_T_EXP = 9, FMM_T_ALL = 13 };
 
 struct Ctx {
     int device = 0;
@@ -190,8 +192,9 @@ struct Ctx {
     DevBuf flagrow;   // int32[F * n_r]: row at which the root was flagged
     DevBuf fronts;    // Front[F]
     DevBuf counts;    // int32[F]: unflagged roots after the last sweep
-    DevBuf passupd;   // int32[2 * F]: roots updated by the last pass, and those of them
-                      // without a root-root sum
+    DevBuf passupd;   // int32[F]: roots updated by the last round's pass
+    DevBuf next_row;  // int32[2 * blocks]: expansions: each block's next row, and whether it is
+                      // stuck there
     DevBuf control;   // Control
     DevBuf fmm_tally; // uint64[FMM_STRIPES * FMM_STRIPE_U64]: multipole tallies
     DevBuf etab;      // double2[m + 1]: (1 - kappa_s) e^{-i phi_j}
@@ -202,7 +205,6 @@ struct Ctx {
     DevBuf workflags; // int32[poll batch]: phases active in round i
     DevBuf vieta;     // double4[2 * blocks]: per-block row sums and error terms (mixed mode)
     DevBuf errbuf;    // double[F * n_r]: estimated error of each polished root
-    DevBuf fprime;    // double2[FP_RING][F * n_r]: F' at the accepted roots of the last rows
     DevBuf vsum;      // double4[2 * F]: each front's row sums (mixed mode)
     DevBuf pq;        // persistent scheduler: queue header, task ring, slot sequence, pass counts
     DevBuf reals_d;   // Real[n_real]
