@@ -51,8 +51,7 @@ typedef enum {
                       2^-53 for a correctly rounded division); consecutive star terms,
                       and consecutive root-root terms, are taken in groups of eight that
                       share one refined reciprocal of the product of their eight |d|^2.
-                      With predictor > 0, warm rows with three finished rows behind them
-                      are solved from the star field's Taylor expansion about a point of
+                      With predictor > 0, warm rows are solved from the star field's Taylor expansion about a point of
                       each root's chain (14 moments sum m_i u_i^k, every star entering them
                       directly; used only where the terms left out stay below the sums'
                       rounding), with the correction -F''/(2 F') that 2 S1 - R equals at a
@@ -206,7 +205,9 @@ typedef struct {
     int64_t m_steps;       /* phase steps m, even, >= 2: row j <-> phi_j = 2 pi j / m,
                               rows 0..m (Sec. 3.1, Sec. 4.3) */
     int32_t n_subchains;   /* S subchains (Sec. 4.3), each grown from its centre row;
-                              must divide m/2.  0 = chosen by the library */
+                              must divide m/2.  0 = chosen by the library, which for one
+                              field may then grow fewer and longer pieces beside the
+                              first subchain's centre row (predictor > 0) */
     int32_t max_iter_cold; /* sweep cap for a cold-started row (0 = 500) */
     int32_t max_iter_warm; /* sweep cap for a warm-started row (0 = 100) */
     int32_t precision;     /* mlcc_precision */
@@ -254,7 +255,7 @@ typedef struct {
     int64_t unconverged;     /* roots still unflagged in rows that hit a cap */
     int64_t rows_capped;     /* rows that hit an iteration cap */
     int64_t rows_fallback;   /* rows that fell back to FP64 Aberth sweeps (MLCC_MIXED) */
-    int32_t n_subchains;     /* S actually used */
+    int32_t n_subchains;     /* S used: the first piece's centre row is m / (2 S) */
     int32_t max_row_sweeps;  /* most passes (of any kind) any warm row needed */
     int32_t cold_sweeps;     /* most passes any cold start needed */
     int32_t polls;           /* host polls of the device-side front table */

@@ -1117,6 +1117,9 @@ constexpr double EXP_TAIL = 2e-17;
 // A root this does not settle in EXP_STEPS steps is left to the row's passes.
 constexpr double EXP_BASIN = 0.05;
 constexpr double EXP_ERR = 1e-16;
+// A new expansion is formed this share of the last one's reach ahead.
+// (N = 6,000 FP64: 79 ms a call at 0, 72 at 1/2, 70 at 3/4 and 0.9.)
+constexpr double EXP_LEAD = 0.75;
 constexpr int EXP_STEPS = 4;
 
 struct Moments {
@@ -1465,18 +1468,27 @@ expand_rows(RoundArgs<typename StarRec<EQUAL>::T> A)
         Update u{};
         for (int it = 0; it < EXP_STEPS; ++it) {
             if (!__ballot(going)) break;
-            const double ox = xr - cr, oy = xi - ci;
-            bool fresh = going && !(ox * ox + oy * oy <= reach2);
-            const unsigned long long mask = __ballot(fresh);
-            if (mask) {
+            // lanes out of reach of their expansion form a new one, ahead of them by
+            // most of the last one's reach along their chain, so that it serves
+            // from one edge to the other; at their own place if that is still
+            // too far
+            for (int ahead = it == 0; ahead >= 0; --ahead) {
+                const double ox = xr - cr, oy = xi - ci;
+                bool fresh = going && !(ox * ox + oy * oy <= reach2);
+                const unsigned long long mask = __ballot(fresh);
+                if (!mask) break;
                 if (FMM || __popcll(mask) > SPARSE_MAX) fresh = valid;
+                const double vx = pr - z1.x, vy = pi - z1.y, v2 = vx * vx + vy * vy;
+                const double lead =
+                    ahead && reach2 > 0.0 && v2 > 0.0 ? EXP_LEAD * sqrt(reach2 / v2) : 0.0;
+                const double tx = fma(lead, vx, xr), ty = fma(lead, vy, xi);
                 int near = 0;
-                sum_moments<EQUAL, FMM>(A, B, __ballot(fresh), xr, xi, tiles, Mo, near);
+                sum_moments<EQUAL, FMM>(A, B, __ballot(fresh), tx, ty, tiles, Mo, near);
                 if (fresh) {
                     if (B.n_poly > 0)
-                        add_moments_sheet(Mo, B.sheet + B.n_poly, B.n_poly, B.sheet_c, xr, xi);
-                    cr = xr;
-                    ci = xi;
+                        add_moments_sheet(Mo, B.sheet + B.n_poly, B.n_poly, B.sheet_c, tx, ty);
+                    cr = tx;
+                    ci = ty;
                     reach2 = moments_reach2(Mo);
                     t_exp += 1;
                     t_near += near;
@@ -2948,6 +2960,50 @@ static int autotune_subchains(const std::vector<RealHost> &reals, int64_t m, boo
     return best_s;
 }
 
+// A piece of the phase grid grown from one cold start at its centre row.
+struct Piece {
+    int64_t lo, hi, cen;
+};
+
+// With rows from expansions a cold start (11-30 sweeps over every star and
+// root) costs as much as hundreds of rows, so it is the cold starts that make
+// up a call, and no more of them are made than keep the device full: pieces
+// whose fronts hold COLD_BLOCKS blocks of 64 roots between them.  The first
+// one keeps the centre row of the first of S equal subchains, whose cold start
+// numbers the columns.  Measured, ms a call, with one piece per subchain / 2048 /
+// 4096 / 6144 blocks: N = 6,000 FP64 104 / 112 / 73 / 77 (a few long pieces wait
+// for their stuck blocks); N = 4,099 mixed 49 / 32 / 36 / 38; N = 1,000 FP64 14.3 /
+// 9.6 / 11.2 / 12.6; N = 3,000 FP64 with multipole sums 22.2 / 15.7 / 17.2 / 18.5;
+// N = 10,000 mixed with them 67 / 61 / 62 / 65; rectangular N = 437 6.9 / 5.4 / 6.0 /
+// 6.9.  Batches keep their subchains: their largest fields' pieces would set the
+// time (40 fields mixed 65 / 197 / 134 / 112).
+#ifndef MLCC_COLD_BLOCKS
+#define MLCC_COLD_BLOCKS 4096
+#endif
+
+static std::vector<Piece> plan_pieces(const std::vector<RealHost> &reals, int64_t m, int S,
+                                      bool fewer)
+{
+    int64_t blocks = 0;
+    for (const RealHost &r : reals) blocks += ceil_div(2 * r.n + sheet_poly(r).n_extra, 64);
+    const int64_t L = m / S;
+    const int64_t n =
+        fewer ? std::min<int64_t>(S, std::max<int64_t>(1, MLCC_COLD_BLOCKS / (2 * blocks))) : S;
+    std::vector<Piece> v;
+    if (n == S) {
+        for (int64_t s = 0; s < S; ++s) v.push_back(Piece{s * L, (s + 1) * L, s * L + L / 2});
+        return v;
+    }
+    // the first piece's upper half is as long as the halves of the others
+    const int64_t first = n == 1 ? m : (L * (n - 1) + m) / (2 * n - 1);
+    v.push_back(Piece{0, first, L / 2});
+    for (int64_t s = 1; s < n; ++s) {
+        const int64_t lo = v.back().hi, hi = first + (m - first) * s / (n - 1);
+        v.push_back(Piece{lo, hi, lo + (hi - lo) / 2});
+    }
+    return v;
+}
+
 // ---------------------------------------------------------------------------
 // Work groups of the persistent launch
 // ---------------------------------------------------------------------------
@@ -3132,7 +3188,13 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
                                p->star_sums == MLCC_STARS_FMM,
                                p->schedule == MLCC_SCHEDULE_PERSISTENT);
     if ((m / 2) % S) return fail(MLCC_ERR_INVALID, "n_subchains=%d must divide m/2", S);
-    const int64_t L = m / S;
+    // Grown pieces of the phase grid: the S subchains, or, where S is the
+    // library's choice and rows come from expansions, fewer and longer ones.
+    const std::vector<Piece> pieces =
+        plan_pieces(c->reals, m, S, p->n_subchains <= 0 && p->predictor > 0 && n_real == 1);
+    const int NP = (int)pieces.size();
+    int64_t L = 0;   // rows of the longest half
+    for (const Piece &x : pieces) L = std::max({L, 2 * (x.hi - x.cen), 2 * (x.cen - x.lo)});
     const int max_cold = p->max_iter_cold > 0 ? p->max_iter_cold : 500;
     const int max_warm = p->max_iter_warm > 0 ? p->max_iter_warm : 100;
     constexpr int MAX_BATCH = 256;
@@ -3145,11 +3207,11 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
     std::vector<int2> bmap;
     int64_t it_total = 0, bnd_total = 0, max_nr = 0;
     const int32_t warm_phase = mixed ? PH_F32 : PH_F64;
-    // finished rows a warm row needs behind it to be solved by expansions: in
-    // FP64 as many as the quadratic extrapolation takes (from a poorer start many
-    // roots are left to Aberth steps, which then start from a row part old, part
-    // new), in the mixed form the two after which rows start with a polish
-    const int32_t xfrom = p->predictor > 0 ? (mixed ? 2 : 3) : 0;
+    // finished rows a warm row needs behind it to be solved by expansions: the
+    // centre row in FP64; in the mixed form the two after which rows start with a
+    // polish; and two in MLCC_FP64_R32, where one row a front keeps its FP32
+    // root-root sums
+    const int32_t xfrom = p->predictor > 0 ? (p->precision == MLCC_FP64 ? 1 : 2) : 0;
     for (int r = 0; r < n_real; ++r) {
         const RealHost &h = c->reals[r];
         const SheetPoly sp = sheet_poly(h);
@@ -3160,7 +3222,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         R.star_off = h.star_off;
         R.out_off = (m + 1) * 2 * h.star_off;
         R.bnd_off = bnd_total;
-        bnd_total += (int64_t)(S - 1) * n_r;
+        bnd_total += (int64_t)(NP - 1) * n_r;
         R.n_stars = (int32_t)h.n;
         R.n_r = (int32_t)n_r;
         R.m0 = h.m0;
@@ -3196,8 +3258,9 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         R.root32 = p->precision == MLCC_FP64_R32 ? 1 : 0;
         R.restart = p->cold_restart_sweeps > 0 ? p->cold_restart_sweeps : STALL_START;
         const int bpf = (int)ceil_div(n_r, 64);
-        for (int s = 0; s < S; ++s) {
-            const int32_t lo = (int32_t)(s * L), hi = (int32_t)(lo + L), cen = (int32_t)(lo + L / 2);
+        for (int s = 0; s < NP; ++s) {
+            const int32_t lo = (int32_t)pieces[s].lo, hi = (int32_t)pieces[s].hi,
+                          cen = (int32_t)pieces[s].cen;
             const int fd = (int)fr.size();
             Front d{};
             d.row = cen; d.dir = 0; d.end_row = lo; d.state = FRONT_ACTIVE;
@@ -3824,7 +3887,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         // then pair row m with row 0 for chain_next
         std::vector<PairJob> jobs;
         int64_t perm_total = 0;
-        for (int r = 0; r < n_real; ++r) perm_total += (int64_t)S * rd[r].n_r;
+        for (int r = 0; r < n_real; ++r) perm_total += (int64_t)NP * rd[r].n_r;
         MLCC_TRY(c->perm.reserve((size_t)std::max<int64_t>(perm_total, 1) * sizeof(int32_t)));
         int32_t *perm = c->perm.as<int32_t>();
         std::vector<int64_t> perm_off(n_real);
@@ -3833,21 +3896,21 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
             perm_off[r] = po;
             const int64_t n_r = rd[r].n_r;
             double *ore = roots_re + rd[r].out_off, *oim = roots_im + rd[r].out_off;
-            for (int s = 1; s < S; ++s) {
+            for (int s = 1; s < NP; ++s) {
                 PairJob j{};
                 j.a2 = c->bnd.as<double2>() + rd[r].bnd_off + (int64_t)(s - 1) * n_r;
-                j.b_re = ore + s * L * n_r;
-                j.b_im = oim + s * L * n_r;
+                j.b_re = ore + pieces[s].lo * n_r;
+                j.b_im = oim + pieces[s].lo * n_r;
                 j.perm = perm + po + s * n_r;
                 j.n = n_r;
                 jobs.push_back(j);
             }
-            po += (int64_t)S * n_r;
+            po += (int64_t)NP * n_r;
         }
         double md = 0.0;
         MLCC_TRY(pair_all(c, jobs, 1e-6, &md));
         maxdist = std::max(maxdist, md);
-        if (S > 1) {
+        if (NP > 1) {
             std::vector<int32_t> hp((size_t)perm_total), lab((size_t)perm_total);
             MLCC_HIP(hipMemcpyAsync(hp.data(), perm, (size_t)perm_total * sizeof(int32_t),
                                     hipMemcpyDeviceToHost, c->stream));
@@ -3855,7 +3918,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
             for (int r = 0; r < n_real; ++r) {
                 const int64_t n_r = rd[r].n_r, b = perm_off[r];
                 for (int64_t k = 0; k < n_r; ++k) lab[b + k] = (int32_t)k;
-                for (int s = 1; s < S; ++s)
+                for (int s = 1; s < NP; ++s)
                     for (int64_t k = 0; k < n_r; ++k)
                         lab[b + s * n_r + k] = lab[b + (s - 1) * n_r + hp[b + s * n_r + k]];
             }
@@ -3864,13 +3927,13 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
             std::vector<RelabelJob> rj;
             for (int r = 0; r < n_real; ++r) {
                 const int64_t n_r = rd[r].n_r;
-                for (int s = 1; s < S; ++s) {
+                for (int s = 1; s < NP; ++s) {
                     const int32_t *lb = perm + perm_off[r] + s * n_r;
                     rj.push_back(RelabelJob{roots_re + rd[r].out_off, roots_im + rd[r].out_off,
-                                            n_r, s * L + 1, (s + 1) * L + 1, lb});
+                                            n_r, pieces[s].lo + 1, pieces[s].hi + 1, lb});
                     if (caus_re)
                         rj.push_back(RelabelJob{caus_re + rd[r].out_off, caus_im + rd[r].out_off,
-                                                n_r, s * L + 1, (s + 1) * L + 1, lb});
+                                                n_r, pieces[s].lo + 1, pieces[s].hi + 1, lb});
                 }
             }
             MLCC_TRY(relabel_all(c, rj));
