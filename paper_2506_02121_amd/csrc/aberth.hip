@@ -688,6 +688,113 @@ fmm_p2l(int32_t G, int32_t p, int32_t stride, double x0, double y0, double w, in
     if (lane == 0) qfar[cell] = q;
 }
 
+// The same rows bit for bit, a lane a cell, for many cells: the columns of a
+// field are numbered by its cold start, which follows the last bit of these
+// sums, so every order adds up its terms star by star as above.  A wave takes
+// 64 cells and KB of the orders from k0 on: the stars go by in tiles parked in
+// LDS, and their powers, by the same successive products, are added straight
+// into registers (6 FP64 instructions per order and star, 8 for unequal masses,
+// 4 for the orders before k0).  It is bound by that arithmetic on as many SIMDs
+// as there are waves.  N = 10,000 (16,900 cells): 14.9 ms with one work group a
+// cell and the powers through LDS, 8.0 with this (4.0 with the stars split too,
+// but then the columns came out numbered otherwise); 96 fields of 50 to 600
+// stars, 96 launches there and one here: 1.95 -> 0.65 ms; N = 3,000 (5,200
+// cells): 1.4 there, ~2.4 here.
+struct P2lJob {
+    int32_t field, cell0, k0, n;   // n: the field's stars
+};
+
+template <int KB, bool EQUAL>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 8)))
+fmm_p2l_lanes(const P2lJob *__restrict__ jobs, const FmmArgs *__restrict__ recs)
+{
+    __shared__ double4 tile[64];   // x, y, weight, cell column and row
+    const P2lJob J = jobs[blockIdx.x];
+    const FmmArgs &M = recs[J.field];
+    const int n = J.n;
+    const double4 *__restrict__ st = M.fstars;
+    const int lane = threadIdx.x, G = M.G;
+    const int cell = min(J.cell0 + lane, G * G - 1);
+    const int ix = cell % G, iy = cell / G;
+    const double w = M.w, cx = fma(w, ix + 0.5, M.x0), cy = fma(w, iy + 0.5, M.y0);
+    double fr[KB], fi[KB], gr[KB], gi[KB], q = 0.0;
+#pragma unroll
+    for (int k = 0; k < KB; ++k) fr[k] = fi[k] = gr[k] = gi[k] = 0.0;
+    for (int i0 = 0; i0 < n; i0 += 64) {
+        const int cnt = min(64, n - i0);
+        if (lane < cnt) {
+            double4 a = st[i0 + lane];
+            const int sc = (int)a.w;
+            a.w = __hiloint2double(sc / G, sc % G);
+            tile[lane] = a;
+        }
+        wave_sync();
+        // two stars at a time, for two independent chains of products; each sum
+        // still takes its terms in star order
+        for (int t = 0; t < cnt; t += 2) {
+            double vr[2], vi[2], pr[2], pi[2], wi[2];
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const double4 a = tile[min(t + c, cnt - 1)];
+                const int sx = __double2loint(a.w), sy = __double2hiint(a.w);
+                const bool far = t + c < cnt && (abs(sx - ix) > 1 || abs(sy - iy) > 1);
+                const double dx = a.x - cx, dy = a.y - cy;
+                const double r2 = fma(dx, dx, dy * dy);
+                vr[c] = far ? w * dx / r2 : 0.0;
+                vi[c] = far ? -w * dy / r2 : 0.0;
+                wi[c] = EQUAL ? 1.0 : a.z;
+                pr[c] = vr[c];
+                pi[c] = vi[c];
+                if (J.k0 == 0 && far) {
+                    const double ex = fmax(fabs(dx) - 0.5 * w, 0.0);
+                    const double ey = fmax(fabs(dy) - 0.5 * w, 0.0);
+                    const double d2 = fma(ex, ex, ey * ey);
+                    q += wi[c] / (d2 * d2);
+                }
+            }
+            auto next = [&](int c) {
+                const double tr = fma(vr[c], pr[c], -(vi[c] * pi[c]));
+                pi[c] = fma(vr[c], pi[c], vi[c] * pr[c]);
+                pr[c] = tr;
+            };
+#pragma unroll 4
+            for (int k = 0; k < J.k0; ++k) {
+                next(0);
+                next(1);
+            }
+#pragma unroll
+            for (int k = 0; k < KB; ++k) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    if (EQUAL) {
+                        fr[k] -= pr[c];
+                        fi[k] -= pi[c];
+                    } else {
+                        fr[k] = fma(-wi[c], pr[c], fr[k]);
+                        fi[k] = fma(-wi[c], pi[c], fi[k]);
+                        gr[k] -= pr[c];
+                        gi[k] -= pi[c];
+                    }
+                    next(c);
+                }
+            }
+        }
+        wave_sync();
+    }
+    if (J.cell0 + lane >= G * G) return;
+    double2 *cf = const_cast<double2 *>(M.cf) + (int64_t)cell * M.stride + J.k0;
+    double2 *cg = const_cast<double2 *>(M.cg) + (int64_t)cell * M.stride + J.k0;
+#pragma unroll
+    for (int k = 0; k < KB; ++k) {
+        if (J.k0 + k >= M.stride) continue;
+        const double s = J.k0 + k <= M.p ? 1.0 / w : 0.0;
+        const double2 f = make_double2(fr[k] * s, fi[k] * s);
+        cf[k] = f;
+        cg[k] = EQUAL ? f : make_double2(gr[k] * s, gi[k] * s);
+    }
+    if (J.k0 == 0) const_cast<double *>(M.qfar)[cell] = q;
+}
+
 // Calls body(star) for the stars of the 3 x 3 cells around `cell`, in the
 // order of the sorted list (the block's three grid rows, each a run of
 // adjacent cells), and returns their number.  The records are read
@@ -3159,15 +3266,48 @@ static mlcc_status build_fmm(Ctx *c, int order, bool equal, std::vector<FmmArgs>
         M.qfar = c->fmm_q.as<double>() + g.cell_off;
         M.mf = c->fmm_m.as<double2>() + (size_t)r * 2 * (pp + 1);
         M.mg = M.mf + (pp + 1);
-        const unsigned ncell = (unsigned)((int64_t)g.G * g.G);
-        hipLaunchKernelGGL(fmm_p2l, dim3(ncell), dim3(64), 0, c->stream, g.G, pp, stride, g.x0,
-                           g.y0, g.w, (int32_t)equal, (int32_t)c->reals[r].n, M.fstars,
-                           const_cast<double2 *>(M.cf), const_cast<double2 *>(M.cg),
-                           const_cast<double *>(M.qfar));
     }
-    MLCC_HIP(hipGetLastError());
     MLCC_HIP(hipMemcpyAsync(c->fmm_args.p, recs.data(), recs.size() * sizeof(FmmArgs),
                             hipMemcpyHostToDevice, c->stream));
+    // the cells' expansions, by the kernel that takes less time: a work group a
+    // cell costs 0.09 ns per cell and star and ~8 us a launch; a lane a cell 0.8 us
+    // per star of the largest field while there is a SIMD for every wave
+    const int kb = stride == 56 ? 28 : 32, parts = (int)ceil_div(stride, kb);
+    std::vector<P2lJob> jobs;
+    double by_group = 0.0;
+    int64_t n_max = 0;
+    for (int r = 0; r < n_real; ++r) {
+        const int64_t n = c->reals[r].n, cells = (int64_t)grids[r].G * grids[r].G;
+        by_group += 8.0 + 9e-5 * (double)cells * (double)n;
+        n_max = std::max(n_max, n);
+        for (int64_t b = 0; b < cells; b += 64)
+            for (int h = 0; h < parts; ++h) jobs.push_back(P2lJob{r, (int32_t)b, h * kb, (int32_t)n});
+    }
+    const double by_lane = 8.0 + 0.8 * (double)n_max * std::max(1.0, (double)jobs.size() / 1024.0);
+    if (by_lane < by_group) {
+        MLCC_TRY(c->fmm_jobs.reserve(jobs.size() * sizeof(P2lJob)));
+        MLCC_HIP(hipMemcpyAsync(c->fmm_jobs.p, jobs.data(), jobs.size() * sizeof(P2lJob),
+                                hipMemcpyHostToDevice, c->stream));
+        auto lanes = [&](auto k, auto e) {
+            hipLaunchKernelGGL((fmm_p2l_lanes<decltype(k)::value, decltype(e)::value>),
+                               dim3((unsigned)jobs.size()), dim3(64), 0, c->stream,
+                               c->fmm_jobs.as<P2lJob>(), c->fmm_args.as<FmmArgs>());
+        };
+        using K28 = std::integral_constant<int, 28>;
+        using K32 = std::integral_constant<int, 32>;
+        if (kb == 28) equal ? lanes(K28{}, std::true_type{}) : lanes(K28{}, std::false_type{});
+        else equal ? lanes(K32{}, std::true_type{}) : lanes(K32{}, std::false_type{});
+    } else {
+        for (int r = 0; r < n_real; ++r) {
+            const Grid &g = grids[r];
+            const FmmArgs &M = recs[r];
+            hipLaunchKernelGGL(fmm_p2l, dim3((unsigned)((int64_t)g.G * g.G)), dim3(64), 0, c->stream,
+                               g.G, pp, stride, g.x0, g.y0, g.w, (int32_t)equal,
+                               (int32_t)c->reals[r].n, M.fstars, const_cast<double2 *>(M.cf),
+                               const_cast<double2 *>(M.cg), const_cast<double *>(M.qfar));
+        }
+    }
+    MLCC_HIP(hipGetLastError());
     // host vectors must outlive the copies
     MLCC_HIP(hipStreamSynchronize(c->stream));
     return MLCC_OK;

@@ -185,7 +185,7 @@ void mlcc_destroy(mlcc_ctx *ctx)
                       &c.bnd, &c.perm, &c.match_aux, &c.relabel, &c.workflags, &c.vieta, &c.errbuf, &c.next_row, &c.vsum,
                       &c.pq, &c.passupd, &c.reals_d, &c.bmap, &c.diff, &c.edt_col,
                       &c.dmask, &c.fmm_cs, &c.fmm_st, &c.fmm_st2, &c.fmm_cf, &c.fmm_cg,
-                      &c.fmm_q, &c.fmm_m, &c.fmm_args};
+                      &c.fmm_q, &c.fmm_m, &c.fmm_args, &c.fmm_jobs};
     for (DevBuf *b : bufs) b->release();
     if (c.own_stream) (void)hipStreamDestroy(c.own_stream);
     if (c.pinned) (void)hipHostFree(c.pinned);

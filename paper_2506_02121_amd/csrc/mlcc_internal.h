@@ -218,7 +218,7 @@ struct Ctx {
     // fast multipole star sums: the stars sorted by grid cell and each cell's
     // expansions (built by the root finder when asked for)
     std::vector<double4> hstars;   // host copy of the stars (x, y, m, 0)
-    DevBuf fmm_cs, fmm_st, fmm_st2, fmm_cf, fmm_cg, fmm_q, fmm_m, fmm_args;
+    DevBuf fmm_cs, fmm_st, fmm_st2, fmm_cf, fmm_cg, fmm_q, fmm_m, fmm_args, fmm_jobs;
 
     void *pinned = nullptr; // host-pinned readback area
     size_t pinned_bytes = 0;
