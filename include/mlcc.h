@@ -51,8 +51,9 @@ typedef enum {
                       2^-53 for a correctly rounded division); consecutive star terms,
                       and consecutive root-root terms, are taken in groups of eight that
                       share one refined reciprocal of the product of their eight |d|^2.
-                      With predictor > 0, warm rows are solved from the star field's Taylor expansion about a point of
-                      each root's chain (14 moments sum m_i u_i^k, every star entering them
+                      With predictor > 0, warm rows are solved from the star
+                      field's Taylor expansion about a point of each root's chain
+                      (14 moments sum m_i u_i^k, every star entering them
                       directly; used only where the terms left out stay below the sums'
                       rounding), with the correction -F''/(2 F') that 2 S1 - R equals at a
                       root, as long as |F F''/(2 F'^2)| < 0.05; every other root takes Aberth

@@ -1395,6 +1395,43 @@ __device__ __forceinline__ void add_moments_sheet(Moments &S, const double *__re
     S.u2 = u * u;
 }
 
+// The wave's sums of its lanes' moments, in every lane.  At each level a lane
+// hands half of its values over and adds the other half, so 32 exchanges and
+// as many broadcasts do what six exchanges a value did (174).
+__device__ __forceinline__ void spread_sums(Moments &S, int lane)
+{
+    static_assert(2 * NMOM + 1 <= 32, "one value a pair of lanes");
+    double v[32];
+#pragma unroll
+    for (int k = 0; k < NMOM; ++k) {
+        v[2 * k] = S.r[k];
+        v[2 * k + 1] = S.i[k];
+    }
+    v[2 * NMOM] = S.q;
+#pragma unroll
+    for (int k = 2 * NMOM + 1; k < 32; ++k) v[k] = 0.0;
+#pragma unroll
+    for (int half = 16; half >= 1; half >>= 1) {
+        const bool up = lane & (2 * half);
+#pragma unroll
+        for (int j = 0; j < half; ++j) {
+            const double give = up ? v[j] : v[j + half], keep = up ? v[j + half] : v[j];
+            v[j] = keep + __shfl_xor(give, 2 * half, 64);
+        }
+    }
+    const double w = v[0] + __shfl_xor(v[0], 1, 64);   // value lane / 2
+    auto from = [&](int src) {
+        return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(w), src),
+                                __builtin_amdgcn_readlane(__double2loint(w), src));
+    };
+#pragma unroll
+    for (int k = 0; k < NMOM; ++k) {
+        S.r[k] = from(4 * k);
+        S.i[k] = from(4 * k + 2);
+    }
+    S.q = from(4 * NMOM);
+}
+
 // Moments about (zr, zi) for the lanes of `mask`; the other lanes keep theirs
 // where the mask holds few lanes and no multipole sums are on, and receive
 // moments about their own (zr, zi) otherwise.  Direct sums: the whole wave one
@@ -1450,16 +1487,15 @@ __device__ __forceinline__ void sum_moments(const RoundArgs<typename StarRec<EQU
         const double xk = __shfl(zr, l, 64), yk = __shfl(zi, l, 64);
         Moments C;
         zero(C);
-        for (int i = B.lane; i < B.n_stars; i += 64)
-            add_moments_star<EQUAL>(C, xk, yk, B.stars[i]);
-#pragma unroll
-        for (int k = 0; k < NMOM; ++k) {
-            wave_sum(C.r[k]);
-            wave_sum(C.i[k]);
+        int i = B.lane;
+        for (int t = B.n_stars >> 8; t; --t, i += 256) {   // four loads in flight
+            const T r[4] = {B.stars[i], B.stars[i + 64], B.stars[i + 128], B.stars[i + 192]};
+            add_moments_group<EQUAL, 4>(C, xk, yk, r);
         }
-        wave_sum(C.q);
+        for (; i < B.n_stars; i += 64) add_moments_star<EQUAL>(C, xk, yk, B.stars[i]);
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) C.u2 = fmax(C.u2, __shfl_xor(C.u2, off, 64));
+        spread_sums(C, B.lane);
         masses(C);
         if (B.lane == l) S = C;
     }
@@ -1517,7 +1553,17 @@ enum { EXP_NEAR = 0, EXP_STEPS_DONE = 1, EXP_FORMED = 2, EXP_STARS = 3 };
 // registers.  Whole calls, with one sum over the stars per row and with this:
 // N = 6,000 FP64 547 -> 101 ms, N = 1,000 27.4 -> 12.9, N = 4,099 mixed 184 ->
 // 55, rectangular N = 437 10.5 -> 5.6, N = 3,000 FP64 with multipole sums 28.4 ->
-// 22.7, N = 10,000 mixed with them 150 -> 70, 40 fields mixed 130 -> 64 ms.
+// 22.7, N = 10,000 mixed with them 150 -> 70, 40 fields mixed 130 -> 64 ms (with
+// fewer pieces of the phase grid and their nearer starts as well 55, 7.1, 27,
+// 4.8, 12.5, 54 and 54).  A single root's expansion takes four stars a lane at a
+// time, so that their loads are in flight together (58.8 -> 55.4 ms at N = 6,000),
+// and its sums are spread over the lanes in halves (7.8 -> 7.1 at N = 1,000, 57 ->
+// 54 for the 40 fields).  What bounds the kernel now is its last blocks: those
+// whose roots pass close to a star or a critical point form an expansion
+// every few steps, one after another.  Splitting the stars over 2 or 4
+// waves did not help them (61 and 89 ms at N = 6,000 against 58.8), nor did
+// keeping the nearest star out of the expansion (56.3 against 55.4; N = 10,000 with
+// multipole sums 60 against 54).
 // Errors against 80-bit roots of 8 fields of 10 to 3,000 stars: FP64 as before
 // (rms 2e-16 to 2.7e-15), mixed rms 2e-16 to 8e-15 against 2e-14 to
 // 2e-13.
@@ -3021,6 +3067,10 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
 // (polish_pass): a front then needs ~6x fewer passes in a row per row, which
 // an S sweep of n10k (S = 5 ... 40: 299, 288, 289, 303, 311, 340 ms at S = 5,
 // 8, 10, 20, 25, 40) and of the batched workload (S = 2 best) bear out.
+// All of this prices warm rows that sum over every star, as they did before
+// expand_rows; the choice stays what it was because the centre row of the
+// first of the S subchains is where the columns get their numbers (for one
+// field it decides nothing else, plan_pieces; a batch grows its S subchains).
 struct TuneModel {
     double cold_sweeps = 27.0, rounds_per_row = 2.1, tail = 0.8, round_us = 40.0;
     double clock_hz = 2.4e9, simds = 1024.0;
