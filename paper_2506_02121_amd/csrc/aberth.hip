@@ -902,6 +902,7 @@ template <class T> struct RoundArgs {
     // rows a block may be ahead of its front (row sums go to slot row mod
     // ahead), and the stride of the row-sum slots (the launch's block count)
     int32_t *next_row, *stuck;
+    int32_t *root_row;   // FP64: per root its own next row
     int32_t ahead, nvslots;
 };
 
@@ -1544,21 +1545,26 @@ enum { EXP_NEAR = 0, EXP_STEPS_DONE = 1, EXP_FORMED = 2, EXP_STARS = 3 };
 // expansion, which is formed anew about that start once it lies too far from
 // the last centre.  Nothing couples the block's roots to other blocks, so it
 // goes on through its front's rows by itself, from where it stopped last; a
-// row counts when every root of the block is accepted in it.  The first row
-// that leaves a root open ends the block's run (it is stuck): the accepted
-// roots of that row are stored, and the row's passes step the others once
-// every other block has come to it (expand_control).
+// row counts when every root of the block is accepted in it.  At the first row
+// that leaves a root open the block is stuck: the accepted roots of that row are
+// stored, and the row's passes step the others once every other block has come
+// to it (expand_control).  In FP64 only the roots left open wait; the others go
+// on, each with its own next row, so that what is left to do after the passes
+// is one root's rows and not a block's.  In the mixed form the block waits, as
+// a row's sums are taken over all its roots at once.
 //
 // A kernel of its own at two waves per SIMD, so that the moments stay in
 // registers.  Whole calls, with one sum over the stars per row and with this:
 // N = 6,000 FP64 547 -> 101 ms, N = 1,000 27.4 -> 12.9, N = 4,099 mixed 184 ->
 // 55, rectangular N = 437 10.5 -> 5.6, N = 3,000 FP64 with multipole sums 28.4 ->
 // 22.7, N = 10,000 mixed with them 150 -> 70, 40 fields mixed 130 -> 64 ms (with
-// fewer pieces of the phase grid and their nearer starts as well 55, 7.1, 27,
-// 4.8, 12.5, 54 and 54).  A single root's expansion takes four stars a lane at a
+// fewer pieces of the phase grid and their nearer starts as well 45, 6.4, 27,
+// 4.8, 12.6, 54 and 54).  A single root's expansion takes four stars a lane at a
 // time, so that their loads are in flight together (58.8 -> 55.4 ms at N = 6,000),
 // and its sums are spread over the lanes in halves (7.8 -> 7.1 at N = 1,000, 57 ->
-// 54 for the 40 fields).  What bounds the kernel now is its last blocks: those
+// 54 for the 40 fields).  Letting the accepted roots of a stuck block go on by
+// themselves in FP64 took the call at N = 6,000 from 55.4 to 45.2 ms and at
+// N = 1,000 from 7.1 to 6.4.  What bounds the kernel now is its last blocks: those
 // whose roots pass close to a star or a critical point form an expansion
 // every few steps, one after another.  Splitting the stars over 2 or 4
 // waves did not help them (61 and 89 ms at N = 6,000 against 58.8), nor did
@@ -1567,7 +1573,7 @@ enum { EXP_NEAR = 0, EXP_STEPS_DONE = 1, EXP_FORMED = 2, EXP_STARS = 3 };
 // Errors against 80-bit roots of 8 fields of 10 to 3,000 stars: FP64 as before
 // (rms 2e-16 to 2.7e-15), mixed rms 2e-16 to 8e-15 against 2e-14 to
 // 2e-13.
-template <bool EQUAL, bool FMM>
+template <bool EQUAL, bool FMM, bool POLISH>   // POLISH: the mixed form
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MLCC_EXPAND_WAVES, 8)))
 expand_rows(RoundArgs<typename StarRec<EQUAL>::T> A)
 {
@@ -1578,7 +1584,7 @@ expand_rows(RoundArgs<typename StarRec<EQUAL>::T> A)
     if (F->state != FRONT_PARKED) return;
     BlockCtx<typename StarRec<EQUAL>::T> B;
     enter_fq(A, F, fq.x, fq.y, (int32_t *)nullptr, (int32_t *)nullptr, B);
-    const bool polish = F->phase == PH_POLISH;
+    constexpr bool polish = POLISH;
     const int front_row = F->row;
     if (!F->redo) {   // on from where the block stopped, or past the row passes finished since
         const int next = A.next_row[B.vslot];
@@ -1588,14 +1594,15 @@ expand_rows(RoundArgs<typename StarRec<EQUAL>::T> A)
     const int hist0 = B.hist - front_row * B.dir;   // finished rows behind row j: hist0 + j dir
     const int64_t base_f = B.base_f;
     const bool valid = B.valid;
-    double2 z1 = make_double2(0.0, 0.0), z2 = z1, z3 = z1;
-    if (valid && (B.row - B.end_row) * B.dir <= 0) {
-        const int hist = hist0 + B.row * B.dir;
-        const int64_t d = (int64_t)B.dir * n_r, o1 = B.out_off + (int64_t)B.row * n_r + k - d;
-        z1 = make_double2(A.out_re[o1], A.out_im[o1]);
-        if (hist >= 2) z2 = make_double2(A.out_re[o1 - d], A.out_im[o1 - d]);
-        if (hist >= 3) z3 = make_double2(A.out_re[o1 - 2 * d], A.out_im[o1 - 2 * d]);
+    // FP64: the root's own next row; the mixed form's row sums need the block in step
+    int root_row = B.row;
+    if (valid && !polish && !F->redo) {
+        const int next = A.root_row[base_f + k];
+        if ((next - root_row) * B.dir > 0) root_row = next;
     }
+    bool goes_on = valid, loaded = false;   // false: left open in a row of this launch
+    int stuck_row = 0;
+    double2 z1 = make_double2(0.0, 0.0), z2 = z1, z3 = z1;
     Moments Mo;
     zero(Mo);
     double cr = 0.0, ci = 0.0, reach2 = -1.0;   // centre of the expansion, and its reach
@@ -1604,6 +1611,17 @@ expand_rows(RoundArgs<typename StarRec<EQUAL>::T> A)
     for (; (B.row - B.end_row) * B.dir <= 0; B.row += B.dir) {
         // row sums of the mixed form wait for the front's slowest block
         if (polish && (B.row - front_row) * B.dir >= A.ahead) break;
+        if (!__ballot(goes_on && (root_row - B.end_row) * B.dir <= 0)) break;
+        const bool mine = goes_on && root_row == B.row;
+        if (mine && !loaded) {
+            const int hist = hist0 + B.row * B.dir;
+            const int64_t d = (int64_t)B.dir * n_r, o1 = B.out_off + (int64_t)B.row * n_r + k - d;
+            z1 = make_double2(A.out_re[o1], A.out_im[o1]);
+            if (hist >= 2) z2 = make_double2(A.out_re[o1 - d], A.out_im[o1 - d]);
+            if (hist >= 3) z3 = make_double2(A.out_re[o1 - 2 * d], A.out_im[o1 - 2 * d]);
+            reach2 = -1.0;
+            loaded = true;
+        }
         B.boundary = B.has_bnd && B.row == B.end_row;
         const double2 un = A.unit[B.row];
         const double2 e = make_double2(B.a * un.x, B.a * un.y);
@@ -1616,7 +1634,7 @@ expand_rows(RoundArgs<typename StarRec<EQUAL>::T> A)
             pr = fma(3.0, z1.x - z2.x, z3.x);
             pi = fma(3.0, z1.y - z2.y, z3.y);
         }
-        bool going = valid, left = valid;   // left: not accepted in this row
+        bool going = mine, left = mine;   // left: not accepted in this row
         double xr = pr, xi = pi, err = 0.0;
         Update u{};
         for (int it = 0; it < EXP_STEPS; ++it) {
@@ -1694,21 +1712,27 @@ expand_rows(RoundArgs<typename StarRec<EQUAL>::T> A)
                 xi = v.zi;
             }
         }
-        is_stuck = __ballot(left) != 0;
-        if (valid && !left) put(A, B, k, u);
-        if (is_stuck) {
+        if (mine && !left) put(A, B, k, u);
+        if (!is_stuck && __ballot(left)) {   // the block's first row with an open root
+            is_stuck = true;
+            stuck_row = B.row;
             if (valid) {
                 const int64_t i = base_f + k;
                 A.flagrow[i] = left ? -1 : 4 * B.row;
                 if (polish) A.errbuf[i] = err;
             }
-            break;
+            if (polish) break;
         }
         if (polish) put_row_sums(A, B, B.row, u.zr, u.zi, err);
-        z3 = z2;
-        z2 = z1;
-        z1 = make_double2(u.zr, u.zi);
+        if (left) goes_on = false;
+        if (mine && !left) {
+            root_row += B.dir;
+            z3 = z2;
+            z2 = z1;
+            z1 = make_double2(u.zr, u.zi);
+        }
     }
+    if (valid && !polish) A.root_row[base_f + k] = root_row;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
         t_steps += __shfl_xor(t_steps, off, 64);
@@ -1716,7 +1740,7 @@ expand_rows(RoundArgs<typename StarRec<EQUAL>::T> A)
         t_near += __shfl_xor(t_near, off, 64);
     }
     if (B.lane == 0) {
-        A.next_row[B.vslot] = B.row;
+        A.next_row[B.vslot] = is_stuck ? stuck_row : polish ? B.row : B.end_row + B.dir;
         A.stuck[B.vslot] = is_stuck;
         unsigned long long *s = A.fmm_tally + (blockIdx.x % FMM_STRIPES) * FMM_STRIPE_U64 + FMM_T_EXP;
         if (t_steps) atomicAdd(&s[EXP_STEPS_DONE], t_steps);
@@ -3545,6 +3569,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
     MLCC_TRY(c->iter[0].reserve((size_t)it_total * sizeof(double2)));
     MLCC_TRY(c->iter[1].reserve((size_t)it_total * sizeof(double2)));
     MLCC_TRY(c->flagrow.reserve((size_t)it_total * sizeof(int32_t)));
+    MLCC_TRY(c->root_row.reserve((size_t)it_total * sizeof(int32_t)));
     MLCC_TRY(c->fronts.reserve((size_t)(F + 1) * sizeof(Front)));
     MLCC_TRY(c->counts.reserve((size_t)F * sizeof(int32_t)));
     MLCC_TRY(c->passupd.reserve((size_t)F * sizeof(int32_t)));
@@ -3640,6 +3665,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         A.bmap = c->bmap.as<int2>();
         A.fronts = c->fronts.as<Front>();
         A.flagrow = c->flagrow.as<int32_t>();
+        A.root_row = c->root_row.as<int32_t>();
         A.cur = cur;
         A.nxt = nxt;
         A.unit = c->etab.as<double2>();
@@ -3960,7 +3986,8 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         hipLaunchKernelGGL(expand_begin, dim3(1), dim3(1), 0, rs, dctl, dq);
         auto go = [&](auto &A, auto eq, auto fm) {
             constexpr bool E = decltype(eq)::value, M = decltype(fm)::value;
-            hipLaunchKernelGGL((expand_rows<E, M>), grid, dim3(64), 0, rs, A);
+            if (mixed) hipLaunchKernelGGL((expand_rows<E, M, true>), grid, dim3(64), 0, rs, A);
+            else hipLaunchKernelGGL((expand_rows<E, M, false>), grid, dim3(64), 0, rs, A);
         };
         using T_ = std::true_type;
         using F_ = std::false_type;

@@ -190,6 +190,7 @@ struct Ctx {
     // root-finder workspace
     DevBuf iter[2];   // double2[F * n_r]: Jacobi iterates, ping-pong
     DevBuf flagrow;   // int32[F * n_r]: row at which the root was flagged
+    DevBuf root_row;  // int32[F * n_r]: expansions: the root's next row
     DevBuf fronts;    // Front[F]
     DevBuf counts;    // int32[F]: unflagged roots after the last sweep
     DevBuf passupd;   // int32[F]: roots updated by the last round's pass
