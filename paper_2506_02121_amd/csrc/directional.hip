@@ -228,8 +228,10 @@ distance_histogram(int64_t count, const double *__restrict__ dist,
     __syncthreads();
     // Each wave takes HIST_PX runs of 64 consecutive pixels per round and
     // issues all their loads before it counts the first.  Neighbouring
-    // pixels mostly fall in few bins: the lanes of a wave that share a bin
-    // add their count once, through the lowest of them.
+    // pixels often share a bin: the first lane of each run of equal bins adds
+    // the run's length.  (One round per distinct bin of the wave instead, all
+    // its lanes added at once, is a serial chain: 47.5 us against 26.7 for 2048^2
+    // pixels and 100 bins; the loads alone take ~13.)
     const int lane = threadIdx.x & 63;
     constexpr int PX = HIST_PX;
     const int wave = threadIdx.x >> 6;
@@ -252,14 +254,11 @@ distance_histogram(int64_t count, const double *__restrict__ dist,
                              cv[u] < n_classes)
                                 ? cv[u] * (n_bins + 1) + (x < (double)n_bins ? (int)floor(x) : n_bins)
                                 : -1;
-            unsigned long long left = __ballot(bin >= 0);
-            while (left) {
-                const int leader = __builtin_ctzll(left);
-                const int b = __builtin_amdgcn_readlane(bin, leader);
-                const unsigned long long same = __ballot(bin == b) & left;
-                if (lane == leader) atomicAdd(&local[b], (uint32_t)__popcll(same));
-                left &= ~same;
-            }
+            const int before = __shfl_up(bin, 1, 64);
+            const unsigned long long heads = __ballot(lane == 0 || bin != before);
+            const unsigned long long later = (heads >> lane) >> 1;
+            const int run = later ? __builtin_ctzll(later) + 1 : 64 - lane;
+            if (((heads >> lane) & 1) && bin >= 0) atomicAdd(&local[bin], (uint32_t)run);
         }
     }
     __syncthreads();
