@@ -699,7 +699,7 @@ fmm_p2l(int32_t G, int32_t p, int32_t stride, double x0, double y0, double w, in
 // cell and the powers through LDS, 8.0 with this (4.0 with the stars split too,
 // but then the columns came out numbered otherwise); 96 fields of 50 to 600
 // stars, 96 launches there and one here: 1.95 -> 0.65 ms; N = 3,000 (5,200
-// cells): 1.4 there, ~2.4 here.
+// cells): 1.4 there, 2.4 here by its cost per star.
 struct P2lJob {
     int32_t field, cell0, k0, n;   // n: the field's stars
 };
