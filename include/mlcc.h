@@ -57,7 +57,10 @@ typedef enum {
                       directly; used only where the terms left out stay below the sums'
                       rounding), with the correction -F''/(2 F') that 2 S1 - R equals at a
                       root, as long as |F F''/(2 F'^2)| < 0.05; every other root takes Aberth
-                      steps with the root-root sum */
+                      steps with the root-root sum.  A row with roots from expansions
+                      counts once its row identities hold (sum r and sum r^2, which a root
+                      found twice and one missed would shift); else all its roots take
+                      Aberth steps */
     MLCC_MIXED = 1,/* Aberth sweeps in FP32 (FP64 star distances, FP32 sums per tile of
                       64 stars carried in FP64), every root finished by FP64 Newton
                       polish passes that accept a root on the same cutoffs as the
@@ -255,7 +258,9 @@ typedef struct {
     int64_t polish_updates;  /* FP64 Newton polish updates (MLCC_MIXED) */
     int64_t unconverged;     /* roots still unflagged in rows that hit a cap */
     int64_t rows_capped;     /* rows that hit an iteration cap */
-    int64_t rows_fallback;   /* rows that fell back to FP64 Aberth sweeps (MLCC_MIXED) */
+    int64_t rows_fallback;   /* rows that fell back to FP64 Aberth sweeps of every root: unsettled
+                                by the polish (MLCC_MIXED), or expanded with row identities
+                                that did not hold */
     int32_t n_subchains;     /* S used: the first piece's centre row is m / (2 S) */
     int32_t max_row_sweeps;  /* most passes (of any kind) any warm row needed */
     int32_t cold_sweeps;     /* most passes any cold start needed */

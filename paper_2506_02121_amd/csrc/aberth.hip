@@ -919,6 +919,7 @@ template <class T> struct BlockCtx {
     bool fast;       // root-root terms in FP32 (fast_roots_pass)
     bool fresh;      // first pass over the row (roots flagged by then: expand_rows)
     bool has_bnd;    // the front's end row is a duplicate boundary row
+    bool settled;    // its row is finished already (Front::settled)
     int32_t *count, *upd;   // the pass's totals: roots left open (or moving), updates made
     int64_t base_f, out_off, bnd_row_off;
     const T *stars;
@@ -957,6 +958,7 @@ __device__ __forceinline__ void enter_fq(const RoundArgs<T> &A, const Front *F, 
     B.fast = fast_roots_pass(*F, *R);
     B.fresh = F->fresh != 0;
     B.has_bnd = F->bnd_slot >= 0;
+    B.settled = F->settled != 0;
     B.count = count;
     B.upd = upd;
     B.hist = F->hist;
@@ -1586,9 +1588,10 @@ expand_rows(RoundArgs<typename StarRec<EQUAL>::T> A)
     enter_fq(A, F, fq.x, fq.y, (int32_t *)nullptr, (int32_t *)nullptr, B);
     constexpr bool polish = POLISH;
     const int front_row = F->row;
+    if (B.settled) B.row += B.dir;   // the passes finished this one
     if (!F->redo) {   // on from where the block stopped, or past the row passes finished since
         const int next = A.next_row[B.vslot];
-        if ((next - front_row) * B.dir > 0) B.row = next;
+        if ((next - B.row) * B.dir > 0) B.row = next;
     }
     const int k = B.k, n_r = B.n_r;
     const int hist0 = B.hist - front_row * B.dir;   // finished rows behind row j: hist0 + j dir
@@ -2345,6 +2348,8 @@ __device__ __forceinline__ void start_row(Front &fr, int predictor, int xfrom)
     fr.reseed = 0;
     fr.stamp = 4 * fr.row;
     fr.fresh = 1;
+    fr.shared = 0;
+    fr.settled = 0;
     if (fr.mode == PH_F64)
         fr.phase = PH_F64;
     else
@@ -2394,12 +2399,22 @@ __device__ __forceinline__ int row_converged(Front &fr, int f, Front *fronts, in
         return p;
     }
     fr.max_warm = max(fr.max_warm, fr.passes_row);
-    row_done(fr, st, f - f0, predictor, xfrom);
+    if (fr.shared && fr.mode == PH_F64) {   // its identities are checked first (expand_check)
+        fr.settled = 1;
+        fr.state = FRONT_PARKED;
+        if (st) st[f - f0] = fr.state;
+    } else {
+        row_done(fr, st, f - f0, predictor, xfrom);
+    }
     return -1;
 }
 
-// The two row identities of a polished row (see aberth_control) from its
-// row sums rs: sum r and sum r^2, then the error terms.
+// The two row identities of a row (see aberth_control) from its row sums rs:
+// sum r and sum r^2, then the error terms.
+// A sheet -P(z), P = sum_{k=1..n} d_2k z^2k, makes the polynomial
+// (c - P) prod (z - z_i)^2 + ..., where the dots stay 2 n + 2 degrees below the
+// leading term: sum r stays 2 sum z_i, and sum r^2 is 2 sum z_i^2 plus that of
+// the roots of c - P, -2 d_2(n-1) / d_2n, or 2 c / d_2 for n = 1.
 __device__ __forceinline__ bool row_identities_hold(const Real &R, double2 u, const double4 *rs)
 {
     const int bpf = (R.n_r + 63) / 64;
@@ -2408,7 +2423,10 @@ __device__ __forceinline__ bool row_identities_hold(const Real &R, double2 u, co
     const double se = q.x, se2 = q.y, sa = q.z, sa2 = q.w;
     const double cr = R.gamma - R.a * u.x, ci = -R.a * u.y;   // c(phi)
     const double cc = cr * cr + ci * ci;
-    const double mcr = R.M * cr / cc, mci = -R.M * ci / cc;   // M / c
+    // M / c, or what takes its place with a sheet
+    const bool sheet = R.n_poly > 0;
+    const double mcr = sheet ? fma(R.sheet_mc, cr, R.sheet_m) : R.M * cr / cc;
+    const double mci = sheet ? R.sheet_mc * ci : -R.M * ci / cc;
     const double e1r = a1r - 2.0 * R.sz_r, e1i = a1i - 2.0 * R.sz_i;
     const double e2r = a2r - (2.0 * R.sz2_r - 2.0 * mcr);
     const double e2i = a2i - (2.0 * R.sz2_i - 2.0 * mci);
@@ -2716,13 +2734,105 @@ __global__ void expand_begin(Control *__restrict__ ctl, PQueue *q)
     }
 }
 
+// FP64 rows with roots from expansions, each accepted by itself: nothing kept
+// two chains from ending at one root, as the root-root sum of an Aberth step
+// does, so a row counts once its identities hold.  For every parked front in
+// FP64, the work groups of grid row blockIdx.x take in turn the rows which all
+// its blocks have settled, read their roots back and leave in bad[f] the first
+// row, counted from the front's own, whose identities fail.  The error of a root
+// is allowed EXP_ERR, which acceptance bounds, and what the rounding of F leaves,
+// 4 u (|gamma| + |1 - kappa_s|) / |F'| with F' = -2 M / d^3 of all stars at their
+// centre, d away: roots far outside the stars are moved most by it.  The sums of
+// those errors, and sum |r|, are bounded through sums of even powers (Cauchy's
+// inequality), so that no root takes a square root.
+// Bound by the latency of a row: a few reads a lane, then the reduction.  One
+// work group of four waves a row and eight separate reductions took 163 us a
+// launch for 86 fields of 1,088 steps; a wave a row and one reduction in halves
+// take 70 (2.8 and 1.2 ms a call; N = 6,000, 1.9 GB of roots: 0.9 ms).
+__global__ void __launch_bounds__(CONTROL_THREADS)
+expand_check(const Front *__restrict__ fronts, const Real *__restrict__ reals,
+             const double2 *__restrict__ unit, const int32_t *__restrict__ next_row,
+             const double *__restrict__ out_re, const double *__restrict__ out_im,
+             const double2 *__restrict__ bnd, int32_t *__restrict__ bad)
+{
+    constexpr int NV = 8;
+    __shared__ double part[CONTROL_THREADS / 64][NV];
+    const Front *F = fronts + blockIdx.x;
+    if (F->state != FRONT_PARKED || F->phase != PH_F64) return;
+    const Real &R = reals[F->real];
+    const int n_r = R.n_r, bpf = (n_r + 63) >> 6, dir = F->dir, row0 = F->row;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    int h = 0x7fffffff;   // rows settled by every block
+    for (int b = lane; b < bpf; b += 64) h = min(h, (next_row[F->blk0 + b] - row0) * dir);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) h = min(h, __shfl_xor(h, off, 64));
+    const double cx = R.sz_r / R.n_stars, cy = R.sz_i / R.n_stars;
+    const double far = 2.0 * 1.1102230246251565e-16 * (fabs(R.gamma) + R.a1) / R.M;
+    for (int i = blockIdx.y; i < h; i += gridDim.y) {
+        const int row = row0 + i * dir;
+        const bool boundary = F->bnd_slot >= 0 && row == F->end_row;
+        const int64_t o = R.out_off + (int64_t)row * n_r;
+        const double2 *br = bnd + R.bnd_off + (int64_t)max(F->bnd_slot, 0) * n_r;
+        // sum r, sum r^2, sum |r|^2, and sum d^2, d^4, d^6
+        double v[NV] = {};
+#pragma unroll 4
+        for (int k = threadIdx.x; k < n_r; k += blockDim.x) {
+            const double2 z = boundary ? br[k] : make_double2(out_re[o + k], out_im[o + k]);
+            const double dx = z.x - cx, dy = z.y - cy, d2 = fma(dx, dx, dy * dy);
+            v[0] += z.x;
+            v[1] += z.y;
+            v[2] += z.x * z.x - z.y * z.y;
+            v[3] += 2.0 * z.x * z.y;
+            v[4] += fma(z.x, z.x, z.y * z.y);
+            v[5] += d2;
+            v[6] += d2 * d2;
+            v[7] += d2 * d2 * d2;
+        }
+        // a lane hands half of its values over at each of three levels, so that
+        // the lanes of an eighth of the wave come to hold one of them
+#pragma unroll
+        for (int half = NV / 2; half >= 1; half >>= 1) {
+            const bool up = lane & (8 * half);
+#pragma unroll
+            for (int j = 0; j < half; ++j) {
+                const double give = up ? v[j] : v[j + half], keep = up ? v[j + half] : v[j];
+                v[j] = keep + __shfl_xor(give, 8 * half, 64);
+            }
+        }
+        double w = v[0];   // value lane / 8
+#pragma unroll
+        for (int off = 4; off >= 1; off >>= 1) w += __shfl_xor(w, off, 64);
+        if ((lane & 7) == 0) part[wave][lane >> 3] = w;
+        if (waves > 1) __syncthreads();
+        else wave_sync();
+        if (threadIdx.x == 0) {
+            double s[NV];
+#pragma unroll
+            for (int q = 0; q < NV; ++q) {
+                s[q] = part[0][q];
+                for (int x = 1; x < waves; ++x) s[q] += part[x][q];
+            }
+            const double e2 = 2.0 * (n_r * EXP_ERR * EXP_ERR + far * far * s[7]);   // sum err^2
+            const double4 rs[2] = {
+                make_double4(s[0], s[1], s[2], s[3]),
+                make_double4(n_r * EXP_ERR + far * sqrt(s[5] * s[6]), 2.0 * sqrt(e2 * s[4]) + e2,
+                             sqrt(n_r * s[4]), s[4])};
+            if (!row_identities_hold(R, unit[row], rs)) atomicMin(&bad[blockIdx.x], i);
+        }
+        if (waves > 1) __syncthreads();
+        else wave_sync();
+    }
+}
+
 // After the expansions, one work group per parked front: the front moves past the
-// rows all its blocks have settled (in the mixed form while their row
-// identities hold).  If a block is stuck at the row it comes to, the front is
-// active again: the row's first pass steps the roots left open, from their
-// extrapolation, the others entering at the previous row's roots.  If a row's
-// identities fail it goes the way of a polish that does, and what blocks ahead
-// of it found is done anew.  Otherwise the front stays parked, or is done.
+// rows all its blocks have settled, while their row identities hold.  If a
+// block is stuck at the row it comes to, the front is active again: the row's
+// first pass steps the roots left open, from their extrapolation, the others
+// entering at the previous row's roots.  If a row's identities fail, the mixed
+// form goes the way of a polish that does; in FP64 every root of the row takes
+// Aberth steps from its extrapolation, as without expansions, which keep the
+// roots apart.  Either way, what blocks ahead of it found is done anew.
+// Otherwise the front stays parked, or is done.
 // (Each wave checks the identities of one row at a time: the sums of a row are
 // a few dependent loads, and one wave for all rows took 3.4 us a row.)
 constexpr int CHECK_WAVES = 16;
@@ -2732,8 +2842,8 @@ expand_control(Front *__restrict__ fronts, const Real *__restrict__ reals,
                const double2 *__restrict__ unit, const double4 *__restrict__ vieta,
                const int32_t *__restrict__ next_row, const int32_t *__restrict__ stuck,
                int32_t ahead, int32_t nvslots, int32_t predictor, int32_t xfrom,
-               Control *__restrict__ ctl, PQueue *q, int2 *tasks, unsigned long long *seq,
-               unsigned long long mask)
+               int32_t *__restrict__ bad, Control *__restrict__ ctl, PQueue *q, int2 *tasks,
+               unsigned long long *seq, unsigned long long mask)
 {
     __shared__ int row_ok[CHECK_WAVES];
     const int f = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -2746,7 +2856,8 @@ expand_control(Front *__restrict__ fronts, const Real *__restrict__ reals,
     for (int b = lane; b < bpf; b += 64) h = min(h, (next_row[fr.blk0 + b] - fr.row) * fr.dir);
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) h = min(h, __shfl_xor(h, off, 64));
-    const int row0 = fr.row, dir = fr.dir;
+    const int row0 = fr.row, dir = fr.dir, first_bad = polish ? 0 : bad[f];
+    const int counted = fr.settled;   // its roots are in the tallies
     fr.redo = 0;
     fr.npass += 1;
     bool failed = false;
@@ -2765,8 +2876,10 @@ expand_control(Front *__restrict__ fronts, const Real *__restrict__ reals,
                 __syncthreads();
             }
             failed = !row_ok[c];
-            if (failed) break;
+        } else {
+            failed = moved == first_bad;
         }
+        if (failed) break;
         fr.max_warm = max(fr.max_warm, 1);
         row_done(fr, nullptr, f, predictor, xfrom);
     }
@@ -2778,16 +2891,24 @@ expand_control(Front *__restrict__ fronts, const Real *__restrict__ reals,
     if (fr.state == FRONT_PARKED && (failed || held)) {
         fr.state = FRONT_ACTIVE;
         fr.src = f;
-        fr.passes_row = 1;
-        if (failed) {
+        if (!failed) {
+            fr.shared = 1;
+        } else if (polish) {
             fr.fresh = 0;
             retry_row(fr, ctl, threadIdx.x == 0);
+        } else {
+            start_row(fr, predictor, 0);
+            fr.stamp += 1;
+            fr.redo = 1;
+            if (threadIdx.x == 0) atomicAdd((unsigned long long *)&ctl->rows_fallback, 1ull);
         }
+        fr.passes_row = 1;
     }
     __syncthreads();   // the record is read by every wave before it is written
     if (threadIdx.x == 0) {
         fronts[f] = fr;
-        const unsigned long long up = (unsigned long long)moved * (unsigned)R.n_r;
+        if (!polish) bad[f] = 0x7fffffff;   // for the next time
+        const unsigned long long up = (unsigned long long)max(moved - counted, 0) * (unsigned)R.n_r;
         if (up) atomicAdd(&ctl->upd[polish ? TALLY_ROOTS + 1 : TALLY_ROOTS], up);
         if (fr.state == FRONT_ACTIVE) atomicAdd(&ctl->active_fronts, 1);
         if (fr.state == FRONT_PARKED) atomicAdd(&ctl->parked_fronts, 1);
@@ -2799,9 +2920,9 @@ expand_control(Front *__restrict__ fronts, const Real *__restrict__ reals,
 }
 
 // Iterates of the fronts expand_control made active: the previous row's roots
-// for a row's first pass, the row's own for one that is retried; roots of
-// blocks that had settled the row are flagged (the stuck ones' flags are in
-// place).  Counts the accepted roots.
+// for a row's first pass, the row's own for one that is retried; where the row
+// keeps the roots its blocks found, those of blocks that had settled it are
+// flagged (the stuck ones' flags are in place).  Counts the accepted roots.
 __global__ void __launch_bounds__(64)
 expand_gather(const Front *__restrict__ fronts, const Real *__restrict__ reals,
               const int2 *__restrict__ bmap, const int32_t *__restrict__ next_row,
@@ -2824,7 +2945,9 @@ expand_gather(const Front *__restrict__ fronts, const Real *__restrict__ reals,
         const bool b = F->bnd_slot >= 0 && row == F->end_row;
         (F->par ? iter1 : iter0)[i] =
             b ? bnd[R->bnd_off + (int64_t)F->bnd_slot * R->n_r + k] : make_double2(out_re[o], out_im[o]);
-        if (next_row[F->blk0 + fq.y] != F->row) {
+        if (!F->shared) {
+            flagged = false;
+        } else if (next_row[F->blk0 + fq.y] != F->row) {
             flagrow[i] = F->stamp;
             if (errbuf) errbuf[i] = 0.0;
             flagged = true;
@@ -2833,7 +2956,7 @@ expand_gather(const Front *__restrict__ fronts, const Real *__restrict__ reals,
         }
     }
     const unsigned long long n = __popcll(__ballot(flagged));
-    if (threadIdx.x == 0 && n && !(F->tried & TRIED_POLISH))
+    if (threadIdx.x == 0 && n)
         atomicAdd(&ctl->upd[F->phase == PH_F64 ? TALLY_ROOTS : TALLY_ROOTS + 1], n);
 }
 
@@ -3494,6 +3617,9 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         R.tol1 = 8.0 * u_ro * h.sum_abs_z;
         R.tol2 = 16.0 * u_ro * h.sum_abs_z2;
         R.root32 = p->precision == MLCC_FP64_R32 ? 1 : 0;
+        R.sheet_m = R.sheet_mc = 0.0;   // sum r^2 = 2 sum z_i^2 - 2 (sheet_m + sheet_mc c)
+        if (sp.n > 1) R.sheet_m = sp.d[sp.n - 2] / sp.d[sp.n - 1];
+        if (sp.n == 1) R.sheet_mc = -1.0 / sp.d[0];
         R.restart = p->cold_restart_sweeps > 0 ? p->cold_restart_sweeps : STALL_START;
         const int bpf = (int)ceil_div(n_r, 64);
         for (int s = 0; s < NP; ++s) {
@@ -3584,6 +3710,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
                                                                                    (64 * nblocks)))
                           : 1;
     MLCC_TRY(c->next_row.reserve((size_t)2 * nblocks * sizeof(int32_t)));
+    MLCC_TRY(c->bad_row.reserve((size_t)F * sizeof(int32_t)));
     if (mixed) {
         MLCC_TRY(c->vieta.reserve((size_t)2 * ahead * nblocks * sizeof(double4)));
         MLCC_TRY(c->errbuf.reserve((size_t)it_total * sizeof(double)));
@@ -3634,6 +3761,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
     MLCC_HIP(hipMemsetAsync(c->fmm_tally.p, 0,
                             (size_t)FMM_STRIPES * FMM_STRIPE_U64 * sizeof(uint64_t), c->stream));
     MLCC_HIP(hipMemsetAsync(c->passupd.p, 0, F * sizeof(int32_t), c->stream));
+    MLCC_HIP(hipMemsetAsync(c->bad_row.p, 0x7f, F * sizeof(int32_t), c->stream));
     const int32_t near_seeds = p->n_subchains <= 0 && p->predictor > 0;
     if (equal)
         hipLaunchKernelGGL(seed_centres<double2>, dim3((unsigned)ngrid), dim3(64), 0, c->stream,
@@ -3980,6 +4108,11 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         return MLCC_OK;
     };
 
+    // expand_check: a wave a row while a lane then has few reads, else a work group
+    // of four; as many as are resident at once
+    const unsigned check_threads = max_nr > 4096 ? CONTROL_THREADS : 64;
+    const unsigned check_groups = (unsigned)std::max<int64_t>(
+        1, std::min<int64_t>(L / 2 + 1, (int64_t)(8192 * 64 / check_threads) / F));
     // The expansions over every parked front, and what comes of them: fronts
     // that passes take over, and fronts still parked.
     auto run_expansions = [&](int &active, int &parked) -> mlcc_status {
@@ -3998,11 +4131,17 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
             fill(A4, stars4, c->iter[0].as<double2>(), c->iter[1].as<double2>());
             if (fmm_on) go(A4, F_{}, T_{}); else go(A4, F_{}, F_{});
         }
+        if (!mixed)
+            hipLaunchKernelGGL(expand_check, dim3((unsigned)F, check_groups), dim3(check_threads), 0,
+                               rs, c->fronts.as<Front>(), c->reals_d.as<Real>(),
+                               c->etab.as<double2>(), c->next_row.as<int32_t>(), roots_re, roots_im,
+                               c->bnd.as<double2>(), c->bad_row.as<int32_t>());
         hipLaunchKernelGGL(expand_control, dim3((unsigned)F), dim3(64 * CHECK_WAVES), 0, rs,
                            c->fronts.as<Front>(), c->reals_d.as<Real>(), c->etab.as<double2>(),
                            c->vieta.as<double4>(), c->next_row.as<int32_t>(),
                            c->next_row.as<int32_t>() + nblocks, ahead, (int32_t)nblocks,
-                           p->predictor, xfrom, dctl, dq, dtasks, dseq, qmask);
+                           p->predictor, xfrom, c->bad_row.as<int32_t>(), dctl, dq, dtasks, dseq,
+                           qmask);
         hipLaunchKernelGGL(expand_gather, grid, dim3(64), 0, rs, c->fronts.as<Front>(),
                            c->reals_d.as<Real>(), c->bmap.as<int2>(), c->next_row.as<int32_t>(),
                            roots_re, roots_im, c->bnd.as<double2>(), c->iter[0].as<double2>(),

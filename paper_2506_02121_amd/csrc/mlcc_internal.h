@@ -76,6 +76,8 @@ struct Front {
     int32_t par;      // persistent scheduler: which iterate buffer holds the current values
     int32_t npass;    // passes run by this front (all rows)
     int32_t redo;     // 1: blocks ahead of its row start over from it (expand_rows)
+    int32_t shared;   // 1: roots of its row come from expansions, others from passes
+    int32_t settled;  // FP64, parked: its row is finished and waits for the row identities
     int32_t seedvar;  // cold start: 0 = the seeds z_i +- 1; 1 = the second set (after a stall)
     int64_t it_off;   // first element of its roots in the iterate and flag arrays
 };
@@ -101,6 +103,7 @@ struct Real {
     int32_t restart;    // FP64 sweeps after which an unsettled cold start begins again
     int32_t chunk;      // persistent schedule: blocks of a front per task
     double sheet_c;     // |c| of a rectangular sheet
+    double sheet_m, sheet_mc;   // its terms of sum r^2 (row identities)
     int64_t sheet_off;  // its record in the sheet array: d_2..d_{t-1} (n_poly), the lens-map
                         // terms d_2k / (2k + 1) (n_poly), start values of the extra roots
                         // (2 n_extra: re, im)
@@ -196,6 +199,7 @@ struct Ctx {
     DevBuf passupd;   // int32[F]: roots updated by the last round's pass
     DevBuf next_row;  // int32[2 * blocks]: expansions: each block's next row, and whether it is
                       // stuck there
+    DevBuf bad_row;   // int32[F]: expansions: first settled row whose identities fail
     DevBuf control;   // Control
     DevBuf fmm_tally; // uint64[FMM_STRIPES * FMM_STRIPE_U64]: multipole tallies
     DevBuf etab;      // double2[m + 1]: (1 - kappa_s) e^{-i phi_j}
