@@ -456,13 +456,6 @@ constexpr int STALL_START = 100;
 // Newton steps a root may take within one polish pass.
 constexpr int POLISH_STEPS = 3;
 
-// Rows by which the blocks of a front of the mixed form may be ahead of its row
-// in expand_rows: their row sums wait there for the slowest block.
-#ifndef MLCC_AHEAD
-#define MLCC_AHEAD 1024
-#endif
-constexpr int AHEAD = MLCC_AHEAD;
-
 // Resident waves per SIMD the expansion kernel is compiled for: its 28 moment
 // sums and the terms of four stars need more than the 168 registers of three.
 #ifndef MLCC_EXPAND_WAVES
@@ -898,12 +891,8 @@ template <class T> struct RoundArgs {
     double2 *iter0, *iter1;
     const double *sheet; // rectangular fields' sheet records (Real::sheet_off)
     const FmmArgs *fmm;  // fast multipole star sums: one record per field (kernels built with them)
-    // expand_rows: per block its next row and whether it is stuck there, the
-    // rows a block may be ahead of its front (row sums go to slot row mod
-    // ahead), and the stride of the row-sum slots (the launch's block count)
-    int32_t *next_row, *stuck;
-    int32_t *root_row;   // FP64: per root its own next row
-    int32_t ahead, nvslots;
+    int32_t *next_row, *stuck;   // expand_rows: per block its next row, and whether it is stuck there
+    int32_t *root_row;           // FP64: per root its own next row
 };
 
 // What one block knows about its front and star field.
@@ -1515,11 +1504,11 @@ __device__ __forceinline__ double moments_reach2(const Moments &S)
     return r2 > 0.0 ? r2 : 0.0;   // also an expansion that is not finite
 }
 
-// A block's share of a row's sums sum r and sum r^2 (row identities), and of
-// what bounds their error: the roots' own estimated errors, and sum |r|,
-// sum |r|^2 for the rounding of the sums.
+// A block's share of its polished row's sums sum r and sum r^2 (row
+// identities), and of what bounds their error: the roots' own estimated errors,
+// and sum |r|, sum |r|^2 for the rounding of the sums.
 template <class T>
-__device__ __forceinline__ void put_row_sums(const RoundArgs<T> &A, const BlockCtx<T> &B, int row,
+__device__ __forceinline__ void put_row_sums(const RoundArgs<T> &A, const BlockCtx<T> &B,
                                              double zr, double zi, double er)
 {
     const bool valid = B.valid;
@@ -1531,9 +1520,8 @@ __device__ __forceinline__ void put_row_sums(const RoundArgs<T> &A, const BlockC
     wave_sum(s1r); wave_sum(s1i); wave_sum(s2r); wave_sum(s2i);
     wave_sum(t_e); wave_sum(t_e2); wave_sum(t_a); wave_sum(t_a2);
     if (B.lane == 0) {
-        const int64_t sl = 2 * ((int64_t)(row % A.ahead) * A.nvslots + B.vslot);
-        A.vieta[sl] = make_double4(s1r, s1i, s2r, s2i);
-        A.vieta[sl + 1] = make_double4(t_e, t_e2, t_a, t_a2);
+        A.vieta[2 * B.vslot] = make_double4(s1r, s1i, s2r, s2i);
+        A.vieta[2 * B.vslot + 1] = make_double4(t_e, t_e2, t_a, t_a2);
     }
 }
 
@@ -1552,8 +1540,7 @@ enum { EXP_NEAR = 0, EXP_STEPS_DONE = 1, EXP_FORMED = 2, EXP_STARS = 3 };
 // stored, and the row's passes step the others once every other block has come
 // to it (expand_control).  In FP64 only the roots left open wait; the others go
 // on, each with its own next row, so that what is left to do after the passes
-// is one root's rows and not a block's.  In the mixed form the block waits, as
-// a row's sums are taken over all its roots at once.
+// is one root's rows and not a block's.  In the mixed form the block waits.
 //
 // A kernel of its own at two waves per SIMD, so that the moments stay in
 // registers.  Whole calls, with one sum over the stars per row and with this:
@@ -1597,7 +1584,7 @@ expand_rows(RoundArgs<typename StarRec<EQUAL>::T> A)
     const int hist0 = B.hist - front_row * B.dir;   // finished rows behind row j: hist0 + j dir
     const int64_t base_f = B.base_f;
     const bool valid = B.valid;
-    // FP64: the root's own next row; the mixed form's row sums need the block in step
+    // FP64: the root's own next row; blocks of the mixed form stay in step
     int root_row = B.row;
     if (valid && !polish && !F->redo) {
         const int next = A.root_row[base_f + k];
@@ -1612,8 +1599,6 @@ expand_rows(RoundArgs<typename StarRec<EQUAL>::T> A)
     unsigned long long t_steps = 0, t_exp = 0, t_near = 0;   // per lane
     bool is_stuck = false;
     for (; (B.row - B.end_row) * B.dir <= 0; B.row += B.dir) {
-        // row sums of the mixed form wait for the front's slowest block
-        if (polish && (B.row - front_row) * B.dir >= A.ahead) break;
         if (!__ballot(goes_on && (root_row - B.end_row) * B.dir <= 0)) break;
         const bool mine = goes_on && root_row == B.row;
         if (mine && !loaded) {
@@ -1726,7 +1711,6 @@ expand_rows(RoundArgs<typename StarRec<EQUAL>::T> A)
             }
             if (polish) break;
         }
-        if (polish) put_row_sums(A, B, B.row, u.zr, u.zi, err);
         if (left) goes_on = false;
         if (mine && !left) {
             root_row += B.dir;
@@ -2218,7 +2202,7 @@ __device__ __forceinline__ void polish_pass(const RoundArgs<typename StarRec<EQU
         tl.far_n = (unsigned long long)n_upd * (unsigned long long)B.n_stars;
         fmm_flush(A.fmm_tally, FMM_T_POLISH, tl);
     }
-    put_row_sums(A, B, B.row, zr, zi, er);
+    put_row_sums(A, B, zr, zi, er);
 }
 
 template <bool EQUAL, bool FMM>
@@ -2287,14 +2271,12 @@ __global__ void seed_centres(const T *__restrict__ stars, const Real *__restrict
 // a butterfly), so the control kernel reads eight numbers per front.
 __global__ void __launch_bounds__(64)
 row_sums(const Front *__restrict__ fronts, const Real *__restrict__ reals,
-         const double4 *__restrict__ vieta, double4 *__restrict__ vsum,
-         int32_t ahead, int32_t nvslots)
+         const double4 *__restrict__ vieta, double4 *__restrict__ vsum)
 {
     const int f = blockIdx.x;
     const Front *F = fronts + f;
     if (F->state != FRONT_ACTIVE || F->phase != PH_POLISH) return;
     const int bpf = (reals[F->real].n_r + 63) / 64;
-    vieta += 2 * (int64_t)(F->row % ahead) * nvslots;
     double v0 = 0, v1 = 0, v2 = 0, v3 = 0, v4 = 0, v5 = 0, v6 = 0, v7 = 0;
     for (int b = threadIdx.x; b < bpf; b += 64) {
         const double4 t = vieta[2 * (F->blk0 + b)], q = vieta[2 * (F->blk0 + b) + 1];
@@ -2734,10 +2716,9 @@ __global__ void expand_begin(Control *__restrict__ ctl, PQueue *q)
     }
 }
 
-// FP64 rows with roots from expansions, each accepted by itself: nothing kept
-// two chains from ending at one root, as the root-root sum of an Aberth step
-// does, so a row counts once its identities hold.  For every parked front in
-// FP64, the work groups of grid row blockIdx.x take in turn the rows which all
+// Rows with roots from expansions, each accepted by itself: nothing kept two
+// chains from ending at one root, as the root-root sum of an Aberth step does, so
+// a row counts once its identities hold.  For every parked front, the work groups of grid row blockIdx.x take in turn the rows which all
 // its blocks have settled, read their roots back and leave in bad[f] the first
 // row, counted from the front's own, whose identities fail.  The error of a root
 // is allowed EXP_ERR, which acceptance bounds, and what the rounding of F leaves,
@@ -2748,7 +2729,11 @@ __global__ void expand_begin(Control *__restrict__ ctl, PQueue *q)
 // Bound by the latency of a row: a few reads a lane, then the reduction.  One
 // work group of four waves a row and eight separate reductions took 163 us a
 // launch for 86 fields of 1,088 steps; a wave a row and one reduction in halves
-// take 70 (2.8 and 1.2 ms a call; N = 6,000, 1.9 GB of roots: 0.9 ms).
+// take 70 (2.8 and 1.2 ms a call; N = 6,000, 1.9 GB of roots: 0.9 ms).  In the mixed
+// form it takes the place of row sums formed in the expansion kernel, which held
+// a block to 1,024 rows ahead of its front and took up to 512 MiB, and of their
+// check one row at a time: N = 10,000 with multipole sums 52.0 -> 44.9 ms, of which
+// 1.4 here for 6.4 GB.
 __global__ void __launch_bounds__(CONTROL_THREADS)
 expand_check(const Front *__restrict__ fronts, const Real *__restrict__ reals,
              const double2 *__restrict__ unit, const int32_t *__restrict__ next_row,
@@ -2758,7 +2743,7 @@ expand_check(const Front *__restrict__ fronts, const Real *__restrict__ reals,
     constexpr int NV = 8;
     __shared__ double part[CONTROL_THREADS / 64][NV];
     const Front *F = fronts + blockIdx.x;
-    if (F->state != FRONT_PARKED || F->phase != PH_F64) return;
+    if (F->state != FRONT_PARKED) return;
     const Real &R = reals[F->real];
     const int n_r = R.n_r, bpf = (n_r + 63) >> 6, dir = F->dir, row0 = F->row;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
@@ -2833,21 +2818,15 @@ expand_check(const Front *__restrict__ fronts, const Real *__restrict__ reals,
 // Aberth steps from its extrapolation, as without expansions, which keep the
 // roots apart.  Either way, what blocks ahead of it found is done anew.
 // Otherwise the front stays parked, or is done.
-// (Each wave checks the identities of one row at a time: the sums of a row are
-// a few dependent loads, and one wave for all rows took 3.4 us a row.)
-constexpr int CHECK_WAVES = 16;
-
-__global__ void __launch_bounds__(64 * CHECK_WAVES)
+__global__ void __launch_bounds__(64)
 expand_control(Front *__restrict__ fronts, const Real *__restrict__ reals,
-               const double2 *__restrict__ unit, const double4 *__restrict__ vieta,
                const int32_t *__restrict__ next_row, const int32_t *__restrict__ stuck,
-               int32_t ahead, int32_t nvslots, int32_t predictor, int32_t xfrom,
-               int32_t *__restrict__ bad, Control *__restrict__ ctl, PQueue *q, int2 *tasks,
-               unsigned long long *seq, unsigned long long mask)
+               int32_t predictor, int32_t xfrom, int32_t *__restrict__ bad,
+               Control *__restrict__ ctl, PQueue *q, int2 *tasks, unsigned long long *seq,
+               unsigned long long mask)
 {
-    __shared__ int row_ok[CHECK_WAVES];
-    const int f = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    Front fr = fronts[f];   // every thread advances a copy of its own
+    const int f = blockIdx.x, lane = threadIdx.x;
+    Front fr = fronts[f];   // every lane advances a copy of its own
     if (fr.state != FRONT_PARKED) return;
     const Real &R = reals[fr.real];
     const int bpf = (R.n_r + 63) >> 6;
@@ -2856,31 +2835,16 @@ expand_control(Front *__restrict__ fronts, const Real *__restrict__ reals,
     for (int b = lane; b < bpf; b += 64) h = min(h, (next_row[fr.blk0 + b] - fr.row) * fr.dir);
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) h = min(h, __shfl_xor(h, off, 64));
-    const int row0 = fr.row, dir = fr.dir, first_bad = polish ? 0 : bad[f];
+    const int row0 = fr.row, dir = fr.dir;
     const int counted = fr.settled;   // its roots are in the tallies
+    const int moved = min(h, bad[f]);
+    const bool failed = moved < h;
     fr.redo = 0;
     fr.npass += 1;
-    bool failed = false;
-    int moved = 0;
-    for (; moved < h; ++moved) {
-        if (polish) {
-            const int c = moved % CHECK_WAVES;
-            if (c == 0) {   // the next rows, one a wave
-                const int row = fr.row + wave * dir;
-                __syncthreads();
-                if (moved + wave < h) {
-                    double4 rs[2];
-                    sum_row(vieta + 2 * ((int64_t)(row % ahead) * nvslots + fr.blk0), bpf, rs);
-                    if (lane == 0) row_ok[wave] = row_identities_hold(R, unit[row], rs);
-                }
-                __syncthreads();
-            }
-            failed = !row_ok[c];
-        } else {
-            failed = moved == first_bad;
-        }
-        if (failed) break;
+    if (moved > 0) {   // the last of them is done
         fr.max_warm = max(fr.max_warm, 1);
+        fr.row += (moved - 1) * dir;
+        fr.hist = min(fr.hist + moved - 1, 3);
         row_done(fr, nullptr, f, predictor, xfrom);
     }
     bool any = false;
@@ -2895,25 +2859,24 @@ expand_control(Front *__restrict__ fronts, const Real *__restrict__ reals,
             fr.shared = 1;
         } else if (polish) {
             fr.fresh = 0;
-            retry_row(fr, ctl, threadIdx.x == 0);
+            retry_row(fr, ctl, lane == 0);
         } else {
             start_row(fr, predictor, 0);
             fr.stamp += 1;
             fr.redo = 1;
-            if (threadIdx.x == 0) atomicAdd((unsigned long long *)&ctl->rows_fallback, 1ull);
+            if (lane == 0) atomicAdd((unsigned long long *)&ctl->rows_fallback, 1ull);
         }
         fr.passes_row = 1;
     }
-    __syncthreads();   // the record is read by every wave before it is written
-    if (threadIdx.x == 0) {
+    if (lane == 0) {   // every lane has read them
         fronts[f] = fr;
-        if (!polish) bad[f] = 0x7fffffff;   // for the next time
+        bad[f] = 0x7fffffff;   // for the next time
         const unsigned long long up = (unsigned long long)max(moved - counted, 0) * (unsigned)R.n_r;
         if (up) atomicAdd(&ctl->upd[polish ? TALLY_ROOTS + 1 : TALLY_ROOTS], up);
         if (fr.state == FRONT_ACTIVE) atomicAdd(&ctl->active_fronts, 1);
         if (fr.state == FRONT_PARKED) atomicAdd(&ctl->parked_fronts, 1);
     }
-    if (q && wave == 0 && fr.state == FRONT_ACTIVE) {   // persistent schedule: the next launch's work
+    if (q && fr.state == FRONT_ACTIVE) {   // persistent schedule: the next launch's work
         push_front(q, tasks, seq, mask, f, task_count(R));
         if (lane == 0) atomicAdd(&q->target, 1);
     }
@@ -3102,8 +3065,7 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
                 if (last) {
                     double4 rs[2] = {make_double4(0, 0, 0, 0), make_double4(0, 0, 0, 0)};
                     if (ph == PH_POLISH)
-                        sum_row(A.vieta + 2 * ((int64_t)(fr.row % A.ahead) * A.nvslots + fr.blk0),
-                                bpf, rs);
+                        sum_row(A.vieta + 2 * fr.blk0, bpf, rs);
                     int finished = 0;
                     if (lane == 0) {
                         const int dir0 = fr.dir;
@@ -3703,16 +3665,10 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
     MLCC_TRY(c->fmm_tally.reserve((size_t)FMM_STRIPES * FMM_STRIPE_U64 * sizeof(uint64_t)));
     MLCC_TRY(c->etab.reserve((size_t)(m + 1) * sizeof(double2)));
     MLCC_TRY(c->bnd.reserve((size_t)std::max<int64_t>(bnd_total, 1) * sizeof(double2)));
-    // row sums of the rows a block may be ahead of its front (mixed form; fewer
-    // rows where those would pass 512 MiB)
-    const int ahead = mixed && xfrom > 0
-                          ? (int)std::max<int64_t>(1, std::min<int64_t>(AHEAD, ((int64_t)1 << 29) /
-                                                                                   (64 * nblocks)))
-                          : 1;
     MLCC_TRY(c->next_row.reserve((size_t)2 * nblocks * sizeof(int32_t)));
     MLCC_TRY(c->bad_row.reserve((size_t)F * sizeof(int32_t)));
     if (mixed) {
-        MLCC_TRY(c->vieta.reserve((size_t)2 * ahead * nblocks * sizeof(double4)));
+        MLCC_TRY(c->vieta.reserve((size_t)2 * nblocks * sizeof(double4)));
         MLCC_TRY(c->errbuf.reserve((size_t)it_total * sizeof(double)));
     }
     MLCC_TRY(c->vsum.reserve((size_t)2 * F * sizeof(double4)));
@@ -3815,8 +3771,6 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         A.xfrom = xfrom;
         A.next_row = c->next_row.as<int32_t>();
         A.stuck = c->next_row.as<int32_t>() + nblocks;
-        A.ahead = ahead;
-        A.nvslots = (int32_t)nblocks;
         A.persistent = p->schedule == MLCC_SCHEDULE_PERSISTENT;
         A.iter0 = c->iter[0].as<double2>();
         A.iter1 = c->iter[1].as<double2>();
@@ -3907,8 +3861,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
                 if (kind == 2)
                     hipLaunchKernelGGL(row_sums, dim3((unsigned)F), dim3(64), 0, rs,
                                        c->fronts.as<Front>(), c->reals_d.as<Real>(),
-                                       c->vieta.as<double4>(), c->vsum.as<double4>(), ahead,
-                                       (int32_t)nblocks);
+                                       c->vieta.as<double4>(), c->vsum.as<double4>());
             }
             int32_t *wf = c->workflags.as<int32_t>() + slot * MAX_BATCH + i;
             hipLaunchKernelGGL(control_begin, dim3(1), dim3(64), 0, rs, dctl, wf);
@@ -4131,17 +4084,14 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
             fill(A4, stars4, c->iter[0].as<double2>(), c->iter[1].as<double2>());
             if (fmm_on) go(A4, F_{}, T_{}); else go(A4, F_{}, F_{});
         }
-        if (!mixed)
-            hipLaunchKernelGGL(expand_check, dim3((unsigned)F, check_groups), dim3(check_threads), 0,
-                               rs, c->fronts.as<Front>(), c->reals_d.as<Real>(),
-                               c->etab.as<double2>(), c->next_row.as<int32_t>(), roots_re, roots_im,
-                               c->bnd.as<double2>(), c->bad_row.as<int32_t>());
-        hipLaunchKernelGGL(expand_control, dim3((unsigned)F), dim3(64 * CHECK_WAVES), 0, rs,
+        hipLaunchKernelGGL(expand_check, dim3((unsigned)F, check_groups), dim3(check_threads), 0, rs,
                            c->fronts.as<Front>(), c->reals_d.as<Real>(), c->etab.as<double2>(),
-                           c->vieta.as<double4>(), c->next_row.as<int32_t>(),
-                           c->next_row.as<int32_t>() + nblocks, ahead, (int32_t)nblocks,
-                           p->predictor, xfrom, c->bad_row.as<int32_t>(), dctl, dq, dtasks, dseq,
-                           qmask);
+                           c->next_row.as<int32_t>(), roots_re, roots_im, c->bnd.as<double2>(),
+                           c->bad_row.as<int32_t>());
+        hipLaunchKernelGGL(expand_control, dim3((unsigned)F), dim3(64), 0, rs,
+                           c->fronts.as<Front>(), c->reals_d.as<Real>(), c->next_row.as<int32_t>(),
+                           c->next_row.as<int32_t>() + nblocks, p->predictor, xfrom,
+                           c->bad_row.as<int32_t>(), dctl, dq, dtasks, dseq, qmask);
         hipLaunchKernelGGL(expand_gather, grid, dim3(64), 0, rs, c->fronts.as<Front>(),
                            c->reals_d.as<Real>(), c->bmap.as<int2>(), c->next_row.as<int32_t>(),
                            roots_re, roots_im, c->bnd.as<double2>(), c->iter[0].as<double2>(),
