@@ -51,12 +51,13 @@ typedef enum {
                       2^-53 for a correctly rounded division); consecutive star terms,
                       and consecutive root-root terms, are taken in groups of eight that
                       share one refined reciprocal of the product of their eight |d|^2.
-                      With predictor > 0, warm rows are solved from the star
-                      field's Taylor expansion about a point of each root's chain
-                      (14 moments sum m_i u_i^k, every star entering them
-                      directly; used only where the terms left out stay below the sums'
-                      rounding), with the correction -F''/(2 F') that 2 S1 - R equals at a
-                      root, as long as |F F''/(2 F'^2)| < 0.05; every other root takes Aberth
+                      With predictor > 0 and at least 256 phase steps (400 for
+                      MLCC_MIXED), warm rows are solved from the star field's Taylor
+                      expansion about a point of each root's chain (14 moments
+                      sum m_i u_i^k, every star entering them directly; used only where
+                      the terms left out stay below the sums' rounding), with the
+                      correction -F''/(2 F') that 2 S1 - R equals at a root, as long as
+                      |F F''/(2 F'^2)| < 0.05; every other root takes Aberth
                       steps with the root-root sum.  A row with roots from expansions
                       counts once its row identities hold (sum r and sum r^2, which a root
                       found twice and one missed would shift); else all its roots take
@@ -211,7 +212,8 @@ typedef struct {
     int32_t n_subchains;   /* S subchains (Sec. 4.3), each grown from its centre row;
                               must divide m/2.  0 = chosen by the library, which for one
                               field may then grow fewer and longer pieces beside the
-                              first subchain's centre row (predictor > 0) */
+                              first subchain's centre row (where rows come from
+                              expansions) */
     int32_t max_iter_cold; /* sweep cap for a cold-started row (0 = 500) */
     int32_t max_iter_warm; /* sweep cap for a warm-started row (0 = 100) */
     int32_t precision;     /* mlcc_precision */

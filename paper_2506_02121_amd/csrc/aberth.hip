@@ -1220,6 +1220,17 @@ constexpr double EXP_ERR = 1e-16;
 // (N = 6,000 FP64: 79 ms a call at 0, 72 at 1/2, 70 at 3/4 and 0.9.)
 constexpr double EXP_LEAD = 0.75;
 constexpr int EXP_STEPS = 4;
+// Phase grids of at least this many steps take their warm rows from expansions
+// (FP64 and MLCC_FP64_R32; the mixed form, whose blocks wait for each of their
+// open roots).  On coarser ones a root leaves its expansion, or its zero's
+// basin, nearly every row, and the passes alone are the faster way.  Time with
+// expansions over time without, the mean and the slowest of 13 to 15 fields,
+// batches and piece counts from 10 to 2,500 stars at 96 / 160 / 256 / 400 / 512
+// steps: FP64 1.25 1.03 0.94 0.75 0.66, slowest 1.8 1.4 1.6 1.7 1.5 (a rectangular
+// field of 40 stars), with multipole sums 1.28 1.02 0.88 0.67 0.58 and 1.6 1.4 1.5
+// 1.05 1.1; mixed 1.83 1.51 1.19 0.92 0.86 and 4.6 4.1 2.4 1.5 1.2, with multipole
+// sums 1.61 1.31 1.08 0.85 0.78 and 3.2 3.0 2.4 1.4 1.2.
+constexpr int64_t EXP_MIN_STEPS = 256, EXP_MIN_STEPS_MIXED = 400;
 
 struct Moments {
     double r[NMOM], i[NMOM];   // s_1 .. s_M
@@ -3511,10 +3522,18 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
                                p->star_sums == MLCC_STARS_FMM,
                                p->schedule == MLCC_SCHEDULE_PERSISTENT);
     if ((m / 2) % S) return fail(MLCC_ERR_INVALID, "n_subchains=%d must divide m/2", S);
+    // finished rows a warm row needs behind it to be solved by expansions: the
+    // centre row in FP64; in the mixed form the two after which rows start with a
+    // polish; and two in MLCC_FP64_R32, where one row a front keeps its FP32
+    // root-root sums
+    const int32_t xfrom =
+        p->predictor > 0 && m >= (mixed ? EXP_MIN_STEPS_MIXED : EXP_MIN_STEPS)
+            ? (p->precision == MLCC_FP64 ? 1 : 2)
+            : 0;
     // Grown pieces of the phase grid: the S subchains, or, where S is the
     // library's choice and rows come from expansions, fewer and longer ones.
     const std::vector<Piece> pieces =
-        plan_pieces(c->reals, m, S, p->n_subchains <= 0 && p->predictor > 0 && n_real == 1);
+        plan_pieces(c->reals, m, S, p->n_subchains <= 0 && xfrom > 0 && n_real == 1);
     const int NP = (int)pieces.size();
     int64_t L = 0;   // rows of the longest half
     for (const Piece &x : pieces) L = std::max({L, 2 * (x.hi - x.cen), 2 * (x.cen - x.lo)});
@@ -3530,11 +3549,6 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
     std::vector<int2> bmap;
     int64_t it_total = 0, bnd_total = 0, max_nr = 0;
     const int32_t warm_phase = mixed ? PH_F32 : PH_F64;
-    // finished rows a warm row needs behind it to be solved by expansions: the
-    // centre row in FP64; in the mixed form the two after which rows start with a
-    // polish; and two in MLCC_FP64_R32, where one row a front keeps its FP32
-    // root-root sums
-    const int32_t xfrom = p->predictor > 0 ? (p->precision == MLCC_FP64 ? 1 : 2) : 0;
     for (int r = 0; r < n_real; ++r) {
         const RealHost &h = c->reals[r];
         const SheetPoly sp = sheet_poly(h);
@@ -3718,7 +3732,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
                             (size_t)FMM_STRIPES * FMM_STRIPE_U64 * sizeof(uint64_t), c->stream));
     MLCC_HIP(hipMemsetAsync(c->passupd.p, 0, F * sizeof(int32_t), c->stream));
     MLCC_HIP(hipMemsetAsync(c->bad_row.p, 0x7f, F * sizeof(int32_t), c->stream));
-    const int32_t near_seeds = p->n_subchains <= 0 && p->predictor > 0;
+    const int32_t near_seeds = p->n_subchains <= 0 && xfrom > 0;
     if (equal)
         hipLaunchKernelGGL(seed_centres<double2>, dim3((unsigned)ngrid), dim3(64), 0, c->stream,
                            stars2, c->reals_d.as<Real>(), c->fronts.as<Front>(),
