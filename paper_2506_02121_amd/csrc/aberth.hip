@@ -1455,10 +1455,10 @@ __device__ __forceinline__ void spread_sums(Moments &S, int lane)
 
 // Moments about (zr, zi) for the lanes of `mask`; the other lanes keep theirs
 // where the mask holds few lanes and no multipole sums are on, and receive
-// moments about their own (zr, zi) otherwise.  Direct sums: the whole wave one
-// root after another when the mask holds few, else the star tiles for every
-// lane.  Multipole sums: each lane its cell's series and near stars; a lane
-// outside the grid sums over all stars.
+// moments about their own (zr, zi) otherwise, unless they are out of the grid.
+// Direct sums: the whole wave one root after another when the mask holds few,
+// else the star tiles for every lane.  Multipole sums: each lane its cell's
+// series and near stars; a lane of the mask outside the grid sums over all stars.
 template <bool EQUAL, bool FMM>
 __device__ __forceinline__ void sum_moments(const RoundArgs<typename StarRec<EQUAL>::T> &A,
                                             const BlockCtx<typename StarRec<EQUAL>::T> &B,
@@ -1662,10 +1662,10 @@ expand_rows(RoundArgs<typename StarRec<EQUAL>::T> A)
             // too far
             for (int ahead = it == 0; ahead >= 0; --ahead) {
                 const double ox = xr - cr, oy = xi - ci;
-                bool fresh = going && !(ox * ox + oy * oy <= reach2);
-                const unsigned long long mask = __ballot(fresh);
+                const bool out = going && !(ox * ox + oy * oy <= reach2);
+                const unsigned long long mask = __ballot(out);
                 if (!mask) break;
-                if (FMM || __popcll(mask) > SPARSE_MAX) fresh = valid;
+                const bool fresh = FMM || __popcll(mask) > SPARSE_MAX ? mine : out;
                 const double vx = pr - z1.x, vy = pi - z1.y, v2 = vx * vx + vy * vy;
                 const double lead =
                     ahead && reach2 > 0.0 && v2 > 0.0 ? EXP_LEAD * sqrt(reach2 / v2) : 0.0;
@@ -1678,8 +1678,8 @@ expand_rows(RoundArgs<typename StarRec<EQUAL>::T> A)
                     cr = tx;
                     ci = ty;
                     reach2 = moments_reach2(Mo);
-                    t_exp += 1;
-                    t_near += near;
+                    t_exp += out;   // those formed along with them are not counted
+                    t_near += out ? near : 0;
                 }
             }
             // f, f', f''/2 and f'''/6 in h = z0 - z by Horner's rule
