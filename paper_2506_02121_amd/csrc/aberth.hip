@@ -630,6 +630,28 @@ __device__ __forceinline__ void fmm_far(const FmmArgs &M, double zr, double zi, 
     q = M.wsum / (dd * dd * dd * dd);
 }
 
+// One far star's place in a cell's expansion, the next power of v, and the
+// cell's centre, as both kernels below form them: each product and sum is
+// written out, so that their rows agree to the last bit.
+__device__ __forceinline__ void p2l_star(double w, double dx, double dy, double &vr, double &vi)
+{
+    const double r2 = fma(dx, dx, dy * dy);
+    vr = w * dx / r2;
+    vi = -w * dy / r2;
+}
+
+__device__ __forceinline__ void p2l_next(double vr, double vi, double &pr, double &pi)
+{
+    const double tr = fma(vr, pr, -(vi * pi));
+    pi = fma(vr, pi, vi * pr);
+    pr = tr;
+}
+
+__device__ __forceinline__ double2 p2l_centre(double x0, double y0, double w, int ix, int iy)
+{
+    return make_double2(fma(w, ix + 0.5, x0), fma(w, iy + 0.5, y0));
+}
+
 // Local expansions of every cell from its far stars, one work group of 64
 // lanes per cell.  The stars go by in blocks of 64: lane k takes star k of
 // the block, forms v = w / (z_k - c) (0 for a star of the 3 x 3 near cells,
@@ -648,7 +670,7 @@ fmm_p2l(int32_t G, int32_t p, int32_t stride, double x0, double y0, double w, in
     __shared__ double wk[64];
     const int cell = blockIdx.x;
     const int ix = cell % G, iy = cell / G;
-    const double cx = x0 + (ix + 0.5) * w, cy = y0 + (iy + 0.5) * w;
+    const double2 ctr = p2l_centre(x0, y0, w, ix, iy);
     const int lane = threadIdx.x;
     double fr = 0.0, fi = 0.0, gr = 0.0, gi = 0.0, q = 0.0;
     for (int i0 = 0; i0 < n; i0 += 64) {
@@ -659,10 +681,8 @@ fmm_p2l(int32_t G, int32_t p, int32_t stride, double x0, double y0, double w, in
             const int sc = (int)st.w;
             const int sx = sc % G, sy = sc / G;
             if (abs(sx - ix) > 1 || abs(sy - iy) > 1) {
-                const double dx = st.x - cx, dy = st.y - cy;
-                const double r2 = dx * dx + dy * dy;
-                vr = w * dx / r2;
-                vi = -w * dy / r2;
+                const double dx = st.x - ctr.x, dy = st.y - ctr.y;
+                p2l_star(w, dx, dy, vr, vi);
                 wi = equal ? 1.0 : st.z;
                 const double ex = fmax(fabs(dx) - 0.5 * w, 0.0), ey = fmax(fabs(dy) - 0.5 * w, 0.0);
                 const double d2 = ex * ex + ey * ey;
@@ -672,9 +692,7 @@ fmm_p2l(int32_t G, int32_t p, int32_t stride, double x0, double y0, double w, in
         double pr = vr, pi = vi;
         for (int j = 0; j < stride; ++j) {
             pw[j * 65 + lane] = make_double2(pr, pi);
-            const double t = pr * vr - pi * vi;
-            pi = pr * vi + pi * vr;
-            pr = t;
+            p2l_next(vr, vi, pr, pi);
         }
         wk[lane] = wi;
         __syncthreads();
@@ -700,10 +718,12 @@ fmm_p2l(int32_t G, int32_t p, int32_t stride, double x0, double y0, double w, in
     if (lane == 0) qfar[cell] = q;
 }
 
-// The same rows bit for bit, a lane a cell, for many cells: the columns of a
-// field are numbered by its cold start, which follows the last bit of these
-// sums, so every order adds up its terms star by star as above.  A wave takes
-// 64 cells and KB of the orders from k0 on: the stars go by in tiles parked in
+// The same coefficients bit for bit, a lane a cell, for many cells: the columns
+// of a field are numbered by its cold start, which follows the last bit of these
+// sums, so every order adds up its terms star by star as above.  (The bounds
+// qfar add theirs in another order: they say how far a series or a Newton step
+// is trusted, and enter no FP64 cold start.)  A wave takes 64 cells and KB of the
+// orders from k0 on: the stars go by in tiles parked in
 // LDS, and their powers, by the same successive products, are added straight
 // into registers (6 FP64 instructions per order and star, 8 for unequal masses,
 // 4 for the orders before k0).  It is bound by that arithmetic on as many SIMDs
@@ -728,7 +748,8 @@ fmm_p2l_lanes(const P2lJob *__restrict__ jobs, const FmmArgs *__restrict__ recs)
     const int lane = threadIdx.x, G = M.G;
     const int cell = min(J.cell0 + lane, G * G - 1);
     const int ix = cell % G, iy = cell / G;
-    const double w = M.w, cx = fma(w, ix + 0.5, M.x0), cy = fma(w, iy + 0.5, M.y0);
+    const double w = M.w;
+    const double2 ctr = p2l_centre(M.x0, M.y0, w, ix, iy);
     double fr[KB], fi[KB], gr[KB], gi[KB], q = 0.0;
 #pragma unroll
     for (int k = 0; k < KB; ++k) fr[k] = fi[k] = gr[k] = gi[k] = 0.0;
@@ -750,10 +771,11 @@ fmm_p2l_lanes(const P2lJob *__restrict__ jobs, const FmmArgs *__restrict__ recs)
                 const double4 a = tile[min(t + c, cnt - 1)];
                 const int sx = __double2loint(a.w), sy = __double2hiint(a.w);
                 const bool far = t + c < cnt && (abs(sx - ix) > 1 || abs(sy - iy) > 1);
-                const double dx = a.x - cx, dy = a.y - cy;
-                const double r2 = fma(dx, dx, dy * dy);
-                vr[c] = far ? w * dx / r2 : 0.0;
-                vi[c] = far ? -w * dy / r2 : 0.0;
+                const double dx = a.x - ctr.x, dy = a.y - ctr.y;
+                double br, bi;
+                p2l_star(w, dx, dy, br, bi);
+                vr[c] = far ? br : 0.0;
+                vi[c] = far ? bi : 0.0;
                 wi[c] = EQUAL ? 1.0 : a.z;
                 pr[c] = vr[c];
                 pi[c] = vi[c];
@@ -764,11 +786,7 @@ fmm_p2l_lanes(const P2lJob *__restrict__ jobs, const FmmArgs *__restrict__ recs)
                     q += wi[c] / (d2 * d2);
                 }
             }
-            auto next = [&](int c) {
-                const double tr = fma(vr[c], pr[c], -(vi[c] * pi[c]));
-                pi[c] = fma(vr[c], pi[c], vi[c] * pr[c]);
-                pr[c] = tr;
-            };
+            auto next = [&](int c) { p2l_next(vr[c], vi[c], pr[c], pi[c]); };
 #pragma unroll 4
             for (int k = 0; k < J.k0; ++k) {
                 next(0);
