@@ -3,14 +3,16 @@
 // subchains (Sec. 4.3), in plain FP64 or in a mixed-precision form.
 //
 // Layout and scheduling (gfx950):
-//  * One lane per root, one 64-lane wavefront per work-group.  Each
-//    work-group owns 64 consecutive roots of one "front" (a growing end of a
-//    subchain).  Star positions and the other roots stream through LDS in
-//    tiles and are read back as wave-uniform broadcasts.
+//  * One lane per root; a wave takes a block of 64 consecutive roots of one
+//    "front" (a growing end of a subchain).  Star positions and the other
+//    roots stream through LDS in tiles of the wave's own and are read back as
+//    wave-uniform broadcasts.  Work groups have one wave in the round schedule
+//    and the expansion kernel, and up to eight in the persistent launch.
 //  * A block with only a few unconverged roots left (the last sweep of a row)
 //    works on them one at a time with the whole wave.
-//  * Jacobi double buffering: every kernel of a launch round reads iterate
-//    `cur` and writes `nxt`; the host alternates the two.
+//  * Jacobi double buffering: every pass reads one iterate and writes the
+//    other; a round alternates them for all fronts, the persistent launch for
+//    each front by itself.
 //  * Each front carries a phase.  FP64 mode: every row is FP64 Aberth sweeps.
 //    Mixed mode: cold starts are FP32 Aberth sweeps until the roots settle;
 //    warm rows with a chain prediction start directly with FP64 Newton
@@ -25,8 +27,12 @@
 //    kernel of their own, in which every block of 64 roots goes through the
 //    rows of its front by itself (expand_rows); passes take the cold starts,
 //    the rows next to them and the roots an expansion leaves open.
-//  * A single-work-group control kernel after every round advances the
-//    fronts (device-side; the host polls a status block one batch ahead).
+//    expand_check then tests the rows they finished, whose roots nothing kept
+//    apart, by their row identities, and expand_control moves the fronts on.
+//    Coarse phase grids take no expansions.
+//  * A control kernel after every round advances the fronts (device-side; the
+//    host polls a status block one batch ahead); in the persistent launch the
+//    work group that finishes a front's pass does.
 //  * Converged roots are mapped to the caustic in the same kernel.
 #include <algorithm>
 #include <chrono>
@@ -3218,15 +3224,14 @@ aberth_persistent(RoundArgs<typename StarRec<EQUAL>::T> A, Front *__restrict__ f
 // latency of its chain of dependent loads (cell, coefficients chunk by
 // chunk, near-cell ranges): measured on n10k at 4 waves per SIMD, a polish
 // pass occupies ~94k SIMD cycles whatever N, and the star part of a sweep
-// is priced the same; the root terms keep their cost.  In the persistent
-// mixed form a multipole polish pass goes on through up to 7 further rows
-// (polish_pass): a front then needs ~6x fewer passes in a row per row, which
-// an S sweep of n10k (S = 5 ... 40: 299, 288, 289, 303, 311, 340 ms at S = 5,
-// 8, 10, 20, 25, 40) and of the batched workload (S = 2 best) bear out.
-// All of this prices warm rows that sum over every star, as they did before
-// expand_rows; the choice stays what it was because the centre row of the
-// first of the S subchains is where the columns get their numbers (for one
-// field it decides nothing else, plan_pieces; a batch grows its S subchains).
+// is priced the same; the root terms keep their cost.
+// All of this prices warm rows that sum over every star in passes, among them
+// multipole polish passes of the persistent mixed form that went on through
+// further rows (fmm_rows_per_pass), as they no longer do: rows come from
+// expansions, priced by nothing here.  The choice stays what it was because the
+// centre row of the first of the S subchains is where the columns get their
+// numbers.  For one field it decides nothing else (plan_pieces), but a batch
+// grows its S subchains, and what S would be best for it now is not measured.
 struct TuneModel {
     double cold_sweeps = 27.0, rounds_per_row = 2.1, tail = 0.8, round_us = 40.0;
     double clock_hz = 2.4e9, simds = 1024.0;
@@ -3307,13 +3312,17 @@ struct Piece {
 // up a call, and no more of them are made than keep the device full: pieces
 // whose fronts hold COLD_BLOCKS blocks of 64 roots between them.  The first
 // one keeps the centre row of the first of S equal subchains, whose cold start
-// numbers the columns.  Measured, ms a call, with one piece per subchain / 2048 /
-// 4096 / 6144 blocks: N = 6,000 FP64 104 / 112 / 73 / 77 (a few long pieces wait
-// for their stuck blocks); N = 4,099 mixed 49 / 32 / 36 / 38; N = 1,000 FP64 14.3 /
-// 9.6 / 11.2 / 12.6; N = 3,000 FP64 with multipole sums 22.2 / 15.7 / 17.2 / 18.5;
-// N = 10,000 mixed with them 67 / 61 / 62 / 65; rectangular N = 437 6.9 / 5.4 / 6.0 /
-// 6.9.  Batches keep their subchains: their largest fields' pieces would set the
-// time (40 fields mixed 65 / 197 / 134 / 112).
+// numbers the columns.  Measured, ms a call for each of two fields, with 2048 /
+// 3072 / 4096 / 6144 blocks: N = 6,000 FP64 52 47 / 44 47 / 43 43 / 46 44; N = 4,099
+// mixed 23 41 / 24 37 / 26 36 / 30 34; N = 10,000 mixed with multipole sums 43 66 /
+// 44 57 / 45 51 / 46 51; N = 5,000 FP64 with them 25 28 / 21 22 / 20 22 / 20 21; N = 3,000
+// 11.9 9.6 / 11.4 10.4 / 10.8 10.4 / 11.8 10.7; N = 1,000 FP64 5.4 5.2 / 6.1 5.6 / 5.8 6.3 / 7.4
+// 6.9; N = 300 2.1 1.7 / 2.5 1.9 / 2.6 2.3 / 2.9 2.5; rectangular N = 437 4.2 5.2 / 4.3 4.7 / 4.4
+// 5.0 / 5.2 5.8.  A few long pieces wait for their stuck blocks, most in the largest
+// fields, and how long differs from field to field; 4096 is near the best for all
+// of them but the small ones, which 2048 serves 10 to 25% faster.  Batches keep
+// their subchains: their largest fields' pieces would set the time (40 fields mixed
+// 65 ms with one piece per subchain, 197 / 134 / 112 with 2048 / 4096 / 6144 blocks).
 #ifndef MLCC_COLD_BLOCKS
 #define MLCC_COLD_BLOCKS 4096
 #endif
@@ -3715,8 +3724,7 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
     MLCC_TRY(c->fmm_tally.reserve((size_t)FMM_STRIPES * FMM_STRIPE_U64 * sizeof(uint64_t)));
     MLCC_TRY(c->etab.reserve((size_t)(m + 1) * sizeof(double2)));
     MLCC_TRY(c->bnd.reserve((size_t)std::max<int64_t>(bnd_total, 1) * sizeof(double2)));
-    MLCC_TRY(c->next_row.reserve((size_t)2 * nblocks * sizeof(int32_t)));
-    MLCC_TRY(c->bad_row.reserve((size_t)F * sizeof(int32_t)));
+    MLCC_TRY(c->next_row.reserve((size_t)(2 * nblocks + F) * sizeof(int32_t)));
     if (mixed) {
         MLCC_TRY(c->vieta.reserve((size_t)2 * nblocks * sizeof(double4)));
         MLCC_TRY(c->errbuf.reserve((size_t)it_total * sizeof(double)));
@@ -3767,7 +3775,8 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
     MLCC_HIP(hipMemsetAsync(c->fmm_tally.p, 0,
                             (size_t)FMM_STRIPES * FMM_STRIPE_U64 * sizeof(uint64_t), c->stream));
     MLCC_HIP(hipMemsetAsync(c->passupd.p, 0, F * sizeof(int32_t), c->stream));
-    MLCC_HIP(hipMemsetAsync(c->bad_row.p, 0x7f, F * sizeof(int32_t), c->stream));
+    int32_t *const bad_row = c->next_row.as<int32_t>() + 2 * nblocks;
+    if (xfrom > 0) MLCC_HIP(hipMemsetAsync(bad_row, 0x7f, F * sizeof(int32_t), c->stream));
     const int32_t near_seeds = p->n_subchains <= 0 && xfrom > 0;
     if (equal)
         hipLaunchKernelGGL(seed_centres<double2>, dim3((unsigned)ngrid), dim3(64), 0, c->stream,
@@ -4137,11 +4146,11 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
         hipLaunchKernelGGL(expand_check, dim3((unsigned)F, check_groups), dim3(check_threads), 0, rs,
                            c->fronts.as<Front>(), c->reals_d.as<Real>(), c->etab.as<double2>(),
                            c->next_row.as<int32_t>(), roots_re, roots_im, c->bnd.as<double2>(),
-                           c->bad_row.as<int32_t>());
+                           bad_row);
         hipLaunchKernelGGL(expand_control, dim3((unsigned)F), dim3(64), 0, rs,
                            c->fronts.as<Front>(), c->reals_d.as<Real>(), c->next_row.as<int32_t>(),
-                           c->next_row.as<int32_t>() + nblocks, p->predictor, xfrom,
-                           c->bad_row.as<int32_t>(), dctl, dq, dtasks, dseq, qmask);
+                           c->next_row.as<int32_t>() + nblocks, p->predictor, xfrom, bad_row,
+                           dctl, dq, dtasks, dseq, qmask);
         hipLaunchKernelGGL(expand_gather, grid, dim3(64), 0, rs, c->fronts.as<Front>(),
                            c->reals_d.as<Real>(), c->bmap.as<int2>(), c->next_row.as<int32_t>(),
                            roots_re, roots_im, c->bnd.as<double2>(), c->iter[0].as<double2>(),

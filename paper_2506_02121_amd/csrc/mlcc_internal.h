@@ -197,9 +197,8 @@ struct Ctx {
     DevBuf fronts;    // Front[F]
     DevBuf counts;    // int32[F]: unflagged roots after the last sweep
     DevBuf passupd;   // int32[F]: roots updated by the last round's pass
-    DevBuf next_row;  // int32[2 * blocks]: expansions: each block's next row, and whether it is
-                      // stuck there
-    DevBuf bad_row;   // int32[F]: expansions: first settled row whose identities fail
+    DevBuf next_row;  // int32[2 * blocks + F]: expansions: each block's next row, whether it is
+                      // stuck there, and each front's first settled row whose identities fail
     DevBuf control;   // Control
     DevBuf fmm_tally; // uint64[FMM_STRIPES * FMM_STRIPE_U64]: multipole tallies
     DevBuf etab;      // double2[m + 1]: (1 - kappa_s) e^{-i phi_j}
