@@ -56,3 +56,27 @@ def test_rows_hold_each_root_once(mlcc, n, m_steps, seeds, schedule, precision):
         # pairs every root of a row with one of the oracle's, or fails
         _, ratio = parity.compare_row_sets(rows, ref, parity.root_bound(f, slope))
         assert ratio <= 1.0
+
+
+@pytest.mark.parametrize("schedule", ["persistent", "rounds"])
+@pytest.mark.parametrize("precision", ["fp64", "fp64_r32"])
+def test_rows_whose_identities_fail(mlcc, schedule, precision):
+    """Cutoffs of 1e-3 leave some roots of passes that far from their zeros: rows
+    that hold them beside roots from expansions fail their identities, and all their
+    roots take Aberth steps; the rows after them start anew."""
+    print("[case]", schedule, precision, flush=True)
+    m_steps, tol = 600, 1e-3
+    f = fields.random_field(3, 300, kappa_star=0.45, kappa_s=0.0, gamma=0.3, masses="salpeter")
+    ctx = mlcc.Context(0)
+    ctx.set_lenses(dev(f.x), dev(f.y), dev(f.m), f.kappa_s, f.gamma)
+    re, im, _, s, _ = ctx.find_critical_curves(m_steps, schedule=schedule, precision=precision,
+                                               tol_step=tol, tol_inv_mu=tol)
+    fine = ctx.find_critical_curves(m_steps, predictor=0)
+    rows = re.cpu().numpy() + 1j * im.cpu().numpy()
+    ref = fine[0].cpu().numpy() + 1j * fine[1].cpu().numpy()
+    ctx.close()
+    assert s["rows_fallback"] > 0
+    slope = np.stack([oracle.eval_F(f, oracle.phase(j, m_steps), ref[j])[1]
+                      for j in range(m_steps + 1)])
+    _, ratio = parity.compare_row_sets(rows, ref, parity.root_bound(f, slope, tol))
+    assert ratio <= 1.0
