@@ -8,10 +8,10 @@ image of every root mapped in the same pass) + caustic_crossings +
 caustic_distances on one seeded synthetic field whose inputs are already in
 HBM, in the paper's double precision.  Prints one JSON line:
   value           roots/s = m * 2N / (seconds per step)
-  roofline        the root finder's dominant kernel (the persistent launch
-                  that runs every pass, by default): algorithmic FLOP per
-                  launch / its HIP-event-timed duration, against the FP64
-                  vector peak
+  roofline        the root finder (by default the interval of its launches, the
+                  persistent ones that run the passes and the expansions between
+                  them): algorithmic FLOP per call / its HIP-event-timed
+                  duration, against the FP64 vector peak
   accuracy        the timed run's roots and caustics against oracle rows
   forms           the other forms on the same field, each with its own few
                   steps: FP32 root-root sums in warm rows, mixed precision
@@ -205,16 +205,22 @@ def kernel_line(stats, name, flop_keys, ms_key, n_key, dtype):
             "launches": launches}
 
 
+# the persistent schedule's line: every launch of a call together
+PERSISTENT = "aberth_persistent+expand_rows"
+
+
 def root_kernels(stats):
-    """Rooflines of the root finder's launches.  The persistent launch runs
-    every pass kind; its FLOP are split by the precision they run in."""
+    """Rooflines of the root finder's launches.  In the persistent schedule one
+    line for all of a call's, persistent launches and expansions in turn, timed from
+    the first to the end of the last ("launches" counts such intervals); its FLOP
+    are split by the precision they run in."""
     f64 = sum(s["algorithmic_flop"] + s["algorithmic_flop_polish"] for s in stats)
     f32 = sum(s["algorithmic_flop_f32"] + s["algorithmic_flop_sweep_roots"] for s in stats)
     if any(s["persistent_launches"] for s in stats):
         ms = sum(s["persistent_ms"] for s in stats)
         launches = sum(s["persistent_launches"] for s in stats)
         achieved = (f64 + f32) / (ms * 1e-3) / 1e12 if ms > 0 else None
-        return [{"kernel": "aberth_persistent", "dtype": "f64" if f32 == 0 else "f64+f32",
+        return [{"kernel": PERSISTENT, "dtype": "f64" if f32 == 0 else "f64+f32",
                  "achieved": achieved, "peak": FP64_VECTOR_PEAK_TFLOPS,
                  "frac": achieved / FP64_VECTOR_PEAK_TFLOPS if achieved else None,
                  "time_s": ms * 1e-3, "avg_launch_ms": ms / launches, "launches": launches,
@@ -423,7 +429,7 @@ def single_block(args, wl, precision, steps, warmup, forms, directional, oracle_
     stages = stage_ms(stats)
     s0 = stats[-1]
     rf = roofline(stats, wl.name, args.star_sums)
-    if rf["kernel"] == "aberth_persistent":
+    if rf["kernel"] == PERSISTENT:
         rf["measured_peak"] = measured_peaks(rf["kernels"][0])
     rf["flop_per_root_update"] = 29 * n + 10 * (n_r - 1)
     ncc_h = ncc.cpu().numpy()

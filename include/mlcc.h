@@ -270,19 +270,23 @@ typedef struct {
     double match_maxdist;    /* largest distance between paired duplicate roots */
     double sweep_ms;         /* GPU time of FP64 sweep launches that did work (timing != 0) */
     double sweep_f32_ms;     /* same, FP32 sweep launches */
-    double polish_ms;        /* same, polish launches */
+    double polish_ms;        /* same, polish launches (the expansions between rounds are in none
+                                of these) */
     int64_t sweep_launches, sweep_f32_launches, polish_launches;   /* launches that did work */
     double algorithmic_flop; /* FP64 sweeps, FP64 part: root_updates * 29 N (star terms) plus
                                 10 (2N - 1) per update that sums its root-root terms in FP64;
                                 rows from expansions: their star moments (per star term 133,
                                 with multipole sums per near star, plus 112 p for the series)
-                                and 508 per step; FMA = 2, add/mul/reciprocal = 1 */
+                                where a root needs a new expansion, and 508 per step;
+                                FMA = 2, add/mul/reciprocal = 1 */
     double algorithmic_flop_f32;    /* FP32 sweeps: root_updates_f32 * (29 N + 10 (2N - 1)) */
-    double algorithmic_flop_polish; /* polish: polish_updates * 29 N (star terms only) */
+    double algorithmic_flop_polish; /* polish: 29 N per update (star terms only), and the mixed
+                                form's rows from expansions, counted as above */
     double persistent_ms;    /* MLCC_SCHEDULE_PERSISTENT: GPU time of the launches that run the
                                 passes and the expansions, from the first to the end of the last
                                 (timing != 0); the per-kind times above stay 0 */
-    int64_t persistent_launches;    /* 1 with MLCC_SCHEDULE_PERSISTENT, else 0 */
+    int64_t persistent_launches;    /* 1 with MLCC_SCHEDULE_PERSISTENT, however many launches
+                                the call took, else 0 */
     double algorithmic_flop_sweep_roots; /* FP64 sweeps, FP32 part: 10 (2N - 1) per update of
                                 a warm MLCC_FP64_R32 row that sums its root-root terms (they
                                 run in FP32); 0 for MLCC_FP64 */
