@@ -2782,7 +2782,8 @@ __global__ void expand_begin(Control *__restrict__ ctl, PQueue *q)
 // Bound by the latency of a row: a few reads a lane, then the reduction.  One
 // work group of four waves a row and eight separate reductions took 163 us a
 // launch for 86 fields of 1,088 steps; a wave a row and one reduction in halves
-// take 70 (2.8 and 1.2 ms a call; N = 6,000, 1.9 GB of roots: 0.9 ms).  In the mixed
+// take 70, and 48 with a work group for every eight rows of a front (2.8, 1.2 and
+// 0.8 ms a call; N = 6,000, 1.9 GB of roots: 0.9 ms).  In the mixed
 // form it takes the place of row sums formed in the expansion kernel, which held
 // a block to 1,024 rows ahead of its front and took up to 512 MiB, and of their
 // check one row at a time: N = 10,000 with multipole sums 52.0 -> 44.9 ms, of which
@@ -4121,10 +4122,13 @@ mlcc_status find_critical_curves_impl(Ctx *c, const mlcc_cc_params *p, double *r
     };
 
     // expand_check: a wave a row while a lane then has few reads, else a work group
-    // of four; as many as are resident at once
+    // of four.  As many as are resident at once, or, as later launches find all
+    // their rows in a few fronts, one for every eight rows a front may have (40
+    // fields 1.9 -> 0.8 ms a call, 97 small ones 1.3 -> 0.6).
     const unsigned check_threads = max_nr > 4096 ? CONTROL_THREADS : 64;
+    const int64_t resident = 8192 * 64 / check_threads, front_rows = L / 2 + 1;
     const unsigned check_groups = (unsigned)std::max<int64_t>(
-        1, std::min<int64_t>(L / 2 + 1, (int64_t)(8192 * 64 / check_threads) / F));
+        1, std::min(front_rows, std::max(resident / F, std::min(ceil_div(front_rows, 8), 8 * resident / F))));
     // The expansions over every parked front, and what comes of them: fronts
     // that passes take over, and fronts still parked.
     auto run_expansions = [&](int &active, int &parked) -> mlcc_status {
